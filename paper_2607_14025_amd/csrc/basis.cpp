@@ -85,7 +85,9 @@ std::string build_basis(const CellParams& c, HostBasis& hb, bool sphere_only) {
       ++hb.ncol;
     }
   if (start != hb.npw) return "internal error: column count mismatch";
-  hb.ncol_pad = (hb.ncol + kColPad - 1) / kColPad * kColPad;
+  // at least two padding columns: where a line has no column the plane kernels read the first (the
+  // inverse x pass writes zeros to it) and write the second
+  hb.ncol_pad = (hb.ncol + 1 + kColPad) / kColPad * kColPad;
   hb.col_start.resize(hb.ncol_pad, 0);
   hb.col_len.resize(hb.ncol_pad, 0);
   hb.col_xmin.resize(hb.ncol_pad, 0);
@@ -94,6 +96,7 @@ std::string build_basis(const CellParams& c, HostBasis& hb, bool sphere_only) {
   hb.nza = (int)hb.zl.size();
   hb.zact_lo = nm;
   hb.zact_hi = N - nm;
+  hb.ymax.assign(hb.nza, 0);
   hb.ycol.assign((size_t)hb.nza * N, -1);
   for (int f = 0; f < hb.nza; ++f) {
     const int iz = hb.zl[f];
@@ -101,7 +104,9 @@ std::string build_basis(const CellParams& c, HostBasis& hb, bool sphere_only) {
     for (int iy = 0; iy < N; ++iy) {
       const int ny = (2 * iy < N) ? iy : iy - N;
       if (ny < -nm || ny > nm) continue;
-      hb.ycol[(size_t)iy * hb.nza + f] = colid[(ny + nm) * (2 * nm + 1) + (nz + nm)];
+      const int c = colid[(ny + nm) * (2 * nm + 1) + (nz + nm)];
+      hb.ycol[(size_t)iy * hb.nza + f] = c;
+      if (c >= 0) hb.ymax[f] = std::max(hb.ymax[f], ny < 0 ? -ny : ny);
     }
   }
 

@@ -15,7 +15,7 @@
 #include <algorithm>
 #include <mutex>
 
-#include "fft_dev.hpp"
+#include "fft_half.hpp"
 #include "kernels.hpp"
 
 namespace stern {
@@ -746,6 +746,145 @@ __global__ __launch_bounds__(64 * W) void k_plane_hw(Z<T>* __restrict__ pen, con
   }
 }
 
+// ---- H apply with half-transforms in registers (even N) ----
+//
+// A workgroup takes the same plane ix of nv vectors; only their active z lines are in LDS, as
+// Q[v][f][y]. Two neighbouring lanes hold one line: the y pass has nv nza lines, the z pass nv N
+// rows, each transformed whole in registers (fft_half.hpp), the z pass with V_loc between its two
+// directions. A pair of transforms costs one LDS write and one read of a line instead of an
+// exchange, a twiddle load and index arithmetic per stage, and every address is a lane base plus
+// constants.
+//
+// Bound by the vector ALU: counters put it at 85% of the issue slots at N = 64 and 72 in FP32 (FP64
+// instructions take about twice the slots, and the share is the same), 70% at N = 128, where 200
+// registers leave two waves per SIMD. The scheduling barriers of fft_half.hpp hold the registers near
+// the 2 M of the line itself: without them the compiler needs twice as many and spills. Microseconds
+// for 1,024 vectors, against the two-stage kernel below (k_plane_hw):
+//     N     FP32           FP64             N     FP32           FP64
+//    24     96 (190)      140 (287)        72    1,270 (1,690)  2,480 (3,060)
+//    36    178 (370)      298 (690)        96    3,170 (4,040)  8,640 (10,080)
+//    48    346 (549)      738 (1,180)     108    5,550 (7,370) 11,890 (13,950)
+//    54    615 (903)    1,280 (1,550)     128    8,300 (9,880) 18,290 (23,280)
+// Odd N (9, 27, 81) has no two lanes to a line and stays with the two-stage kernel.
+template <int N, class T>
+struct PlaneHCfg {
+  using H = HalfFft<N, T>;
+  // vectors to a workgroup of 4 waves, one on each SIMD: their 2 NV N z lanes and 2 NV nza y lanes fill
+  // whole waves to 80% or more on most grids, while two or more workgroups still fit in LDS
+  static constexpr int NV = N >= 108 || (N >= 96 && sizeof(T) == 8) ? 1 : N >= 54 ? 2 : N >= 32 ? 4 : N >= 16 ? 8 : 16;
+  static constexpr int W = 4, NT = 64 * W;
+  // lines Q[f][.] are written and read by lane pairs, f apart: 2 mod 4 spreads them over the banks
+  static constexpr int QLD = N + (6 - N % 4) % 4;
+  // waves per SIMD that the M-point working set (2 M registers of T) leaves room for
+  static constexpr int WPS = sizeof(T) == 4 ? (H::M <= 36 ? 4 : H::M <= 48 ? 3 : 2) : (H::M <= 12 ? 4 : H::M <= 24 ? 3 : H::M <= 36 ? 2 : 1);
+};
+template <int N, class T>
+constexpr size_t planeh_lds_bytes(int nv, int nza) {
+  using C = PlaneHCfg<N, T>;
+  return ((size_t)nv * nza * C::QLD + 2 * HalfFft<N, T>::TW) * sizeof(Z<T>) + 2 * HalfFft<N, T>::TW * sizeof(int);
+}
+
+template <int N, class T>
+__global__ __launch_bounds__((PlaneHCfg<N, T>::NT), (PlaneHCfg<N, T>::WPS)) void k_plane_half(
+    Z<T>* __restrict__ pen, const int* __restrict__ vidx, int nvec, int nv, const T* __restrict__ vt,
+    const int* __restrict__ ycol, FftGeom g) {
+  using C = PlaneHCfg<N, T>;
+  using H = HalfFft<N, T>;
+  constexpr int M = H::M, K = H::K, QLD = C::QLD;
+  extern __shared__ unsigned char smem_raw[];
+  const int nza = g.nza, nm = g.zact_lo, tid = threadIdx.x;
+  Z<T>* Q = reinterpret_cast<Z<T>*>(smem_raw);
+  Z<T>* tws = Q + (size_t)nv * nza * QLD;
+  H::twiddles(tws, twtab<T>(g), nm, tid, C::NT);
+  // columns of (n_y, n_z = 0), n_y = 0..K, then n_y = 0..-K; those of one n_y are consecutive in n_z
+  int* cys = reinterpret_cast<int*>(tws + 2 * H::TW);
+  for (int i = tid; i < 2 * H::TW; i += C::NT) {
+    const int n = i % H::TW;
+    cys[i] = ycol[(size_t)(i < H::TW || n == 0 ? n : N - n) * nza];
+  }
+  __syncthreads();
+  const int odd = tid & 1;
+  const Z<T>* tl = tws + odd * H::TW;
+  const int* cl = cys + odd * H::TW;
+  if (g.live) nvec = min(nvec, *g.live);
+  if (nvec <= 0) return;
+  const int ngrp = (nvec + nv - 1) / nv;
+  const long total = (long)N * ngrp;
+  // neither pass fills the 4 waves evenly: which of them starts a pass moves on from group to group,
+  // so that every SIMD gets the same work
+  const int yw = (2 * nv * nza + 63) / 64, zw = (2 * nv * N + 63) / 64;
+  int ry = 0, rz = 0;
+  for (long q = blockIdx.x; q < total; q += gridDim.x) {
+    const int ix = (int)(q / ngrp), b0 = (int)(q - (long)ix * ngrp) * nv;
+    ry = (ry + yw) % C::W;
+    rz = (rz + zw) % C::W;
+    int tq = (tid + 64 * ry) % C::NT, tz = (tid + 64 * rz) % C::NT;
+    asm volatile("" : "+v"(tq), "+v"(tz));  // what hangs on them would otherwise be kept in registers
+    // ---- inverse y ----
+    for (int it = tq; it < 2 * nv * nza; it += C::NT) {
+      const int f = (it >> 1) % nza, b = b0 + (it >> 1) / nza;
+      const int nz = f <= nm ? f : f - nza;
+      const int ym = b < nvec ? g.ymax[f] : -1;
+      const int vec = b < nvec ? (vidx ? vidx[b] : b) : 0;
+      const Z<T>* __restrict__ tp = pen + ((size_t)vec * N + ix) * g.ncol_pad;
+      Z<T> v[M];
+      // outside the disk: the zero column behind the last one
+      H::to_points(v, tl, [&](int n) {
+        int c = (n < 0 ? cys[H::TW - n] : cys[n]) + nz;
+        asm volatile("" : "+v"(c));  // keeps the selection below a selection: a branch per frequency otherwise
+        return tp[(n < 0 ? -n : n) <= ym ? c : g.ncol];
+      });
+      Z<T>* q0 = Q + (size_t)(it >> 1) * QLD + odd;
+#pragma unroll
+      for (int k = 0; k < M; ++k) q0[2 * k] = v[k];
+    }
+    __syncthreads();
+    // ---- z: inverse, x V_loc, forward ----
+    const T* __restrict__ vx = vt + (size_t)ix * N * N;
+    for (int it = tz; it < 2 * nv * N; it += C::NT) {
+      const int y = (it >> 1) % N;
+      Z<T>* qr = Q + (size_t)((it >> 1) / N) * nza * QLD + y;
+      const T* __restrict__ vr = vx + (size_t)odd * N + y;
+      Z<T> v[M];
+      Z<T>* qn = qr + (size_t)nza * QLD;
+      H::to_points(v, tl, [&](int n) { return n < 0 ? qn[n * QLD] : qr[n * QLD]; });
+#pragma unroll
+      for (int k = 0; k < M; ++k) {
+        v[k] = zscale(v[k], vr[2 * k * N]);
+        if (k % 12 == 11) __builtin_amdgcn_sched_barrier(0);
+      }
+      // n > nm writes to a line of the other sign, which a later (smaller) n overwrites
+      Z<T>* qw = odd ? qn - (K + 1) * QLD : qr + (K + 1) * QLD;
+      const int step = odd ? QLD : -QLD;
+      H::to_freqs(v, tl, odd, [&](int n, Z<T> x) {
+        qw += step;
+        if (n == 0) qw = qr;
+        *qw = x;
+      });
+    }
+    __syncthreads();
+    // ---- forward y ----
+    for (int it = tq; it < 2 * nv * nza; it += C::NT) {
+      const int f = (it >> 1) % nza, b = b0 + (it >> 1) / nza;
+      const int nz = f <= nm ? f : f - nza;
+      const int ym = b < nvec ? g.ymax[f] : -1;
+      const int vec = b < nvec ? (vidx ? vidx[b] : b) : 0;
+      Z<T>* __restrict__ tp = pen + ((size_t)vec * N + ix) * g.ncol_pad;
+      const Z<T>* q0 = Q + (size_t)(it >> 1) * QLD + odd;
+      Z<T> v[M];
+#pragma unroll
+      for (int k = 0; k < M; ++k) v[k] = q0[2 * k];
+      // outside the disk: the second padding column, which nothing reads
+      H::to_freqs(v, tl, odd, [&](int n, Z<T> x) {
+        int c = cl[n] + nz;
+        asm volatile("" : "+v"(c));
+        tp[n <= ym ? c : g.ncol + 1] = x;
+      });
+    }
+    __syncthreads();  // the next group rewrites Q
+  }
+}
+
 // Right-hand sides of one band for every field of a batch: workgroup (ix, bb) keeps
 // plane ix of psi_{v0 + bb}(r) in registers (the items of its first stage) and, for
 // each field pl, forms psi * dv, transforms the plane and writes the pencils of solve
@@ -1300,6 +1439,30 @@ int blocks_per_cu(const void* kernel, int nt, size_t lds) {
 }
 }  // namespace
 
+// grids that run k_plane_half; its z pass reads Q at lines up to K, which are there when the sphere
+// reaches half as far as the grid allows (an explicit fft_n far above the cutoff's need not)
+template <int NN, class T>
+constexpr bool half_grid() {
+  return NN % 2 == 0;
+}
+template <int NN, class T>
+constexpr bool half_plane(int nm) {
+  return half_grid<NN, T>() && 2 * nm >= HalfFft<NN, T>::K;
+}
+
+template <int NN, class T>
+void launch_plane_half_n(const FftGeom& g, Z<T>* pen, const int* vidx, int nvec, const T* vt, hipStream_t st) {
+  using C = PlaneHCfg<NN, T>;
+  // few vectors: fewer to a workgroup, so that there is a group for every CU
+  const int nv = (int)std::max<long>(1, std::min<long>(C::NV, (long)NN * nvec / g.n_cu));
+  const size_t lds = planeh_lds_bytes<NN, T>(nv, g.nza);
+  const void* kp = (const void*)k_plane_half<NN, T>;
+  const int per_cu = blocks_per_cu(kp, C::NT, lds);
+  const long groups = (long)NN * ((nvec + nv - 1) / nv);
+  const int grid = (int)std::min<long>(groups, (long)g.n_cu * per_cu);
+  k_plane_half<NN, T><<<grid, C::NT, lds, st>>>(pen, vidx, nvec, nv, vt, g.ycol, g);
+}
+
 template <int NN, class T, bool PF>
 void launch_plane_hw_n(const FftGeom& g, Z<T>* pen, const int* vidx, int nvec, const T* vt, hipStream_t st) {
   constexpr int W = PlaneShape<NN, T>::W, ZR = PlaneShape<NN, T>::ZR;
@@ -1320,7 +1483,9 @@ void launch_plane_hw(const FftGeom& g, Z<T>* pen, const int* vidx, int nvec, con
   STERN_DISPATCH_N(g.N, ({
                      if (prefetch)
                        launch_plane_hw_n<NN, T, true>(g, pen, vidx, nvec, vt, st);
-                     else
+                     else if (half_plane<NN, T>(g.zact_lo)) {
+                       if constexpr (half_grid<NN, T>()) launch_plane_half_n<NN, T>(g, pen, vidx, nvec, vt, st);
+                     } else
                        launch_plane_hw_n<NN, T, false>(g, pen, vidx, nvec, vt, st);
                    }));
 }

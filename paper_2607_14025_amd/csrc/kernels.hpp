@@ -22,6 +22,7 @@ struct FftGeom {
   const int* col_pos;       // [ncol] iy * N + iz of the column in a yz plane
   const int* zl;            // [nza] iz of the active lines
   const int* ycol;          // [N][nza] pencil column of (iy, zl[f]), -1 outside the sphere's disk
+  const int* ymax;          // [nza] largest |n_y| on the line
   int zact_lo, zact_hi;     // active lines are iz <= zact_lo or iz >= zact_hi
   int n_cu;                 // compute units of the device (persistent launches)
   const double* g2h;        // [npw_pad] |G|^2 / 2 in column order (0 for padding)

@@ -154,7 +154,7 @@ struct stern_system {
   HostBasis hb;
   int n_atoms = 0, natoms_pad = 0;
   // static device data
-  DBuf col_start, col_len, col_xmin, col_pos, zl, ycol, g2h, tw64, tw32, v_r, v_r32, v_t, v_t32, kb, perm;
+  DBuf col_start, col_len, col_xmin, col_pos, zl, ycol, ymax, g2h, tw64, tw32, v_r, v_r32, v_t, v_t32, kb, perm;
   // yz-plane kernel of the H apply per precision: 0 full-plane, 1 compact wave-local
   int plane_var64 = 1, plane_var32 = 1;
   // split-K workgroup targets of the FP64 and split-BF16 reduces (0 = default)
@@ -228,6 +228,7 @@ struct stern_system {
     g.col_pos = col_pos.as<int>();
     g.zl = zl.as<int>();
     g.ycol = ycol.as<int>();
+    g.ymax = ymax.as<int>();
     g.zact_lo = hb.zact_lo;
     g.zact_hi = hb.zact_hi;
     g.n_cu = n_cu;
@@ -252,6 +253,7 @@ struct stern_system {
     g.col_pos = d_col_pos.as<int>();
     g.zl = d_zl.as<int>();
     g.ycol = d_ycol.as<int>();
+    g.ymax = nullptr;
     g.zact_lo = hbd.zact_lo;
     g.zact_hi = hbd.zact_hi;
     g.n_cu = n_cu;
@@ -275,6 +277,7 @@ struct stern_system {
     g.col_pos = c_col_pos.as<int>();
     g.zl = c_zl.as<int>();
     g.ycol = c_ycol.as<int>();
+    g.ymax = nullptr;
     g.zact_lo = hbc.zact_lo;
     g.zact_hi = hbc.zact_hi;
     g.n_cu = n_cu;
@@ -285,7 +288,7 @@ struct stern_system {
   }
 
   void release_all() {
-    DBuf* all[] = {&ycol, &tw32, &v_r32, &col_start, &col_len,  &col_xmin, &col_pos, &zl,       &g2h,     &tw64,     &v_r,      &kb,
+    DBuf* all[] = {&ycol, &ymax, &tw32, &v_r32, &col_start, &col_len,  &col_xmin, &col_pos, &zl,       &g2h,     &tw64,     &v_r,      &kb,
                    &perm,      &psi,      &psi_r,    &wx,      &wr,       &wp,      &wq,       &wz,       &wb,
                    &pen,       &cpart,    &cmat,     &sv_eps,  &sv_invT,  &sv_band, &sv_pert,  &sv_bb,    &sv_rz,
                    &sv_rr,     &sv_flag,  &sv_iters, &sv_tres, &list_act, &list_f,  &pert_out, &dv_dev,   &dn_dev,
@@ -1284,6 +1287,7 @@ int stern_init_system(const stern_cell* cell, const stern_runtime* rt, stern_sys
     CHECKED(upload(S->col_pos, hb.col_pos.data(), hb.col_pos.size() * sizeof(int), st));
     CHECKED(upload(S->zl, hb.zl.data(), hb.zl.size() * sizeof(int), st));
     CHECKED(upload(S->ycol, hb.ycol.data(), hb.ycol.size() * sizeof(int), st));
+    CHECKED(upload(S->ymax, hb.ymax.data(), hb.ymax.size() * sizeof(int), st));
     CHECKED(upload(S->g2h, hb.g2h.data(), hb.g2h.size() * sizeof(double), st));
     {  // -G of every coefficient in column order (the sphere is symmetric under G -> -G)
       std::map<std::array<int32_t, 3>, int> canon;
