@@ -7,7 +7,10 @@
 // groups of a wavefront cover eight complex k per MFMA quadruple. Because the
 // k order inside a reduction is free, the A and B fragments only have to agree
 // on which k each lane group carries.
+#include <algorithm>
+
 #include "kernels.hpp"
+#include "stern.h"
 
 namespace stern {
 
@@ -25,11 +28,12 @@ constexpr int kGemmThreads = 256;  // 4 waves, 2 x 2 arrangement of 32 x 32 wave
 __global__ __launch_bounds__(kGemmThreads) void k_zgemm_reduce(const Z64* __restrict__ A, int M_pad,
                                                                const Z64* __restrict__ X, int ldx,
                                                                const int* __restrict__ xidx, int ncols, int K,
-                                                               int kchunk, Z64* __restrict__ cpart) {
+                                                               int kchunk, Z64* __restrict__ cpart, int M) {
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int l16 = lane & 15, g = lane >> 4;
   const int m0 = blockIdx.x * 64 + (wave & 1) * 32;
   const int n0 = blockIdx.y * 64 + (wave >> 1) * 32;
+  if (m0 >= M || n0 >= ncols) return;  // padding only (no barrier, no LDS)
   const int split = blockIdx.z;
   const int kb = split * kchunk;
   const int ke = min(K, kb + kchunk);
@@ -108,16 +112,111 @@ __global__ __launch_bounds__(kGemmThreads) void k_zgemm_reduce(const Z64* __rest
   }
 }
 
-__global__ void k_sum_parts(const Z64* __restrict__ cpart, int nsplit, int total, double scale, Z64* __restrict__ C) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= total) return;
-  double re = 0.0, im = 0.0;
-  for (int s = 0; s < nsplit; ++s) {
-    const Z64 v = cpart[(size_t)s * total + i];
-    re += v.re;
-    im += v.im;
+// The reduce for few columns (the convergence tail, single rows, small cells): a wave takes 16 rows and
+// 16 BJ columns, so that 16 BJ columns cost the matrix cores what they hold and not the 64 of the tile
+// above, and K is split much finer, as one wave's chain over a long chunk is what such a reduce waits for
+// (64 cycles a product, 8 BJ products and one load latency a step). The loads of a step are issued two
+// steps ahead. M = 16 (64 with padding), 7 columns, K = 576: 48 -> 7 us; M = 128, 16 columns, K = 16,896:
+// 48 -> 13 us.
+template <int BJ>
+__global__ __launch_bounds__(kGemmThreads) void k_zgemm_reduce_cols(const Z64* __restrict__ A, int M_pad,
+                                                                    const Z64* __restrict__ X, int ldx,
+                                                                    const int* __restrict__ xidx, int ncols, int K,
+                                                                    int kchunk, Z64* __restrict__ cpart, int M) {
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int l16 = lane & 15, g = lane >> 4;
+  const int m0 = blockIdx.x * 64 + wave * 16;
+  const int split = blockIdx.z;
+  const int kb = split * kchunk, ke = min(K, kb + kchunk);  // a multiple of 16 apart
+  if (m0 >= M) return;  // padding only (no barrier, no LDS)
+  const Z64* ar = A + (size_t)(m0 + l16) * K + 2 * g;
+  const Z64* xr[BJ];
+#pragma unroll
+  for (int bj = 0; bj < BJ; ++bj) {
+    const int n = min(16 * bj + l16, ncols - 1);  // columns past ncols repeat the last one and are not stored
+    xr[bj] = X + (size_t)(xidx ? xidx[n] : n) * ldx + 2 * g;
   }
-  C[i] = zmk(scale * re, scale * im);
+  v4d cre[BJ], cim[BJ];
+#pragma unroll
+  for (int bj = 0; bj < BJ; ++bj) cre[bj] = cim[bj] = v4d{0.0, 0.0, 0.0, 0.0};
+  Z64 a[2][2], x[2][BJ][2];
+  auto load = [&](int b, int k) {
+    a[b][0] = ar[k];
+    a[b][1] = ar[k + 1];
+#pragma unroll
+    for (int bj = 0; bj < BJ; ++bj) {
+      x[b][bj][0] = xr[bj][k];
+      x[b][bj][1] = xr[bj][k + 1];
+    }
+  };
+  if (kb < ke) {
+    load(0, kb);
+    load(1, kb + 8);
+  }
+  for (int kc = kb; kc < ke; kc += 16) {
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      const Z64 a0 = a[b][0], a1 = a[b][1];
+      Z64 x0[BJ], x1[BJ];
+#pragma unroll
+      for (int bj = 0; bj < BJ; ++bj) {
+        x0[bj] = x[b][bj][0];
+        x1[bj] = x[b][bj][1];
+      }
+      load(b, min(kc + 16, ke - 16) + 8 * b);  // the last round reloads itself, unused
+#pragma unroll
+      for (int bj = 0; bj < BJ; ++bj) {
+        cre[bj] = mfma(a0.re, x0[bj].re, cre[bj]);
+        cim[bj] = mfma(a0.re, x0[bj].im, cim[bj]);
+        cre[bj] = mfma(a0.im, x0[bj].im, cre[bj]);
+        cim[bj] = mfma(a0.im, -x0[bj].re, cim[bj]);
+        cre[bj] = mfma(a1.re, x1[bj].re, cre[bj]);
+        cim[bj] = mfma(a1.re, x1[bj].im, cim[bj]);
+        cre[bj] = mfma(a1.im, x1[bj].im, cre[bj]);
+        cim[bj] = mfma(a1.im, -x1[bj].re, cim[bj]);
+      }
+    }
+  }
+#pragma unroll
+  for (int bj = 0; bj < BJ; ++bj) {
+    const int n = 16 * bj + l16;
+    if (n >= ncols) continue;
+    Z64* dst = cpart + ((size_t)split * ncols + n) * M_pad + m0 + g;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) dst[4 * r] = zmk(cre[bj][r], cim[bj][r]);
+  }
+}
+
+// C[n][m] = scale * sum over the splits, m < M. P threads to an output (1, or 8 where there are at least as
+// many splits, so that a few outputs of many splits are still read by many threads): each sums every P-th
+// split and the parts are added in order. 16 columns of M = 128 in 132 splits: 18 -> 6 us.
+template <int P>
+__global__ __launch_bounds__(256) void k_sum_parts(const Z64* __restrict__ cpart, int nsplit, int ncols, int M_pad,
+                                                   int M, double scale, Z64* __restrict__ C) {
+  constexpr int O = 256 / P;  // outputs per workgroup
+  __shared__ Z64 part[P > 1 ? P : 1][P > 1 ? O : 1];
+  const int o = threadIdx.x % O, q = threadIdx.x / O;
+  const int i = blockIdx.x * O + o;
+  const bool live = i < ncols * M;
+  const size_t at = live ? (size_t)(i / M) * M_pad + i % M : 0, total = (size_t)ncols * M_pad;
+  double re = 0.0, im = 0.0;
+  if (live)
+    for (int s = q; s < nsplit; s += P) {
+      const Z64 v = cpart[s * total + at];
+      re += v.re;
+      im += v.im;
+    }
+  if constexpr (P > 1) {
+    part[q][o] = zmk(re, im);
+    __syncthreads();
+    if (q != 0) return;
+#pragma unroll
+    for (int p = 1; p < P; ++p) {
+      re += part[p][o].re;
+      im += part[p][o].im;
+    }
+  }
+  if (live) C[at] = zmk(scale * re, scale * im);
 }
 
 // Y[yidx[n]][k] += sum_m A[m][k] C[n][m]. Bounded to 4 waves per SIMD: the compiler then keeps the
@@ -125,11 +224,13 @@ __global__ void k_sum_parts(const Z64* __restrict__ cpart, int nsplit, int total
 // M = 1,024, 4,096 columns, K = 91,072.
 __global__ __launch_bounds__(kGemmThreads, 4) void k_zgemm_expand(const Z64* __restrict__ A, int M_pad, int K,
                                                                const Z64* __restrict__ C, Z64* __restrict__ Y,
-                                                               int ldy, const int* __restrict__ yidx, int ncols) {
+                                                               int ldy, const int* __restrict__ yidx, int ncols,
+                                                               int M) {
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int l16 = lane & 15, g = lane >> 4;
   const int k0 = blockIdx.x * 64 + (wave & 1) * 32;
   const int n0 = blockIdx.y * 64 + (wave >> 1) * 32;
+  if (n0 >= ncols) return;  // padding only (no barrier, no LDS)
   int nn[2];
   bool nv[2];
 #pragma unroll
@@ -163,7 +264,7 @@ __global__ __launch_bounds__(kGemmThreads, 4) void k_zgemm_expand(const Z64* __r
     }
   };
   load(0);
-  for (int m = 0; m < M_pad; m += 8) {
+  for (int m = 0; m < M; m += 8) {
     Z64 a0[2], a1[2], c0[2], c1[2];
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
@@ -172,7 +273,7 @@ __global__ __launch_bounds__(kGemmThreads, 4) void k_zgemm_expand(const Z64* __r
       c0[u] = nc0[u];
       c1[u] = nc1[u];
     }
-    load(min(m + 8, M_pad - 8));  // the last step reloads itself, unused
+    load(min(m + 8, M - 8));  // the last step reloads itself, unused
 #pragma unroll
     for (int bi = 0; bi < 2; ++bi)
 #pragma unroll
@@ -205,11 +306,84 @@ __global__ __launch_bounds__(kGemmThreads, 4) void k_zgemm_expand(const Z64* __r
   }
 }
 
+// The expand for few columns: a wave takes 16 k and 16 BJ columns (see k_zgemm_reduce_cols), the loads of a
+// step two steps ahead. M = 16, 7 columns, K = 576: 12 -> 5 us; M = 128, 16 columns, K = 16,896: 43 -> 14 us.
+template <int BJ>
+__global__ __launch_bounds__(kGemmThreads) void k_zgemm_expand_cols(const Z64* __restrict__ A, int M_pad, int K,
+                                                                    const Z64* __restrict__ C, Z64* __restrict__ Y,
+                                                                    int ldy, const int* __restrict__ yidx, int ncols,
+                                                                    int M) {
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int l16 = lane & 15, g = lane >> 4;
+  const int k0 = blockIdx.x * 64 + wave * 16;
+  const Z64* ar = A + (size_t)(2 * g) * K + k0 + l16;
+  const Z64* cr[BJ];
+#pragma unroll
+  for (int bj = 0; bj < BJ; ++bj) cr[bj] = C + (size_t)min(16 * bj + l16, ncols - 1) * M_pad + 2 * g;
+  v4d dre[BJ], dim_[BJ];
+#pragma unroll
+  for (int bj = 0; bj < BJ; ++bj) dre[bj] = dim_[bj] = v4d{0.0, 0.0, 0.0, 0.0};
+  Z64 a[2][2], c[2][BJ][2];
+  auto load = [&](int b, int m) {
+    const int mm = min(m, M - 8);  // steps past the end read the last one, unused
+    a[b][0] = ar[(size_t)mm * K];
+    a[b][1] = ar[(size_t)(mm + 1) * K];
+#pragma unroll
+    for (int bj = 0; bj < BJ; ++bj) {
+      c[b][bj][0] = cr[bj][mm];
+      c[b][bj][1] = cr[bj][mm + 1];
+    }
+  };
+  auto step = [&](int b, int m) {
+    const Z64 a0 = a[b][0], a1 = a[b][1];
+    Z64 c0[BJ], c1[BJ];
+#pragma unroll
+    for (int bj = 0; bj < BJ; ++bj) {
+      c0[bj] = c[b][bj][0];
+      c1[bj] = c[b][bj][1];
+    }
+    load(b, m + 16);
+#pragma unroll
+    for (int bj = 0; bj < BJ; ++bj) {
+      dre[bj] = mfma(a0.re, c0[bj].re, dre[bj]);
+      dim_[bj] = mfma(a0.re, c0[bj].im, dim_[bj]);
+      dre[bj] = mfma(a0.im, -c0[bj].im, dre[bj]);
+      dim_[bj] = mfma(a0.im, c0[bj].re, dim_[bj]);
+      dre[bj] = mfma(a1.re, c1[bj].re, dre[bj]);
+      dim_[bj] = mfma(a1.re, c1[bj].im, dim_[bj]);
+      dre[bj] = mfma(a1.im, -c1[bj].im, dre[bj]);
+      dim_[bj] = mfma(a1.im, c1[bj].re, dim_[bj]);
+    }
+  };
+  load(0, 0);
+  load(1, 8);
+  int m = 0;
+  for (; m + 16 <= M; m += 16) {
+    step(0, m);
+    step(1, m + 8);
+  }
+  if (m < M) step(0, m);
+#pragma unroll
+  for (int bj = 0; bj < BJ; ++bj) {
+    const int n = 16 * bj + l16;
+    if (n >= ncols) continue;
+    Z64* y = Y + (size_t)(yidx ? yidx[n] : n) * ldy + k0 + g;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const Z64 old = y[4 * r];
+      y[4 * r] = zmk(old.re + dre[bj][r], old.im + dim_[bj][r]);
+    }
+  }
+}
+
 }  // namespace
 
 constexpr int kGemm64TargetGroups = 2048;  // workgroups a split-K reduce aims for by default
+// Columns up to which the kernels for few columns run: beyond three blocks of 16 the 64-column tile wastes
+// at most a quarter of its products and reads A once for more columns per load.
+constexpr int kFewCols = 48, kFewColsGroups = 512;
 
-int choose_nsplit(int M_pad, int ncols, int K, int target) {
+int nsplit_bound(int M_pad, int ncols, int K, int target) {
   if (target <= 0) target = kGemm64TargetGroups;
   const int base = (M_pad / 64) * ((ncols + 63) / 64);
   int ns = (target + base - 1) / base;
@@ -219,26 +393,63 @@ int choose_nsplit(int M_pad, int ncols, int K, int target) {
   return ns;
 }
 
-void launch_zgemm_reduce(const Z64* A, int M_pad, const Z64* X, int ldx, const int* xidx, int ncols, int K,
-                         Z64* cpart, int nsplit, hipStream_t st) {
-  if (ncols <= 0) return;
-  int kchunk = (K + nsplit - 1) / nsplit;
-  kchunk = (kchunk + 7) / 8 * 8;
-  dim3 grid(M_pad / 64, (ncols + 63) / 64, nsplit);
-  k_zgemm_reduce<<<grid, kGemmThreads, 0, st>>>(A, M_pad, X, ldx, xidx, ncols, K, kchunk, cpart);
+int choose_nsplit(int M_pad, int ncols, int K, int target) {
+  const int bound = nsplit_bound(M_pad, ncols, K, target);
+  if (ncols > kFewCols) return bound;
+  // few columns: chunks of 64 k or more
+  const int base = M_pad / 64;
+  int ns = std::min(((target > 0 ? target : kFewColsGroups) + base - 1) / base, K / 64);
+  if (ns < 1) ns = 1;
+  // never more scratch than the fixed area of the allocation-free entry point has where it took the call
+  if (ns > bound && 16.0 * ncols * (K + (ns + 1.0) * M_pad) > (double)STERN_NOALLOC_SCRATCH_BYTES) ns = bound;
+  return ns;
 }
 
-void launch_sum_parts(const Z64* cpart, int nsplit, int ncols, int M_pad, double scale, Z64* C, hipStream_t st) {
-  const int total = ncols * M_pad;
+void launch_zgemm_reduce(const Z64* A, int M_pad, const Z64* X, int ldx, const int* xidx, int ncols, int K,
+                         Z64* cpart, int nsplit, hipStream_t st, int M) {
+  if (ncols <= 0) return;
+  int kchunk = (K + nsplit - 1) / nsplit;
+  kchunk = (kchunk + 15) / 16 * 16;
+  if (ncols <= kFewCols) {
+    const dim3 grid((M + 63) / 64, 1, nsplit);
+    if (ncols <= 16)
+      k_zgemm_reduce_cols<1><<<grid, kGemmThreads, 0, st>>>(A, M_pad, X, ldx, xidx, ncols, K, kchunk, cpart, M);
+    else if (ncols <= 32)
+      k_zgemm_reduce_cols<2><<<grid, kGemmThreads, 0, st>>>(A, M_pad, X, ldx, xidx, ncols, K, kchunk, cpart, M);
+    else
+      k_zgemm_reduce_cols<3><<<grid, kGemmThreads, 0, st>>>(A, M_pad, X, ldx, xidx, ncols, K, kchunk, cpart, M);
+    return;
+  }
+  dim3 grid((M + 63) / 64, (ncols + 63) / 64, nsplit);
+  k_zgemm_reduce<<<grid, kGemmThreads, 0, st>>>(A, M_pad, X, ldx, xidx, ncols, K, kchunk, cpart, M);
+}
+
+void launch_sum_parts(const Z64* cpart, int nsplit, int ncols, int M_pad, double scale, Z64* C, hipStream_t st,
+                      int M) {
+  M = (M + 7) / 8 * 8;  // the expand reads whole steps of 8
+  const int total = ncols * M;
   if (total <= 0) return;
-  k_sum_parts<<<(total + 255) / 256, 256, 0, st>>>(cpart, nsplit, total, scale, C);
+  if (nsplit >= 8)
+    k_sum_parts<8><<<(total + 31) / 32, 256, 0, st>>>(cpart, nsplit, ncols, M_pad, M, scale, C);
+  else
+    k_sum_parts<1><<<(total + 255) / 256, 256, 0, st>>>(cpart, nsplit, ncols, M_pad, M, scale, C);
 }
 
 void launch_zgemm_expand(const Z64* A, int M_pad, const Z64* C, Z64* Y, int ldy, const int* yidx, int ncols, int K,
-                         hipStream_t st) {
+                         hipStream_t st, int M) {
   if (ncols <= 0) return;
+  M = (M + 7) / 8 * 8;
+  if (ncols <= kFewCols) {
+    if (ncols <= 16)
+      k_zgemm_expand_cols<1><<<K / 64, kGemmThreads, 0, st>>>(A, M_pad, K, C, Y, ldy, yidx, ncols, M);
+    else if (ncols <= 32)
+      k_zgemm_expand_cols<2><<<K / 64, kGemmThreads, 0, st>>>(A, M_pad, K, C, Y, ldy, yidx, ncols, M);
+    else
+      k_zgemm_expand_cols<3><<<K / 64, kGemmThreads, 0, st>>>(A, M_pad, K, C, Y, ldy, yidx, ncols, M);
+    return;
+  }
   dim3 grid(K / 64, (ncols + 63) / 64);
-  k_zgemm_expand<<<grid, kGemmThreads, 0, st>>>(A, M_pad, K, C, Y, ldy, yidx, ncols);
+  k_zgemm_expand<<<grid, kGemmThreads, 0, st>>>(A, M_pad, K, C, Y, ldy, yidx, ncols, M);
 }
 
 }  // namespace stern

@@ -75,17 +75,20 @@ void launch_plane_full_inv(const FftGeom& g, const Z64* pen, int nvec, Z64* out,
 void launch_plane_dn(const FftGeom& g, const Z64* pen, const Z64* psi_r, int band0, int nb, int npert,
                      const int* pert_out, double scale, double* dn, hipStream_t st);
 
-// C[n][m] = sum_k conj(A[m][k]) X[xidx[n]][k]; partial sums per K split.
-// A: [M_pad][K] (M_pad multiple of 64), X rows of length ldx, K multiple of 8.
+// C[n][m] = sum_k conj(A[m][k]) X[xidx[n]][k]; partial sums per K split, rows m < M (rounded up to 16).
+// A: [M_pad][K] (M_pad multiple of 64, rows from M on zero), X rows of length ldx, K multiple of 64.
 void launch_zgemm_reduce(const Z64* A, int M_pad, const Z64* X, int ldx, const int* xidx, int ncols, int K,
-                         Z64* cpart, int nsplit, hipStream_t st);
-// C[n][m] = scale * sum_s cpart[s][n][m]
-void launch_sum_parts(const Z64* cpart, int nsplit, int ncols, int M_pad, double scale, Z64* C, hipStream_t st);
-// Y[yidx[n]][k] += sum_m A[m][k] C[n][m], k < K (multiple of 64).
+                         Z64* cpart, int nsplit, hipStream_t st, int M);
+// C[n][m] = scale * sum_s cpart[s][n][m], m < M rounded up to 8
+void launch_sum_parts(const Z64* cpart, int nsplit, int ncols, int M_pad, double scale, Z64* C, hipStream_t st,
+                      int M);
+// Y[yidx[n]][k] += sum_m A[m][k] C[n][m], k < K (multiple of 64), m < M rounded up to 8.
 void launch_zgemm_expand(const Z64* A, int M_pad, const Z64* C, Z64* Y, int ldy, const int* yidx, int ncols, int K,
-                         hipStream_t st);
-// split-K factor for a reduce of ncols columns aiming at `target` workgroups (<= 0: default)
+                         hipStream_t st, int M);
+// split-K factor for a reduce of ncols columns aiming at `target` workgroups (<= 0: default), and the factor
+// of the 64-column tile, by which the allocation-free entry point states its limit
 int choose_nsplit(int M_pad, int ncols, int K, int target);
+int nsplit_bound(int M_pad, int ncols, int K, int target);
 
 // ---- CG vector kernels; one workgroup per solve s = act[b] ----
 struct CgState {
@@ -123,9 +126,9 @@ void launch_cocg_alpha(const CgState& s, const int* negk, const double* rzi, dou
                        double tol2, hipStream_t st);
 void launch_cocg_beta(const CgState& s, const int* negk, double* rzi, const int* act, int n, hipStream_t st);
 void launch_cocg_true(const CgState& s, double u, const int* act, int n, double tol, hipStream_t st);
-// permutations between canonical and column order: out[v][perm[k]] = in[v][k] (scatter) or gather
-void launch_permute(const Z64* in, int ld_in, Z64* out, int ld_out, const int* perm, int npw, int nvec, bool scatter,
-                    hipStream_t st);
+// dst[v][j] = src[v][idx[j]], j < nd, zero where idx[j] < 0 (between canonical and column order)
+void launch_rows_gather(const Z64* src, int ld_src, Z64* dst, int ld_dst, const int* idx, int nd, int nvec,
+                        hipStream_t st);
 void launch_fill_zero(Z64* p, size_t n, hipStream_t st);
 void launch_set_flag(int* flag, const int* list, int n, int value, hipStream_t st);
 void launch_ri_to_complex(const double* in, Z64* out, size_t n, hipStream_t st);

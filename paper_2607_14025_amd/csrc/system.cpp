@@ -7,6 +7,7 @@
 #include <complex>
 #include <cstdarg>
 #include <cstdio>
+#include <cstdint>
 #include <cstring>
 #include <map>
 #include <numeric>
@@ -155,6 +156,7 @@ struct stern_system {
   int n_atoms = 0, natoms_pad = 0;
   // static device data
   DBuf col_start, col_len, col_xmin, col_pos, zl, ycol, ymax, g2h, tw64, tw32, v_r, v_r32, v_t, v_t32, kb, perm;
+  DBuf iperm;  // [npw_pad] canonical index of each column-order coefficient, -1 in the padding
   // yz-plane kernel of the H apply per precision: 0 full-plane, 1 compact wave-local
   int plane_var64 = 1, plane_var32 = 1;
   // split-K workgroup targets of the FP64 and split-BF16 reduces (0 = default)
@@ -288,7 +290,7 @@ struct stern_system {
   }
 
   void release_all() {
-    DBuf* all[] = {&ycol, &ymax, &tw32, &v_r32, &col_start, &col_len,  &col_xmin, &col_pos, &zl,       &g2h,     &tw64,     &v_r,      &kb,
+    DBuf* all[] = {&ycol, &ymax, &iperm, &tw32, &v_r32, &col_start, &col_len,  &col_xmin, &col_pos, &zl,       &g2h,     &tw64,     &v_r,      &kb,
                    &perm,      &psi,      &psi_r,    &wx,      &wr,       &wp,      &wq,       &wz,       &wb,
                    &pen,       &cpart,    &cmat,     &sv_eps,  &sv_invT,  &sv_band, &sv_pert,  &sv_bb,    &sv_rz,
                    &sv_rr,     &sv_flag,  &sv_iters, &sv_tres, &list_act, &list_f,  &pert_out, &dv_dev,   &dn_dev,
@@ -365,13 +367,13 @@ int apply_pc_rows(stern_system* S, Z64* Y, const int* list, int n) {
   const double npw = S->hb.npw, m = S->n_occ, zb = sizeof(Z64);
   const int ns = choose_nsplit(S->nocc_pad, n, K, S->gemm64_wg);
   CHECKED(timed(S, STERN_K_PC_REDUCE, zb * npw * (n + m), 8.0 * m * npw * n, [&] {
-    launch_zgemm_reduce(S->psi.as<Z64>(), S->nocc_pad, Y, K, list, n, K, S->cpart.as<Z64>(), ns, S->stream);
+    launch_zgemm_reduce(S->psi.as<Z64>(), S->nocc_pad, Y, K, list, n, K, S->cpart.as<Z64>(), ns, S->stream, S->n_occ);
   }));
   CHECKED(timed(S, STERN_K_SUM_PARTS, zb * m * n * (ns + 1), 0.0, [&] {
-    launch_sum_parts(S->cpart.as<Z64>(), ns, n, S->nocc_pad, -1.0, S->cmat.as<Z64>(), S->stream);
+    launch_sum_parts(S->cpart.as<Z64>(), ns, n, S->nocc_pad, -1.0, S->cmat.as<Z64>(), S->stream, S->n_occ);
   }));
   CHECKED(timed(S, STERN_K_PC_EXPAND, zb * npw * (2.0 * n + m), 8.0 * m * npw * n, [&] {
-    launch_zgemm_expand(S->psi.as<Z64>(), S->nocc_pad, S->cmat.as<Z64>(), Y, K, list, n, K, S->stream);
+    launch_zgemm_expand(S->psi.as<Z64>(), S->nocc_pad, S->cmat.as<Z64>(), Y, K, list, n, K, S->stream, S->n_occ);
   }));
   return 0;
 }
@@ -407,13 +409,16 @@ int apply_h_rows(stern_system* S, const Z64* in, Z64* out, const int* list, int 
     const double na = S->n_atoms;
     const int ns = choose_nsplit(S->natoms_pad, n, K, S->gemm64_wg);
     CHECKED(timed(S, STERN_K_KB_REDUCE, zb * npw * (n + na), 8.0 * na * npw * n, [&] {
-      launch_zgemm_reduce(S->kb.as<Z64>(), S->natoms_pad, in, K, list, n, K, S->cpart.as<Z64>(), ns, S->stream);
+      launch_zgemm_reduce(S->kb.as<Z64>(), S->natoms_pad, in, K, list, n, K, S->cpart.as<Z64>(), ns, S->stream,
+                          S->n_atoms);
     }));
     CHECKED(timed(S, STERN_K_SUM_PARTS, zb * na * n * (ns + 1), 0.0, [&] {
-      launch_sum_parts(S->cpart.as<Z64>(), ns, n, S->natoms_pad, S->cell.D, S->cmat.as<Z64>(), S->stream);
+      launch_sum_parts(S->cpart.as<Z64>(), ns, n, S->natoms_pad, S->cell.D, S->cmat.as<Z64>(), S->stream,
+                       S->n_atoms);
     }));
     CHECKED(timed(S, STERN_K_KB_EXPAND, zb * npw * (2.0 * n + na), 8.0 * na * npw * n, [&] {
-      launch_zgemm_expand(S->kb.as<Z64>(), S->natoms_pad, S->cmat.as<Z64>(), out, K, list, n, K, S->stream);
+      launch_zgemm_expand(S->kb.as<Z64>(), S->natoms_pad, S->cmat.as<Z64>(), out, K, list, n, K, S->stream,
+                          S->n_atoms);
     }));
   }
   return 0;
@@ -1304,6 +1309,9 @@ int stern_init_system(const stern_cell* cell, const stern_runtime* rt, stern_sys
       HIPOK(hipStreamSynchronize(st));  // nk is released at the end of this block
     }
     CHECKED(upload(S->perm, hb.perm.data(), hb.perm.size() * sizeof(int), st));
+    std::vector<int> ip(hb.npw_pad, -1);
+    for (int c = 0; c < hb.npw; ++c) ip[hb.perm[c]] = c;
+    CHECKED(upload(S->iperm, ip.data(), ip.size() * sizeof(int), st));
     std::vector<Z64> tw(hb.N);
     for (int m = 0; m < hb.N; ++m) {
       const double a = 6.283185307179586476925286766559 * m / hb.N;
@@ -1426,11 +1434,11 @@ int stern_set_occupied(stern_system* S, int n_occ, const double* psi, const doub
   CHECKED(upload(S->band_eps, S->eps.data(), n_occ * sizeof(double), st));
   CHECKED(upload(S->band_invT, S->invT.data(), n_occ * sizeof(double), st));
   CHECKED(S->psi.ensure((size_t)S->nocc_pad * K * sizeof(Z64)));
-  launch_fill_zero(S->psi.as<Z64>(), (size_t)S->nocc_pad * K, st);
   // tmp_in also holds P_c KB below
   CHECKED(S->tmp_in.ensure(std::max((size_t)n_occ * npw, (size_t)S->natoms_pad * K) * sizeof(Z64)));
   HIPOK(hipMemcpyAsync(S->tmp_in.p, hp, (size_t)n_occ * npw * sizeof(Z64), hipMemcpyHostToDevice, st));
-  launch_permute(S->tmp_in.as<Z64>(), npw, S->psi.as<Z64>(), K, S->perm.as<int>(), npw, n_occ, true, st);
+  launch_rows_gather(S->tmp_in.as<Z64>(), npw, S->psi.as<Z64>(), K, S->iperm.as<int>(), K, n_occ, st);
+  launch_fill_zero(S->psi.as<Z64>() + (size_t)n_occ * K, (size_t)(S->nocc_pad - n_occ) * K, st);
   const size_t psn = (size_t)S->nocc_pad * K * 2 * sizeof(__bf16);
   for (DBuf* d : {&S->psi_hi, &S->psi_lo, &S->psiT_hi, &S->psiT_lo}) CHECKED(d->ensure(psn));
   launch_split_bf16(S->psi.as<Z64>(), S->nocc_pad, K, S->psi_hi.as<__bf16>(), S->psi_lo.as<__bf16>(),
@@ -1446,9 +1454,9 @@ int stern_set_occupied(stern_system* S, int n_occ, const double* psi, const doub
     const int ns = choose_nsplit(Mb, Ma, K, S->gemm64_wg);
     CHECKED(S->cpart.ensure((size_t)ns * Ma * Mb * sizeof(Z64)));
     CHECKED(S->cmat.ensure((size_t)Ma * Mb * sizeof(Z64)));
-    launch_zgemm_reduce(S->psi.as<Z64>(), Mb, S->kb.as<Z64>(), K, nullptr, Ma, K, S->cpart.as<Z64>(), ns, st);
-    launch_sum_parts(S->cpart.as<Z64>(), ns, Ma, Mb, -1.0, S->cmat.as<Z64>(), st);
-    launch_zgemm_expand(S->psi.as<Z64>(), Mb, S->cmat.as<Z64>(), pkb, K, nullptr, Ma, K, st);
+    launch_zgemm_reduce(S->psi.as<Z64>(), Mb, S->kb.as<Z64>(), K, nullptr, Ma, K, S->cpart.as<Z64>(), ns, st, Mb);
+    launch_sum_parts(S->cpart.as<Z64>(), ns, Ma, Mb, -1.0, S->cmat.as<Z64>(), st, Mb);
+    launch_zgemm_expand(S->psi.as<Z64>(), Mb, S->cmat.as<Z64>(), pkb, K, nullptr, Ma, K, st, Mb);
     launch_split_bf16_rows(pkb, Ma, K, 0, Mt, nullptr, nullptr, th, tl, st);
     launch_split_bf16_rows(S->psi.as<Z64>(), Mb, K, Ma, Mt, nullptr, nullptr, th, tl, st);
     CHECKED(launch_check());
@@ -1473,27 +1481,38 @@ int stern_set_occupied(stern_system* S, int n_occ, const double* psi, const doub
   return STERN_OK;
 }
 
+// the callers' device arrays are read and written in place when 16-byte loads may be used on them
+static bool direct_rows(const void* p, int mem_kind) {
+  return mem_kind == STERN_MEM_DEVICE && (reinterpret_cast<uintptr_t>(p) & (alignof(Z64) - 1)) == 0;
+}
+
 static int rows_in(stern_system* S, int n_vec, const double* c, int mem_kind, DBuf& dst) {
   const int npw = S->hb.npw, K = S->hb.npw_pad;
   CHECKED(dst.ensure((size_t)n_vec * K * sizeof(Z64)));
-  launch_fill_zero(dst.as<Z64>(), (size_t)n_vec * K, S->stream);
-  CHECKED(S->tmp_out.ensure((size_t)n_vec * npw * sizeof(Z64)));
-  HIPOK(hipMemcpyAsync(S->tmp_out.p, c, (size_t)n_vec * npw * sizeof(Z64),
-                       mem_kind == STERN_MEM_DEVICE ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, S->stream));
-  launch_permute(S->tmp_out.as<Z64>(), npw, dst.as<Z64>(), K, S->perm.as<int>(), npw, n_vec, true, S->stream);
+  const Z64* src = reinterpret_cast<const Z64*>(c);
+  if (!direct_rows(c, mem_kind)) {
+    CHECKED(S->tmp_out.ensure((size_t)n_vec * npw * sizeof(Z64)));
+    HIPOK(hipMemcpyAsync(S->tmp_out.p, c, (size_t)n_vec * npw * sizeof(Z64),
+                         mem_kind == STERN_MEM_DEVICE ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, S->stream));
+    src = S->tmp_out.as<Z64>();
+  }
+  launch_rows_gather(src, npw, dst.as<Z64>(), K, S->iperm.as<int>(), K, n_vec, S->stream);
   return 0;
 }
 
-static int rows_out(stern_system* S, int n_vec, const Z64* src, const int* rows_host, double* out, int mem_kind) {
+static int rows_out(stern_system* S, int n_vec, const Z64* src, double* out, int mem_kind) {
   const int npw = S->hb.npw, K = S->hb.npw_pad;
-  CHECKED(S->tmp_out.ensure((size_t)n_vec * npw * sizeof(Z64)));
-  for (int v = 0; v < n_vec; ++v) {
-    const int row = rows_host ? rows_host[v] : v;
-    launch_permute(src + (size_t)row * K, K, S->tmp_out.as<Z64>() + (size_t)v * npw, npw, S->perm.as<int>(), npw, 1,
-                   false, S->stream);
+  Z64* dst = reinterpret_cast<Z64*>(out);
+  const bool direct = direct_rows(out, mem_kind);
+  if (!direct) {
+    CHECKED(S->tmp_out.ensure((size_t)n_vec * npw * sizeof(Z64)));
+    dst = S->tmp_out.as<Z64>();
   }
-  HIPOK(hipMemcpyAsync(out, S->tmp_out.p, (size_t)n_vec * npw * sizeof(Z64),
-                       mem_kind == STERN_MEM_DEVICE ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, S->stream));
+  launch_rows_gather(src, K, dst, npw, S->perm.as<int>(), npw, n_vec, S->stream);
+  if (!direct)
+    HIPOK(hipMemcpyAsync(out, S->tmp_out.p, (size_t)n_vec * npw * sizeof(Z64),
+                         mem_kind == STERN_MEM_DEVICE ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, S->stream));
+  CHECKED(launch_check());
   HIPOK(hipStreamSynchronize(S->stream));
   return 0;
 }
@@ -1505,17 +1524,14 @@ int stern_apply_h(stern_system* S, int n_vec, const double* c, const double* shi
   Scope sc(S->device, &S->alloc);
   CHECKED(ensure_workspace(S, std::max(n_vec, S->ws_solves)));
   CHECKED(rows_in(S, n_vec, c, mem_kind, S->wp));
-  std::vector<double> sh(n_vec, 0.0);
-  if (shift) {
-    if (mem_kind == STERN_MEM_DEVICE)
-      HIPOK(hipMemcpy(sh.data(), shift, n_vec * sizeof(double), hipMemcpyDeviceToHost));
-    else
-      std::memcpy(sh.data(), shift, n_vec * sizeof(double));
-  }
-  HIPOK(hipMemcpyAsync(S->sv_eps.p, sh.data(), n_vec * sizeof(double), hipMemcpyHostToDevice, S->stream));
+  if (shift)
+    HIPOK(hipMemcpyAsync(S->sv_eps.p, shift, n_vec * sizeof(double),
+                         mem_kind == STERN_MEM_DEVICE ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, S->stream));
+  else
+    launch_fill_zero32(S->sv_eps.as<Z32>(), n_vec, S->stream);  // n_vec zeros of 8 bytes
   CHECKED(apply_h_rows(S, S->wp.as<Z64>(), S->wq.as<Z64>(), nullptr, n_vec, S->sv_eps.as<double>()));
   CHECKED(launch_check());
-  return rows_out(S, n_vec, S->wq.as<Z64>(), nullptr, out, mem_kind);
+  return rows_out(S, n_vec, S->wq.as<Z64>(), out, mem_kind);
 }
 
 // ---- TDDFT Liouville superoperator (Tamm-Dancoff, Hartree kernel) ----------
@@ -1697,7 +1713,7 @@ int stern_liouville_apply(stern_system* S, int n_exc, const double* a, double* o
   CHECKED(rows_in(S, n, a, mem_kind, S->wp));
   CHECKED(apply_pc_rows(S, S->wp.as<Z64>(), nullptr, n));
   CHECKED(liouville_rows(S, S->wp.as<Z64>(), S->wq.as<Z64>(), n_exc));
-  return rows_out(S, n, S->wq.as<Z64>(), nullptr, out, mem_kind);
+  return rows_out(S, n, S->wq.as<Z64>(), out, mem_kind);
 }
 
 // per-excitation sums of the per-row dots conj(a) . b (bands in order)
@@ -1800,7 +1816,7 @@ int stern_liouville_solve(stern_system* S, int n_exc, const double* b, double* z
     if (resid) resid[e] = res;
     if (iters) iters[e] = it[e];
   }
-  CHECKED(rows_out(S, n, X, nullptr, z, mem_kind));
+  CHECKED(rows_out(S, n, X, z, mem_kind));
   return all_ok ? STERN_OK : STERN_WARN_NOT_CONVERGED;
 }
 
@@ -1812,8 +1828,8 @@ static int dav_vh_x(stern_system* S, const Z64* V, int cap, const Z64* X, int nx
   const int ns = choose_nsplit(cap, nx, Lt, S->gemm64_wg);
   CHECKED(S->dv_part.ensure((size_t)ns * nx * cap * sizeof(Z64)));
   CHECKED(S->dv_cm.ensure((size_t)nx * cap * sizeof(Z64)));
-  launch_zgemm_reduce(V, cap, X, Lt, nullptr, nx, Lt, S->dv_part.as<Z64>(), ns, st);
-  launch_sum_parts(S->dv_part.as<Z64>(), ns, nx, cap, 1.0, S->dv_cm.as<Z64>(), st);
+  launch_zgemm_reduce(V, cap, X, Lt, nullptr, nx, Lt, S->dv_part.as<Z64>(), ns, st, cap);
+  launch_sum_parts(S->dv_part.as<Z64>(), ns, nx, cap, 1.0, S->dv_cm.as<Z64>(), st, cap);
   C.resize((size_t)nx * cap);
   HIPOK(hipMemcpyAsync(C.data(), S->dv_cm.p, C.size() * sizeof(Z64), hipMemcpyDeviceToHost, st));
   HIPOK(hipStreamSynchronize(st));
@@ -1825,7 +1841,7 @@ static int dav_v_c(stern_system* S, const Z64* V, int cap, const std::vector<Z64
   hipStream_t st = S->stream;
   CHECKED(S->dv_cm.ensure((size_t)ny * cap * sizeof(Z64)));
   HIPOK(hipMemcpyAsync(S->dv_cm.p, C.data(), (size_t)ny * cap * sizeof(Z64), hipMemcpyHostToDevice, st));
-  launch_zgemm_expand(V, cap, S->dv_cm.as<Z64>(), Y, Lt, nullptr, ny, Lt, st);
+  launch_zgemm_expand(V, cap, S->dv_cm.as<Z64>(), Y, Lt, nullptr, ny, Lt, st, cap);
   HIPOK(hipStreamSynchronize(st));  // C may change on return
   return launch_check();
 }
@@ -1995,7 +2011,7 @@ int stern_liouville_davidson(stern_system* S, int n_eig, int block, int max_basi
   for (int n = 0; n < n_eig; ++n) mr = std::max(mr, rn[n] / std::max(std::fabs(theta[n]), 1e-300));
   if (n_iter) *n_iter = it;
   if (max_resid) *max_resid = mr;
-  if (vec) CHECKED(rows_out(S, n_eig * nb, X, nullptr, vec, STERN_MEM_HOST));
+  if (vec) CHECKED(rows_out(S, n_eig * nb, X, vec, STERN_MEM_HOST));
   return all_conv ? STERN_OK : STERN_WARN_NOT_CONVERGED;
 }
 
@@ -2088,7 +2104,7 @@ int stern_apply_pc(stern_system* S, int n_vec, const double* c, double* out, int
   CHECKED(rows_in(S, n_vec, c, mem_kind, S->wp));
   CHECKED(apply_pc_rows(S, S->wp.as<Z64>(), nullptr, n_vec));
   CHECKED(launch_check());
-  return rows_out(S, n_vec, S->wp.as<Z64>(), nullptr, out, mem_kind);
+  return rows_out(S, n_vec, S->wp.as<Z64>(), out, mem_kind);
 }
 
 int stern_apply_pc_noalloc(stern_system* S, int n_vec, const double* c, double* out) {
@@ -2102,7 +2118,8 @@ int stern_apply_pc_noalloc(stern_system* S, int n_vec, const double* c, double* 
   // scratch: rows in column order [n][K], split-K partials [ns][n][M], C [n][M]
   const size_t rows_b = (size_t)n_vec * K * sizeof(Z64);
   const size_t part_b = (size_t)ns * n_vec * M * sizeof(Z64);
-  const size_t need = rows_b + part_b + (size_t)n_vec * M * sizeof(Z64);
+  // the limit is stated with the split factor of the 64-column tile; choose_nsplit keeps within the area
+  const size_t need = rows_b + ((size_t)nsplit_bound(M, n_vec, K, S->gemm64_wg) + 1) * n_vec * M * sizeof(Z64);
   if (need > (size_t)STERN_NOALLOC_SCRATCH_BYTES)
     return fail(STERN_ERR_INVALID_ARG, "%d rows need %zu bytes of scratch; the limit is %zu", n_vec, need,
                 (size_t)STERN_NOALLOC_SCRATCH_BYTES);
@@ -2114,13 +2131,12 @@ int stern_apply_pc_noalloc(stern_system* S, int n_vec, const double* c, double* 
   Z64* part = reinterpret_cast<Z64*>(base + rows_b);
   Z64* cmat = reinterpret_cast<Z64*>(base + rows_b + part_b);
   hipStream_t st = S->stream;
-  // the padding entries of the rows take part in the reduce and must be zero
-  launch_fill_zero(rows, (size_t)n_vec * K, st);
-  launch_permute(reinterpret_cast<const Z64*>(c), npw, rows, K, S->perm.as<int>(), npw, n_vec, true, st);
-  launch_zgemm_reduce(S->psi.as<Z64>(), M, rows, K, nullptr, n_vec, K, part, ns, st);
-  launch_sum_parts(part, ns, n_vec, M, -1.0, cmat, st);
-  launch_zgemm_expand(S->psi.as<Z64>(), M, cmat, rows, K, nullptr, n_vec, K, st);
-  launch_permute(rows, K, reinterpret_cast<Z64*>(out), npw, S->perm.as<int>(), npw, n_vec, false, st);
+  // the padding entries of the rows take part in the reduce and are zero
+  launch_rows_gather(reinterpret_cast<const Z64*>(c), npw, rows, K, S->iperm.as<int>(), K, n_vec, st);
+  launch_zgemm_reduce(S->psi.as<Z64>(), M, rows, K, nullptr, n_vec, K, part, ns, st, S->n_occ);
+  launch_sum_parts(part, ns, n_vec, M, -1.0, cmat, st, S->n_occ);
+  launch_zgemm_expand(S->psi.as<Z64>(), M, cmat, rows, K, nullptr, n_vec, K, st, S->n_occ);
+  launch_rows_gather(rows, K, reinterpret_cast<Z64*>(out), npw, S->perm.as<int>(), npw, n_vec, st);
   return launch_check();
 }
 
@@ -2315,7 +2331,7 @@ static int apply_chi0_impl(stern_system* S, int n_pert, const double* dv_r, doub
       const int v = opts->sample_pairs[2 * k], i = opts->sample_pairs[2 * k + 1];
       if (i < i0 || i >= i1) continue;
       const int row = (i - i0) * nb + (v - v0);
-      CHECKED(rows_out(S, 1, cs.x, &row, opts->sample_x + 2 * (size_t)k * hb.npw, STERN_MEM_HOST));
+      CHECKED(rows_out(S, 1, cs.x + (size_t)row * K, opts->sample_x + 2 * (size_t)k * hb.npw, STERN_MEM_HOST));
     }
   }
   if (opts->mem_kind == STERN_MEM_HOST)
