@@ -407,21 +407,25 @@ __global__ __launch_bounds__(kCgThreads) void k_cg32_init2(Cg32State S, const in
 // and beta = (r, z) new / old for the direction update that follows; inner
 // flag 1 once ||r||^2 <= tol2 ||r0||^2. (r, z) is taken with z before any
 // projection: r stays in range(P_c), so it equals (r, P_c z).
-template <bool LK>
-__global__ __launch_bounds__(kCgThreads) void k_cg32_alpha(Cg32State S, const int* __restrict__ act, double tol2,
-                                                             const int* __restrict__ live) {
+// Rows longer than one workgroup's registers: kAlphaChunk coefficients to a workgroup, the two sums in
+// parts added in order by the next kernel. (One workgroup to a whole row left all but a few CUs idle
+// once the list had shrunk: 91,072 coefficients took 150 us a launch for one row as for 200.)
+constexpr int kAlphaChunk = 4096;  // 16 per thread
+
+__global__ __launch_bounds__(kCgThreads) void k_cg32_pq(Cg32State S, const int* __restrict__ act,
+                                                        const int* __restrict__ live) {
   __shared__ double sh[kCgThreads / 64];
-  if (live && (int)blockIdx.x >= *live) return;  // list entry past the live count (whole workgroup)
-  const int s = act ? act[blockIdx.x] : blockIdx.x;
+  if (live && (int)blockIdx.y >= *live) return;  // list entry past the live count (whole workgroup)
+  const int s = act ? act[blockIdx.y] : blockIdx.y;
   if (S.flag[s] != 0) return;
   const size_t o = (size_t)s * S.npw_pad;
-  const int n = S.npw_pad;
+  const int k0 = blockIdx.x * kAlphaChunk, n = min(S.npw_pad, k0 + kAlphaChunk);
   double pq = 0.0;
-  for (int k0 = threadIdx.x; k0 < n; k0 += kCgThreads * kU) {
+  for (int k1 = k0 + threadIdx.x; k1 < n; k1 += kCgThreads * kU) {
     Z32 p[kU], q[kU];
 #pragma unroll
     for (int u = 0; u < kU; ++u) {
-      const int k = k0 + u * kCgThreads;
+      const int k = k1 + u * kCgThreads;
       if (k < n) {
         p[u] = S.p[o + k];
         q[u] = S.q[o + k];
@@ -429,19 +433,34 @@ __global__ __launch_bounds__(kCgThreads) void k_cg32_alpha(Cg32State S, const in
     }
 #pragma unroll
     for (int u = 0; u < kU; ++u)
-      if (k0 + u * kCgThreads < n) pq += (double)p[u].re * q[u].re + (double)p[u].im * q[u].im;
+      if (k1 + u * kCgThreads < n) pq += (double)p[u].re * q[u].re + (double)p[u].im * q[u].im;
   }
   pq = block_sum(pq, sh);
+  if (threadIdx.x == 0) S.part[((size_t)s * gridDim.x + blockIdx.x) * 3] = pq;
+}
+
+template <bool LK>
+__global__ __launch_bounds__(kCgThreads) void k_cg32_update(Cg32State S, const int* __restrict__ act,
+                                                            const int* __restrict__ live) {
+  __shared__ double sh[kCgThreads / 64];
+  if (live && (int)blockIdx.y >= *live) return;  // list entry past the live count (whole workgroup)
+  const int s = act ? act[blockIdx.y] : blockIdx.y;
+  if (S.flag[s] != 0) return;
+  double* part = S.part + (size_t)s * gridDim.x * 3;
+  double pq = 0.0;
+  for (int c = 0; c < (int)gridDim.x; ++c) pq += part[c * 3];
   const double rz_old = S.rz[s];
   const float alpha = (float)((pq > 0.0) ? rz_old / pq : 0.0);
   const double iT = S.invT[s];
+  const size_t o = (size_t)s * S.npw_pad;
+  const int k0 = blockIdx.x * kAlphaChunk, n = min(S.npw_pad, k0 + kAlphaChunk);
   double rr = 0.0, rz = 0.0;
-  for (int k0 = threadIdx.x; k0 < n; k0 += kCgThreads * kU) {
+  for (int k1 = k0 + threadIdx.x; k1 < n; k1 += kCgThreads * kU) {
     Z32 p[kU], q[kU], d[kU], r[kU];
     double t[kU];
 #pragma unroll
     for (int u = 0; u < kU; ++u) {
-      const int k = k0 + u * kCgThreads;
+      const int k = k1 + u * kCgThreads;
       if (k < n) {
         p[u] = S.p[o + k];
         q[u] = S.q[o + k];
@@ -452,7 +471,7 @@ __global__ __launch_bounds__(kCgThreads) void k_cg32_alpha(Cg32State S, const in
     }
 #pragma unroll
     for (int u = 0; u < kU; ++u) {
-      const int k = k0 + u * kCgThreads;
+      const int k = k1 + u * kCgThreads;
       if (k < n) {
         const Z32 dn = zmk(d[u].re + alpha * p[u].re, d[u].im + alpha * p[u].im);
         const Z32 rn = zmk(r[u].re - alpha * q[u].re, r[u].im - alpha * q[u].im);
@@ -469,14 +488,32 @@ __global__ __launch_bounds__(kCgThreads) void k_cg32_alpha(Cg32State S, const in
   rr = block_sum(rr, sh);
   rz = block_sum(rz, sh);
   if (threadIdx.x == 0) {
-    S.iters[s] += 1;
-    if (rr <= tol2 * S.rr0[s] || !(pq > 0.0)) S.flag[s] = 1;
-    S.beta[s] = rz_old != 0.0 ? rz / rz_old : 0.0;
-    S.rz[s] = rz;
+    part[blockIdx.x * 3 + 1] = rr;
+    part[blockIdx.x * 3 + 2] = rz;
   }
 }
 
-// The alpha step above with the whole row in one workgroup of kAlphaThreads: each thread
+__global__ void k_cg32_finish(Cg32State S, const int* __restrict__ act, int nrows, int nchunk, double tol2,
+                              const int* __restrict__ live) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= nrows || (live && i >= *live)) return;
+  const int s = act ? act[i] : i;
+  if (S.flag[s] != 0) return;
+  const double* part = S.part + (size_t)s * nchunk * 3;
+  double pq = 0.0, rr = 0.0, rz = 0.0;
+  for (int c = 0; c < nchunk; ++c) {
+    pq += part[c * 3];
+    rr += part[c * 3 + 1];
+    rz += part[c * 3 + 2];
+  }
+  const double rz_old = S.rz[s];
+  S.iters[s] += 1;
+  if (rr <= tol2 * S.rr0[s] || !(pq > 0.0)) S.flag[s] = 1;
+  S.beta[s] = rz_old != 0.0 ? rz / rz_old : 0.0;
+  S.rz[s] = rz;
+}
+
+// The same step with the whole row in one workgroup of kAlphaThreads: each thread
 // keeps its PER elements of p and q in registers from the (p, q) sum to the update, so p
 // and q are read once instead of twice. For rows up to kAlphaThreads * PER elements
 // (PER <= 17 keeps p and q within 68 VGPRs, four waves per SIMD).
@@ -934,6 +971,9 @@ void launch_cg32_init(const Cg32State& s, const Z64* r64, const int* act, int n,
 void launch_cg32_init2(const Cg32State& s, const int* act, int n, hipStream_t st) {
   if (n > 0) k_cg32_init2<<<n, kCgThreads, 0, st>>>(s, act);
 }
+int cg32_chunks(int npw_pad) {
+  return npw_pad <= kAlphaThreads * kAlphaMaxPer ? 0 : (npw_pad + kAlphaChunk - 1) / kAlphaChunk;
+}
 void launch_cg32_alpha(const Cg32State& s, const int* act, int n, double tol2, hipStream_t st, const int* live) {
   if (n <= 0) return;
   if (s.npw_pad <= kAlphaThreads * kAlphaMaxPer) {  // the row fits in one workgroup's registers
@@ -941,10 +981,14 @@ void launch_cg32_alpha(const Cg32State& s, const int* act, int n, double tol2, h
       k_cg32_alpha_row<true, kAlphaMaxPer><<<n, kAlphaThreads, 0, st>>>(s, act, tol2, live);
     else
       k_cg32_alpha_row<false, kAlphaMaxPer><<<n, kAlphaThreads, 0, st>>>(s, act, tol2, live);
-  } else if (s.kprec) {
-    k_cg32_alpha<true><<<n, kCgThreads, 0, st>>>(s, act, tol2, live);
   } else {
-    k_cg32_alpha<false><<<n, kCgThreads, 0, st>>>(s, act, tol2, live);
+    const int nc = cg32_chunks(s.npw_pad);
+    k_cg32_pq<<<dim3(nc, n), kCgThreads, 0, st>>>(s, act, live);
+    if (s.kprec)
+      k_cg32_update<true><<<dim3(nc, n), kCgThreads, 0, st>>>(s, act, live);
+    else
+      k_cg32_update<false><<<dim3(nc, n), kCgThreads, 0, st>>>(s, act, live);
+    k_cg32_finish<<<(n + 255) / 256, 256, 0, st>>>(s, act, n, nc, tol2, live);
   }
 }
 

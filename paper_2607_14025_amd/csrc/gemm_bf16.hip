@@ -10,6 +10,7 @@
 //   Re conj(a) x = (a_re, a_im) . (x_re, x_im),  Im conj(a) x = (a_re, a_im) . (x_im, -x_re)
 //   Re a c       = (a_re, a_im) . (c_re, -c_im), Im a c       = (a_re, a_im) . (c_im, c_re)
 // so no lane ever needs another lane's data.
+#include <algorithm>
 #include <type_traits>
 #include <utility>
 
@@ -107,7 +108,8 @@ __global__ __launch_bounds__(256 * WN) void k_reduce_bf16w(const __bf16* __restr
   const int n0 = (rest % nnb) * kWN;
   const int split = rest / nnb;
   const int m0 = mb * kWM + wm * 32;
-  const bool live = m0 < M_pad;  // wave-uniform: rows past M_pad (M_pad is a multiple of 64) do no products
+  // wave-uniform: rows past M_pad (a multiple of 64) and waves with no live column do no products
+  const bool live = m0 < M_pad && n0 + CW * wn < nlive;
   const int kb = split * kchunk;
   const int ke = min(K, kb + kchunk);
   f32x4 cre[2][NBW], cim[2][NBW];
@@ -242,27 +244,57 @@ __host__ __device__ __forceinline__ size_t blk_index(int m, int row, int nrows) 
   return ((size_t)(m >> 4) * nrows + row) * 32 + 2 * (m & 15);
 }
 
-// C = scale * sum of the split partials, as bf16 hi and lo of (c_re, c_im):
-// Cs[0], Cs[1], each M_pad x ncols in the blocked layout.
-__global__ void k_sum_split(const Z32* __restrict__ cpart, int nsplit, int ncols, int M_pad, float scale,
-                            __bf16* __restrict__ Cs, const int* __restrict__ live) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  const int total = ncols * M_pad;
-  if (i >= total || (live && i / M_pad >= *live)) return;
+// Sum over the splits of the 256 / P outputs of a workgroup, P threads to an output (each every P-th split,
+// the parts added in order), valid in the threads of part 0. at(s): element of split s. P = 8 where there
+// are as many splits: a few live columns of hundreds of splits left most of the card waiting on one
+// thread's chain of loads (128^3 cell, 256 bands: 102 -> 20 us a launch over a solve).
+template <int P, class At>
+__device__ __forceinline__ Z32 sum_splits(bool on, int nsplit, Z32* sh, At at) {
+  constexpr int O = 256 / P;
+  const int o = threadIdx.x % O, q = threadIdx.x / O;
   float re = 0.f, im = 0.f;
-  for (int s = 0; s < nsplit; ++s) {
-    const Z32 v = cpart[(size_t)s * total + i];
-    re += v.re;
-    im += v.im;
+  if (on)
+    for (int s = q; s < nsplit; s += P) {
+      const Z32 v = at(s);
+      re += v.re;
+      im += v.im;
+    }
+  if constexpr (P > 1) {
+    sh[q * O + o] = zmk(re, im);
+    __syncthreads();
+    if (q == 0) {
+#pragma unroll
+      for (int p = 1; p < P; ++p) {
+        re += sh[p * O + o].re;
+        im += sh[p * O + o].im;
+      }
+    }
   }
-  re *= scale;
-  im *= scale;
-  const size_t plane = (size_t)total * 2, o = blk_index(i % M_pad, i / M_pad, ncols);
+  return zmk(re, im);
+}
+
+// hi and lo of (re, im) at element offset o of the two planes of Cs
+__device__ __forceinline__ void put_split(__bf16* __restrict__ Cs, size_t plane, size_t o, float re, float im) {
   const __bf16 rh = (__bf16)re, ih = (__bf16)im;
   Cs[o] = rh;
   Cs[o + 1] = ih;
   Cs[plane + o] = (__bf16)(re - (float)rh);
   Cs[plane + o + 1] = (__bf16)(im - (float)ih);
+}
+
+// C = scale * sum of the split partials, as bf16 hi and lo of (c_re, c_im):
+// Cs[0], Cs[1], each M_pad x ncols in the blocked layout.
+template <int P>
+__global__ __launch_bounds__(256) void k_sum_split(const Z32* __restrict__ cpart, int nsplit, int ncols, int M_pad,
+                                                   float scale, __bf16* __restrict__ Cs,
+                                                   const int* __restrict__ live) {
+  __shared__ Z32 sh[P > 1 ? 256 : 1];
+  const int i0 = blockIdx.x * (256 / P), i = i0 + threadIdx.x % (256 / P);
+  const int total = ncols * M_pad, nlive = live ? min(ncols, *live) * M_pad : total;
+  if (i0 >= nlive) return;  // whole workgroup
+  const Z32 c = sum_splits<P>(i < nlive, nsplit, sh, [&](int s) { return cpart[(size_t)s * total + i]; });
+  if (threadIdx.x < 256 / P && i < nlive)
+    put_split(Cs, (size_t)total * 2, blk_index(i % M_pad, i / M_pad, ncols), scale * c.re, scale * c.im);
 }
 
 // (c_re, -c_im) and (c_im, c_re) of an interleaved bf16x8 of (c_re, c_im)
@@ -471,39 +503,27 @@ __global__ void k_split_rows(const Z64* __restrict__ A, int M, int K, int row0, 
   tlo[t + 1] = lm;
 }
 
-// hi and lo of (re, im) at element offset o of the two planes of Cs
-__device__ __forceinline__ void put_split(__bf16* __restrict__ Cs, size_t plane, size_t o, float re, float im) {
-  const __bf16 rh = (__bf16)re, ih = (__bf16)im;
-  Cs[o] = rh;
-  Cs[o + 1] = ih;
-  Cs[plane + o] = (__bf16)(re - (float)rh);
-  Cs[plane + o + 1] = (__bf16)(im - (float)ih);
-}
-
 // Coefficients of the projected (H - eps) p over the stacked rows [P_c KB (Ma); Psi (Mb)] from
 // the split partials of <beta_a|p> and of <psi_b|q_loc>, q_loc the local part of (H - eps) p:
 // rows a: D <beta_a|p>; rows Ma + b: -<psi_b|q_loc>. With P_c beta_a in the stacked matrix the
 // Psi rows need not remove Psi^H of the KB term. Output as k_sum_split writes it for M_pad = Ma + Mb.
-__global__ void k_sum_proj(const Z32* __restrict__ cp_a, int ns_a, const Z32* __restrict__ cp_b, int ns_b,
-                           int ncols, int Ma, int Mb, float D, __bf16* __restrict__ Cs,
-                           const int* __restrict__ live) {
+template <int P>
+__global__ __launch_bounds__(256) void k_sum_proj(const Z32* __restrict__ cp_a, int ns_a,
+                                                  const Z32* __restrict__ cp_b, int ns_b, int ncols, int Ma, int Mb,
+                                                  float D, __bf16* __restrict__ Cs, const int* __restrict__ live) {
+  __shared__ Z32 sh[P > 1 ? 256 : 1];
   const int Mt = Ma + Mb;
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= ncols * Mt) return;
+  const int i0 = blockIdx.x * (256 / P), i = i0 + threadIdx.x % (256 / P);
+  const int nlive = (live ? min(ncols, *live) : ncols) * Mt;
+  if (i0 >= nlive) return;  // whole workgroup
   const int n = i / Mt, r = i - n * Mt;
-  if (live && n >= *live) return;
   const bool kb = r < Ma;
   const Z32* src = kb ? cp_a + (size_t)n * Ma + r : cp_b + (size_t)n * Mb + (r - Ma);
   const size_t stride = (size_t)ncols * (kb ? Ma : Mb);
-  const int ns = kb ? ns_a : ns_b;
-  float re = 0.f, im = 0.f;
-  for (int s = 0; s < ns; ++s) {
-    const Z32 v = src[s * stride];
-    re += v.re;
-    im += v.im;
-  }
+  const Z32 c = sum_splits<P>(i < nlive, kb ? ns_a : ns_b, sh, [&](int s) { return src[s * stride]; });
   const float f = kb ? D : -1.f;
-  put_split(Cs, (size_t)ncols * Mt * 2, blk_index(r, n, ncols), f * re, f * im);
+  if (threadIdx.x < 256 / P && i < nlive)
+    put_split(Cs, (size_t)ncols * Mt * 2, blk_index(r, n, ncols), f * c.re, f * c.im);
 }
 
 }  // namespace
@@ -512,7 +532,8 @@ int choose_nsplit_bf16(int M_pad, int ncols, int K, int target) {
   if (target <= 0) target = kBf16TargetGroups;
   const int base = ((M_pad + kWM - 1) / kWM) * ((ncols + kWN - 1) / kWN);
   int ns = (target + base - 1) / base;
-  const int maxs = K / 256 > 0 ? K / 256 : 1;
+  // chunks of 128 k or more: 4 steps, after which splitting further costs more in the sums than it saves
+  const int maxs = K / 128 > 0 ? K / 128 : 1;
   if (ns > maxs) ns = maxs;
   if (ns < 1) ns = 1;
   return ns;
@@ -533,7 +554,10 @@ void launch_sum_proj32(const Z32* cp_a, int ns_a, const Z32* cp_b, int ns_b, int
                        __bf16* Cs, hipStream_t st, const int* live) {
   const int total = ncols * (Ma + Mb);
   if (total <= 0) return;
-  k_sum_proj<<<(total + 255) / 256, 256, 0, st>>>(cp_a, ns_a, cp_b, ns_b, ncols, Ma, Mb, D, Cs, live);
+  if (std::max(ns_a, ns_b) >= 8)
+    k_sum_proj<8><<<(total + 31) / 32, 256, 0, st>>>(cp_a, ns_a, cp_b, ns_b, ncols, Ma, Mb, D, Cs, live);
+  else
+    k_sum_proj<1><<<(total + 255) / 256, 256, 0, st>>>(cp_a, ns_a, cp_b, ns_b, ncols, Ma, Mb, D, Cs, live);
 }
 
 void launch_reduce_bf16(const __bf16* Ahi, const __bf16* Alo, int M_pad, const Z32* X, int ldx, const int* xidx,
@@ -552,7 +576,10 @@ void launch_sum_parts32(const Z32* cpart, int nsplit, int ncols, int M_pad, floa
                         hipStream_t st, const int* live) {
   const int total = ncols * M_pad;
   if (total <= 0) return;
-  k_sum_split<<<(total + 255) / 256, 256, 0, st>>>(cpart, nsplit, ncols, M_pad, scale, Cs, live);
+  if (nsplit >= 8)
+    k_sum_split<8><<<(total + 31) / 32, 256, 0, st>>>(cpart, nsplit, ncols, M_pad, scale, Cs, live);
+  else
+    k_sum_split<1><<<(total + 255) / 256, 256, 0, st>>>(cpart, nsplit, ncols, M_pad, scale, Cs, live);
 }
 
 void launch_expand_bf16(const __bf16* ATh, const __bf16* ATl, int M_pad, const __bf16* Cs, Z32* Y, int ldy,
@@ -569,6 +596,13 @@ void launch_expand_bf16(const __bf16* ATh, const __bf16* ATl, int M_pad, const _
     if (P) go(k_expand_bf16s<2, 2, 4, true>, 128, 128, 1024);
     else go(k_expand_bf16s<2, 2, 4, false>, 128, 128, 1024);
   } else if (variant == 2) {  // 128 x 128 tile, 8 waves of 32 x 64
+    if (P) go(k_expand_bf16s<2, 4, 2, true>, 128, 128, 512);
+    else go(k_expand_bf16s<2, 4, 2, false>, 128, 128, 512);
+  } else if (ncols <= 64) {  // few columns: 64 x 64 tile, 8 waves of 16 x 32, for 4 times the workgroups
+    if (P) go(k_expand_bf16s<1, 2, 2, true>, 64, 64, 512);
+    else go(k_expand_bf16s<1, 2, 2, false>, 64, 64, 512);
+  } else if ((long)((K + 255) / 256) * ((ncols + 127) / 128) < 384) {
+    // fewer tiles than 1.5 per CU: 128 x 128, 8 waves of 32 x 64
     if (P) go(k_expand_bf16s<2, 4, 2, true>, 128, 128, 512);
     else go(k_expand_bf16s<2, 4, 2, false>, 128, 128, 512);
   } else {  // 256 x 128 tile, 8 waves of 64 x 64

@@ -192,7 +192,9 @@ struct Cg32State {
   const double* g2h;
   const float* kprec;  // as in CgState
   int npw_pad;
+  double* part;        // [nbatch][cg32_chunks(npw_pad)][3] partial sums of the alpha step of long rows
 };
+int cg32_chunks(int npw_pad);  // workgroups a long row's alpha step is split into, 0: it runs in one
 void launch_cg32_init(const Cg32State& s, const Z64* r64, const int* act, int n, hipStream_t st);
 void launch_cg32_init2(const Cg32State& s, const int* act, int n, hipStream_t st);
 void launch_cg32_alpha(const Cg32State& s, const int* act, int n, double tol2, hipStream_t st,

@@ -178,7 +178,7 @@ struct stern_system {
   // workspace
   DBuf wx, wr, wp, wq, wz, wb, pen, cpart, cpart2, cmat, sv_eps, sv_invT, sv_band, sv_pert, sv_bb, sv_rz, sv_rr, sv_flag,
       sv_iters, sv_tres, list_act, list_f, pert_out, dv_dev, dn_dev, tmp_in, tmp_out;
-  DBuf m_d, m_r, m_p, m_q, m_z, m_rz, m_rr0, m_beta, m_flag;  // mixed inner solve
+  DBuf m_d, m_r, m_p, m_q, m_z, m_rz, m_rr0, m_beta, m_flag, m_part;  // mixed inner solve
   DBuf m_cnt;                 // device count of the inner solve's active list (list_f)
   DBuf negk;                  // [npw_pad] index of -G of each coefficient (column order)
   DBuf sv_rzi;                // [nbatch] imaginary parts of the shifted solves' (r, z)_J
@@ -296,7 +296,7 @@ struct stern_system {
                    &sv_rr,     &sv_flag,  &sv_iters, &sv_tres, &list_act, &list_f,  &pert_out, &dv_dev,   &dn_dev,
                    &tmp_in,    &tmp_out,  &psi_hi,  &psi_lo,   &psiT_hi, &psiT_lo,  &kb_hi,    &kb_lo,
                    &kbT_hi,    &kbT_lo,   &m_d,     &m_r,      &m_p,     &m_q,      &m_z,      &m_rz,  &m_beta,
-                   &m_rr0,     &m_flag,   &c_col_start, &c_col_len, &c_col_xmin, &c_col_pos, &c_zl, &c_ycol,
+                   &m_rr0,     &m_flag, &m_part,   &c_col_start, &c_col_len, &c_col_xmin, &c_col_pos, &c_zl, &c_ycol,
                    &c_tw64,    &psi_c,    &c_pen,   &c_field,  &net_a0,  &net_a1,   &net_a2,   &net_out,
                    &g_rej,     &net_feat, &net_coef, &kprec,  &v_t,     &v_t32,    &band_eps, &band_invT,
                    &band_feat, &projT_hi, &projT_lo, &cpart2, &m_cnt, &negk, &sv_rzi, &xkeep,
@@ -600,6 +600,7 @@ int ensure_workspace32(stern_system* S, int ns) {
   for (DBuf* d : {&S->m_d, &S->m_r, &S->m_p, &S->m_q, &S->m_z}) CHECKED(d->ensure((size_t)ns * K * sizeof(Z32)));
   for (DBuf* d : {&S->m_rz, &S->m_rr0, &S->m_beta}) CHECKED(d->ensure((size_t)ns * sizeof(double)));
   CHECKED(S->m_flag.ensure((size_t)ns * sizeof(int)));
+  if (const int nc = cg32_chunks(S->hb.npw_pad)) CHECKED(S->m_part.ensure((size_t)ns * nc * 3 * sizeof(double)));
   CHECKED(S->m_cnt.ensure(sizeof(int)));
   if (S->ws32_solves < ns) {
     for (DBuf* d : {&S->m_d, &S->m_r, &S->m_p, &S->m_q, &S->m_z})
@@ -625,6 +626,7 @@ Cg32State cg32_state(stern_system* S, int* iters) {
   c.g2h = S->g2h.as<double>();
   c.kprec = nullptr;
   c.npw_pad = S->hb.npw_pad;
+  c.part = S->m_part.as<double>();
   return c;
 }
 
