@@ -963,10 +963,11 @@ __global__ __launch_bounds__(plane_nt<N>()) void k_plane_full_inv(const Z64* __r
       [&](int y, int j, int r, Z64 v) { op[y * N + j + r * R1] = v; }, c.tw);
 }
 
-// forward yz DFT of full planes in[vec][ix][iy][iz] -> pencils of vector `vec`
-template <int N>
+// forward yz DFT of full planes in[vec][ix][iy][iz] -> pencils of vector `vec`. PAIR: of the pair densities
+// scale conj(psi_w) psi_v instead, formed as they are read (in: psi_r; vec counts w = 0..v for v = v0, v0 + 1, ...).
+template <int N, bool PAIR>
 __global__ __launch_bounds__(plane_nt<N>()) void k_plane_full_fwd(const Z64* __restrict__ in, Z64* __restrict__ pen,
-                                                                 FftGeom g) {
+                                                                 int v0, double scale, FftGeom g) {
   using C = PlaneCtx<N, double>;
   constexpr int LD = C::LD, R1 = C::R1, R2 = C::R2, NT = C::NT;
   extern __shared__ unsigned char smem_raw[];
@@ -975,9 +976,20 @@ __global__ __launch_bounds__(plane_nt<N>()) void k_plane_full_fwd(const Z64* __r
   Z64* P = c.P;
   const int ix = blockIdx.x;
   const int vec = blockIdx.y;
-  const Z64* __restrict__ ip = in + ((size_t)vec * N + ix) * N * N;
+  int row = vec, v = v0;
+  if constexpr (PAIR)
+    for (; row > v; ++v) row -= v + 1;
+  const Z64* __restrict__ ip = in + ((size_t)row * N + ix) * N * N;
+  const Z64* __restrict__ vp = PAIR ? in + ((size_t)v * N + ix) * N * N : nullptr;
   stage<N, R1, -1, false, false, false, NT, N>(
-      N, [&](int y, int j, int r) { return ip[y * N + j + r * R2]; },
+      N,
+      [&](int y, int j, int r) {
+        const int k = y * N + j + r * R2;
+        const Z64 a = ip[k];
+        if constexpr (!PAIR) return a;
+        const Z64 b = vp[k];
+        return zmk(scale * (a.re * b.re + a.im * b.im), scale * (a.re * b.im - a.im * b.re));
+      },
       [&](int y, int j, int r, Z64 v) { P[y * LD + j * R1 + r] = v; }, c.tw);
   __syncthreads();
   stage<N, R2, -1, true, false, false, NT, N>(
@@ -1549,12 +1561,22 @@ void launch_plane_full_inv(const FftGeom& g, const Z64* pen, int nvec, Z64* out,
 
 bool plane_full_fwd_fits(int N, size_t lds) { return plane_lds_bytes(N, sizeof(Z64)) <= lds; }
 
-void launch_plane_full_fwd(const FftGeom& g, const Z64* in, int nvec, Z64* pen, hipStream_t st) {
+namespace {
+template <bool PAIR>
+void full_fwd(const FftGeom& g, const Z64* in, int nvec, int v0, double scale, Z64* pen, hipStream_t st) {
   if (nvec <= 0) return;
   const size_t lds = plane_lds_bytes(g.N, sizeof(Z64));
   dim3 grid(g.N, nvec);
-  STERN_DISPATCH_N(g.N, (set_lds((const void*)k_plane_full_fwd<NN>, lds),
-                         k_plane_full_fwd<NN><<<grid, plane_nt<NN>(), lds, st>>>(in, pen, g)));
+  STERN_DISPATCH_N(g.N, (set_lds((const void*)k_plane_full_fwd<NN, PAIR>, lds),
+                         k_plane_full_fwd<NN, PAIR><<<grid, plane_nt<NN>(), lds, st>>>(in, pen, v0, scale, g)));
+}
+}  // namespace
+void launch_plane_full_fwd(const FftGeom& g, const Z64* in, int nvec, Z64* pen, hipStream_t st) {
+  full_fwd<false>(g, in, nvec, 0, 0.0, pen, st);
+}
+void launch_plane_pair_fwd(const FftGeom& g, const Z64* psi_r, int v0, int npairs, double scale, Z64* pen,
+                           hipStream_t st) {
+  full_fwd<true>(g, psi_r, npairs, v0, scale, pen, st);
 }
 
 void launch_plane_dn(const FftGeom& g, const Z64* pen, const Z64* psi_r, int band0, int nb, int npert,

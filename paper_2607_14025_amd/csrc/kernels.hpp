@@ -181,6 +181,9 @@ void launch_pack_target(const Z64* x_c, const double* bnorm2, float* tgt, int Nc
 void launch_unpack_output(const float* out, const double* bnorm2, Z64* x_c, int Nc, int nsolve, hipStream_t st);
 // yz planes, forward: full complex planes in[vec][ix][iy][iz] -> pencils (for the coarse grid)
 void launch_plane_full_fwd(const FftGeom& g, const Z64* in, int nvec, Z64* pen, hipStream_t st);
+// the same of the densities scale conj(psi_r[w]) psi_r[v] of npairs occupied pairs, v from v0 on and w = 0..v for each
+void launch_plane_pair_fwd(const FftGeom& g, const Z64* psi_r, int v0, int npairs, double scale, Z64* pen,
+                           hipStream_t st);
 
 // ---- mixed precision (FP32 vectors, BF16 MFMA GEMMs, FP64 scalars) ----
 struct Cg32State {
@@ -244,15 +247,21 @@ void launch_coulomb(Z64* c, const double* g2h, int K, int nvec, double fac, hipS
 // out[e nb + v] = v_r[e] psi_r[v] - alpha acc[e nb + v] (acc may be null) on full grids (n_exc nb <= 65535 rows)
 void launch_grid_mul(const Z64* v_r, const Z64* psi_r, int n_exc, int nb, size_t n3, const Z64* acc, double alpha,
                      Z64* out, hipStream_t st);
-// out[w] = scale conj(psi_r[w]) psi_r[v] for w < nb
-void launch_pair_density(const Z64* psi_r, int v, int nb, size_t n3, double scale, Z64* out, hipStream_t st);
-// proj[r][a] = N^-3 sum_j w[a][j] rho[r][j] for n real potentials w and nrows complex grids rho
-void launch_scr_proj(const Z64* rho, const double* w, int n, int nrows, size_t n3, Z64* proj, hipStream_t st);
-// tau[r] += sum_a w[a] c[a] proj[r][a]
-void launch_scr_add(Z64* tau, const double* w, const Z64* proj, const double* c, int n, int nrows, size_t n3,
-                    hipStream_t st);
-// acc[e nb + v] = sum_{w < nb} tau[w] a_r[e nb + w] for e < n_exc
-void launch_exch_acc(const Z64* tau, const Z64* a_r, int n_exc, int nb, int v, size_t n3, Z64* acc, hipStream_t st);
+// Occupied pairs (w, v), w <= v, of a block of bands v in [v0, v0 + nv), nv <= kExchBands: pair (w, v0 + q) is
+// row q v0 + q (q + 1) / 2 + w of their arrays.
+constexpr int kExchBands = 4;
+constexpr int kExchScr = 16;  // potentials that launch_exch_block takes in registers
+// pc[pair][a] = scale c[a] N^-3 sum_j w[a][j] conj(psi_w[j]) psi_v[j] for n real potentials w; parts: scratch of
+// scr_proj_stretches(v0, nv, n, n3) * pairs * n values
+void launch_scr_proj(const Z64* psi_r, const double* scr, const double* c, int n, int v0, int nv, size_t n3,
+                     double scale, Z64* parts, Z64* pc, hipStream_t st);
+int scr_proj_stretches(int v0, int nv, int n, size_t n3);
+// tau[r] += sum_a w[a] pc[r][a]
+void launch_scr_add(Z64* tau, const double* w, const Z64* pc, int n, int nrows, size_t n3, hipStream_t st);
+// for every pair: acc[e nb + v] += tau a_r[e nb + w] and, w < v, acc[e nb + w] += conj(tau) a_r[e nb + v];
+// n > 0 (<= kExchScr): with tau + sum_a scr[a] pc[pair][a] for tau
+void launch_exch_block(const Z64* tau, const Z64* a_r, int n_exc, int nb, int v0, int nv, size_t n3,
+                       const double* scr, const Z64* pc, int n, Z64* acc, hipStream_t st);
 void launch_add(Z64* y, const Z64* x, size_t n, hipStream_t st);
 // per-row conj(a) . b; y[row] += c[row / nb] x[row]; p[row] = z[row] + c[row / nb] p[row];
 // z = Teter K_v r with T_v of band row mod nb

@@ -1574,18 +1574,29 @@ static int liouville_chunk(const stern_system* S, int n_exc) {
   return std::min(ce, n_exc);
 }
 
-// n full grids (in place) -> fac / (|q|^2 / 2) times their components on the 4 Ecut sphere,
-// zero at q = 0, back on the grid: the Hartree potential for fac = 2 pi
-static void potential_grids(stern_system* S, Z64* buf, int n, double fac) {
+// fac / (|q|^2 / 2) times the 4 Ecut components of n densities given as pencils (lv_pend), zero at q = 0,
+// back on the grid: the Hartree potential for fac = 2 pi
+static void potential_of_pencils(stern_system* S, Z64* out, int n, double fac) {
   const FftGeom gd = S->geom_d();
   const size_t n3 = (size_t)gd.N * gd.N * gd.N;
   hipStream_t st = S->stream;
-  launch_plane_full_fwd(gd, buf, n, S->lv_pend.as<Z64>(), st);
   launch_xfwd<double>(gd, S->lv_pend.as<Z64>(), nullptr, n, S->lv_rhog.as<Z64>(), 2, nullptr, nullptr, 1.0 / (double)n3,
                       st);
   launch_coulomb(S->lv_rhog.as<Z64>(), gd.g2h, gd.npw_pad, n, fac, st);
   launch_xinv(gd, S->lv_rhog.as<Z64>(), nullptr, n, S->lv_pend.as<Z64>(), st);
-  launch_plane_full_inv(gd, S->lv_pend.as<Z64>(), n, buf, st);
+  launch_plane_full_inv(gd, S->lv_pend.as<Z64>(), n, out, st);
+}
+
+// the same for n full grids, in place
+static void potential_grids(stern_system* S, Z64* buf, int n, double fac) {
+  launch_plane_full_fwd(S->geom_d(), buf, n, S->lv_pend.as<Z64>(), S->stream);
+  potential_of_pencils(S, buf, n, fac);
+}
+
+// bands of the direct term taken together: their pairs' potentials are held at once, up to about 1.5 GB
+static int exch_bands(const stern_system* S) {
+  const size_t grids = (size_t)S->n_occ * S->hb.N * S->hb.N * S->hb.N * sizeof(Z64);
+  return (int)std::max<size_t>(1, std::min<size_t>({(size_t)kExchBands, ((size_t)3 << 29) / grids, (size_t)S->n_occ}));
 }
 
 // out = L A for n_exc excitations of n_occ band rows each (column order, stride npw_pad; A in
@@ -1601,15 +1612,21 @@ static int liouville_rows(stern_system* S, const Z64* A, Z64* out, int n_exc) {
   const int Kd = S->hbd.npw_pad;
   const int ce = liouville_chunk(S, n_exc);
   const bool exch = S->lv_alpha != 0.0 || S->n_scr > 0;
-  const int np = std::max(ce, exch ? nb : 0);  // grids through the potential stage at once
+  const int vb = exch ? exch_bands(S) : 0;
+  const int np = std::max(ce, vb * nb);  // grids through the potential stage at once
   CHECKED(S->lv_ar.ensure((size_t)ce * nb * n3 * sizeof(Z64)));
   CHECKED(S->lv_rho.ensure((size_t)ce * n3 * sizeof(Z64)));
   CHECKED(S->lv_rhog.ensure((size_t)np * Kd * sizeof(Z64)));
   CHECKED(S->lv_pend.ensure((size_t)np * N * S->hbd.ncol_pad * sizeof(Z64)));
   if (exch) {
-    CHECKED(S->lv_tau.ensure((size_t)nb * n3 * sizeof(Z64)));
+    CHECKED(S->lv_tau.ensure((size_t)vb * nb * n3 * sizeof(Z64)));
     CHECKED(S->lv_acc.ensure((size_t)ce * nb * n3 * sizeof(Z64)));
-    if (S->n_scr > 0) CHECKED(S->scr_proj.ensure((size_t)nb * S->n_scr * sizeof(Z64)));
+    if (S->n_scr > 0) {  // the pairs' coefficients, then the partial sums they come from
+      size_t parts = 0;
+      for (int v0 = 0; v0 < nb; v0 += vb)
+        parts = std::max(parts, (size_t)scr_proj_stretches(v0, std::min(vb, nb - v0), S->n_scr, n3));
+      CHECKED(S->scr_proj.ensure((parts + 1) * vb * nb * S->n_scr * sizeof(Z64)));
+    }
   }
   CHECKED(S->lv_k.ensure((size_t)n * K * sizeof(Z64)));
   CHECKED(S->lv_eps.ensure((size_t)n * sizeof(double)));
@@ -1635,18 +1652,23 @@ static int liouville_rows(stern_system* S, const Z64* A, Z64* out, int n_exc) {
       launch_plane_full_inv(g, S->pen.as<Z64>(), rm, ar + (size_t)r0 * n3, st);
     }
     constexpr double kPi = 3.14159265358979323846;
-    if (exch)  // sum_w tau_{wv} a_w of every band v, the pair potentials one band v at a time
-      for (int v = 0; v < nb; ++v) {
-        Z64* tau = S->lv_tau.as<Z64>();
-        launch_pair_density(S->psi_r.as<Z64>(), v, nb, n3, 1.0 / hb.omega, tau, st);
-        if (S->n_scr > 0)
-          launch_scr_proj(tau, S->scr_w.as<double>(), S->n_scr, nb, n3, S->scr_proj.as<Z64>(), st);
-        potential_grids(S, tau, nb, 2.0 * kPi * S->lv_alpha);  // alpha V[rho]
-        if (S->n_scr > 0)
-          launch_scr_add(tau, S->scr_w.as<double>(), S->scr_proj.as<Z64>(), S->scr_c.as<double>(), S->n_scr, nb, n3,
-                         st);
-        launch_exch_acc(tau, ar, c, nb, v, n3, S->lv_acc.as<Z64>(), st);
+    if (exch) {
+      // sum_w tau_{wv} a_w of every band v: the potentials of the pairs w <= v, a block of bands at a time
+      Z64 *tau = S->lv_tau.as<Z64>(), *acc = S->lv_acc.as<Z64>(), *pc = S->scr_proj.as<Z64>();
+      launch_fill_zero(acc, (size_t)m * n3, st);
+      const bool scr_regs = S->n_scr > 0 && S->n_scr <= kExchScr;
+      for (int v0 = 0; v0 < nb; v0 += vb) {
+        const int nv = std::min(vb, nb - v0), pairs = nv * v0 + nv * (nv + 1) / 2;
+        launch_plane_pair_fwd(S->geom_d(), S->psi_r.as<Z64>(), v0, pairs, 1.0 / hb.omega, S->lv_pend.as<Z64>(), st);
+        potential_of_pencils(S, tau, pairs, 2.0 * kPi * S->lv_alpha);  // alpha V[rho]
+        if (S->n_scr > 0) {
+          launch_scr_proj(S->psi_r.as<Z64>(), S->scr_w.as<double>(), S->scr_c.as<double>(), S->n_scr, v0, nv, n3,
+                          1.0 / hb.omega, pc + (size_t)vb * nb * S->n_scr, pc, st);
+          if (!scr_regs) launch_scr_add(tau, S->scr_w.as<double>(), pc, S->n_scr, pairs, n3, st);
+        }
+        launch_exch_block(tau, ar, c, nb, v0, nv, n3, S->scr_w.as<double>(), pc, scr_regs ? S->n_scr : 0, acc, st);
       }
+    }
     launch_band_density(S->psi_r.as<Z64>(), ar, c, nb, n3, 1.0 / hb.omega, rho, st);
     // 2 x 4 pi / |q|^2 = 4 pi / (|q|^2 / 2): the factor 2 of the singlet exchange term folded in
     potential_grids(S, rho, c, 4.0 * kPi);

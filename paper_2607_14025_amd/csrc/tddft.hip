@@ -6,6 +6,9 @@
 // full N^3 grids (one read and one write per point and band), so the kernels are plain
 // grid-stride loops with coalesced complex FP64 accesses; the FFTs between them are the
 // library's pencil and plane kernels.
+#include <algorithm>
+#include <type_traits>
+
 #include "kernels.hpp"
 
 namespace stern {
@@ -61,34 +64,151 @@ __global__ __launch_bounds__(kGridThreads) void k_grid_mul(const Z64* __restrict
   }
 }
 
-// pair densities of one occupied orbital with all of them: out[w][j] = scale conj(psi_r[w][j]) psi_r[v][j]
-__global__ __launch_bounds__(kGridThreads) void k_pair_density(const Z64* __restrict__ psi_r, int v, size_t n3,
-                                                               double scale, Z64* __restrict__ out) {
-  const int w = blockIdx.y;
-  const Z64* pw = psi_r + (size_t)w * n3;
-  const Z64* pv = psi_r + (size_t)v * n3;
-  Z64* o = out + (size_t)w * n3;
-  for (size_t j = (size_t)blockIdx.x * kGridThreads + threadIdx.x; j < n3; j += (size_t)gridDim.x * kGridThreads) {
-    const Z64 a = pw[j], b = pv[j];
-    o[j] = zmk(scale * (a.re * b.re + a.im * b.im), scale * (a.re * b.im - a.im * b.re));
+// The direct term of a block of bands v in [v0, v0 + nv), nv <= VB, from the potentials of the pairs w <= v
+// only: tau_{vw} = conj(tau_{wv}), so pair (w, v) adds tau a_w to band v and conj(tau) a_v to band w:
+//   acc[e nb + v][j] += sum_{w <= v} tau_{wv}[j] a_r[e nb + w][j],   acc[e nb + w][j] += conj(tau_{wv}[j]) a_r[e nb + v][j], w < v,
+// tau rows in the order of pair_of. Streaming: a thread keeps one grid point, the block's a_v and sums of EB
+// excitations in registers and walks w, so a_w and acc_w pass once per VB bands and tau once per EB excitations.
+// NS > 0: tau is still without its screening sum_a w[a][j] pc[pair][a] (n <= NS), added here in registers.
+// 50 bands, 48^3, 3 excitations, 12 potentials: 13 launches of 212 us, against 50 of 65 (the products) and
+// 50 of 52 (the screening) with one band at a time and every pair formed twice.
+template <int VB, int EB, int NS>
+__global__ __launch_bounds__(kGridThreads) void k_exch_block(const Z64* __restrict__ tau, const Z64* __restrict__ a_r,
+                                                             int n_exc, int nb, int v0, int nv, size_t n3,
+                                                             const double* __restrict__ scr,
+                                                             const Z64* __restrict__ pc, int n, Z64* __restrict__ acc) {
+  const int e0 = blockIdx.y * EB;
+  const size_t j = (size_t)blockIdx.x * kGridThreads + threadIdx.x;
+  if (j >= n3) return;
+  const Z64 zero = zmk(0.0, 0.0);
+  Z64 av[VB][EB], sv[VB][EB];
+#pragma unroll
+  for (int q = 0; q < VB; ++q)
+#pragma unroll
+    for (int e = 0; e < EB; ++e) {
+      av[q][e] = sv[q][e] = zero;
+      if (q < nv && e0 + e < n_exc) av[q][e] = a_r[((size_t)(e0 + e) * nb + v0 + q) * n3 + j];
+    }
+  double f[NS > 0 ? NS : 1];
+  if constexpr (NS > 0) {
+#pragma unroll
+    for (int a = 0; a < NS; ++a) f[a] = a < n ? scr[(size_t)a * n3 + j] : 0.0;
+  }
+  for (int w = 0; w < v0 + nv; ++w) {
+    Z64 t[VB], aw[EB], cw[EB];
+#pragma unroll
+    for (int q = 0; q < VB; ++q) {  // pair (w, v0 + q): row q v0 + q (q + 1) / 2 + w
+      const bool on = q < nv && w <= v0 + q;
+      const size_t row = (size_t)q * v0 + q * (q + 1) / 2 + w;
+      t[q] = zero;
+      if (on) t[q] = tau[row * n3 + j];
+      if constexpr (NS > 0) {
+        if (on) {
+          const Z64* p = pc + row * n;
+#pragma unroll
+          for (int a = 0; a < NS; ++a)
+            if (a < n) {
+              t[q].re += f[a] * p[a].re;
+              t[q].im += f[a] * p[a].im;
+            }
+        }
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < EB; ++e) {
+      aw[e] = cw[e] = zero;
+      if (e0 + e < n_exc) aw[e] = a_r[((size_t)(e0 + e) * nb + w) * n3 + j];
+    }
+#pragma unroll
+    for (int q = 0; q < VB; ++q)
+#pragma unroll
+      for (int e = 0; e < EB; ++e) {
+        sv[q][e].re += t[q].re * aw[e].re - t[q].im * aw[e].im;
+        sv[q][e].im += t[q].re * aw[e].im + t[q].im * aw[e].re;
+        if (w < v0 + q) {
+          cw[e].re += t[q].re * av[q][e].re + t[q].im * av[q][e].im;
+          cw[e].im += t[q].re * av[q][e].im - t[q].im * av[q][e].re;
+        }
+      }
+#pragma unroll
+    for (int e = 0; e < EB; ++e)
+      if (e0 + e < n_exc) {
+        Z64* o = acc + ((size_t)(e0 + e) * nb + w) * n3 + j;
+        Z64 c = *o;
+        c = zmk(c.re + cw[e].re, c.im + cw[e].im);
+#pragma unroll
+        for (int q = 0; q < VB; ++q)  // the band's own sum is complete once w has reached it
+          if (w == v0 + q) c = zmk(c.re + sv[q][e].re, c.im + sv[q][e].im);
+        *o = c;
+      }
   }
 }
 
-// acc[e nb + v][j] = sum_w tau[w][j] a_r[e nb + w][j], w in order (tau[w] = tau_{wv} of one band v)
-__global__ __launch_bounds__(kGridThreads) void k_exch_acc(const Z64* __restrict__ tau, const Z64* __restrict__ a_r,
-                                                           int nb, int v, size_t n3, Z64* __restrict__ acc) {
-  const int e = blockIdx.y;
-  const Z64* ae = a_r + (size_t)e * nb * n3;
-  Z64* o = acc + ((size_t)e * nb + v) * n3;
-  for (size_t j = (size_t)blockIdx.x * kGridThreads + threadIdx.x; j < n3; j += (size_t)gridDim.x * kGridThreads) {
-    double re = 0.0, im = 0.0;
-    for (int w = 0; w < nb; ++w) {
-      const Z64 t = tau[(size_t)w * n3 + j], a = ae[(size_t)w * n3 + j];
-      re += t.re * a.re - t.im * a.im;
-      im += t.re * a.im + t.im * a.re;
+// parts[s][pair][a] = sum over the s-th stretch of the grid of w[a][j] conj(psi_w[j]) psi_v[j], the pairs (w, v) of a
+// block of bands as in k_exch_block. A workgroup takes one w, the block's VB bands and AT potentials, so the VB AT
+// products a point share its 1 + VB orbital and AT potential values.
+constexpr int kProjA = 8;
+template <int VB>
+__global__ __launch_bounds__(kGridThreads) void k_scr_proj(const Z64* __restrict__ psi_r, const double* __restrict__ scr,
+                                                           int n, int v0, int nv, size_t n3, size_t stretch,
+                                                           int npairs, Z64* __restrict__ parts) {
+  constexpr int AT = kProjA;
+  __shared__ Z64 sh[kGridThreads / 64][VB * AT];
+  const int w = blockIdx.x, a0 = blockIdx.z * AT;
+  const size_t j0 = blockIdx.y * stretch, j1 = min(n3, j0 + stretch);
+  Z64 s[VB][AT];
+#pragma unroll
+  for (int q = 0; q < VB; ++q)
+#pragma unroll
+    for (int a = 0; a < AT; ++a) s[q][a] = zmk(0.0, 0.0);
+  const Z64* pw = psi_r + (size_t)w * n3;
+  for (size_t j = j0 + threadIdx.x; j < j1; j += kGridThreads) {
+    const Z64 x = pw[j];
+    double f[AT];
+#pragma unroll
+    for (int a = 0; a < AT; ++a) f[a] = scr[(size_t)min(a0 + a, n - 1) * n3 + j];
+#pragma unroll
+    for (int q = 0; q < VB; ++q) {
+      const Z64 y = psi_r[(size_t)(v0 + min(q, nv - 1)) * n3 + j];
+      const double re = x.re * y.re + x.im * y.im, im = x.re * y.im - x.im * y.re;
+#pragma unroll
+      for (int a = 0; a < AT; ++a) {
+        s[q][a].re += f[a] * re;
+        s[q][a].im += f[a] * im;
+      }
     }
-    o[j] = zmk(re, im);
   }
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+#pragma unroll
+  for (int q = 0; q < VB; ++q)
+#pragma unroll
+    for (int a = 0; a < AT; ++a) {
+      double re = s[q][a].re, im = s[q][a].im;
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) {
+        re += __shfl_xor(re, o);
+        im += __shfl_xor(im, o);
+      }
+      if (lane == 0) sh[wave][q * AT + a] = zmk(re, im);
+    }
+  __syncthreads();
+  const int q = threadIdx.x / AT, a = threadIdx.x % AT;
+  if (q >= nv || a0 + a >= n || w > v0 + q) return;
+  Z64 t = zmk(0.0, 0.0);
+#pragma unroll
+  for (int k = 0; k < kGridThreads / 64; ++k) t = t + sh[k][q * AT + a];
+  const size_t row = (size_t)q * v0 + q * (q + 1) / 2 + w;
+  parts[((size_t)blockIdx.y * npairs + row) * n + a0 + a] = t;
+}
+
+// pc[i] = scale c[i mod n] sum_s parts[s][i], s in order
+__global__ void k_scr_sum(const Z64* __restrict__ parts, int ns, int total, int n, const double* __restrict__ c,
+                          double scale, Z64* __restrict__ pc) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= total) return;
+  Z64 t = zmk(0.0, 0.0);
+  for (int s = 0; s < ns; ++s) t = t + parts[(size_t)s * total + i];
+  pc[i] = zscale(t, scale * c[i % n]);
 }
 
 // y[i] += x[i]
@@ -99,52 +219,16 @@ __global__ __launch_bounds__(kGridThreads) void k_add(Z64* __restrict__ y, const
   }
 }
 
-// proj[r][a] = N^-3 sum_j w[a][j] rho[r][j] (one workgroup per (a, r), fixed order)
-__global__ __launch_bounds__(kGridThreads) void k_scr_proj(const Z64* __restrict__ rho, const double* __restrict__ w,
-                                                           int n, size_t n3, Z64* __restrict__ proj) {
-  __shared__ double sre[kGridThreads / 64], sim[kGridThreads / 64];
-  const int a = blockIdx.x, r = blockIdx.y;
-  const Z64* x = rho + (size_t)r * n3;
-  const double* wa = w + (size_t)a * n3;
-  double re = 0.0, im = 0.0;
-  for (size_t j = threadIdx.x; j < n3; j += kGridThreads) {
-    const double f = wa[j];
-    const Z64 v = x[j];
-    re += f * v.re;
-    im += f * v.im;
-  }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    re += __shfl_xor(re, o);
-    im += __shfl_xor(im, o);
-  }
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  if (lane == 0) {
-    sre[wave] = re;
-    sim[wave] = im;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double tr = 0.0, ti = 0.0;
-    for (int k = 0; k < kGridThreads / 64; ++k) {
-      tr += sre[k];
-      ti += sim[k];
-    }
-    proj[(size_t)r * n + a] = zmk(tr / (double)n3, ti / (double)n3);
-  }
-}
-
-// tau[r][j] += sum_a w[a][j] c[a] proj[r][a]
+// tau[r][j] += sum_a w[a][j] pc[r][a] (more potentials than k_exch_block holds in registers)
 __global__ __launch_bounds__(kGridThreads) void k_scr_add(Z64* __restrict__ tau, const double* __restrict__ w,
-                                                          const Z64* __restrict__ proj, const double* __restrict__ c,
-                                                          int n, size_t n3) {
+                                                          const Z64* __restrict__ pc, int n, size_t n3) {
   const int r = blockIdx.y;
   Z64* t = tau + (size_t)r * n3;
-  const Z64* p = proj + (size_t)r * n;
+  const Z64* p = pc + (size_t)r * n;
   for (size_t j = (size_t)blockIdx.x * kGridThreads + threadIdx.x; j < n3; j += (size_t)gridDim.x * kGridThreads) {
     double re = 0.0, im = 0.0;
     for (int a = 0; a < n; ++a) {
-      const double f = w[(size_t)a * n3 + j] * c[a];
+      const double f = w[(size_t)a * n3 + j];
       re += f * p[a].re;
       im += f * p[a].im;
     }
@@ -181,16 +265,39 @@ void launch_grid_mul(const Z64* v_r, const Z64* psi_r, int n_exc, int nb, size_t
   k_grid_mul<<<grid, kGridThreads, 0, st>>>(v_r, psi_r, nb, n3, acc, alpha, out);
 }
 
-void launch_pair_density(const Z64* psi_r, int v, int nb, size_t n3, double scale, Z64* out, hipStream_t st) {
-  if (nb <= 0) return;
-  dim3 grid(grid_blocks(n3, nb), nb);
-  k_pair_density<<<grid, kGridThreads, 0, st>>>(psi_r, v, n3, scale, out);
+void launch_exch_block(const Z64* tau, const Z64* a_r, int n_exc, int nb, int v0, int nv, size_t n3,
+                       const double* scr, const Z64* pc, int n, Z64* acc, hipStream_t st) {
+  if (n_exc <= 0 || nv <= 0) return;
+  const unsigned gx = (unsigned)((n3 + kGridThreads - 1) / kGridThreads);
+  auto go = [&](auto eb, auto ns) {
+    constexpr int EB = decltype(eb)::value, NS = decltype(ns)::value;
+    k_exch_block<kExchBands, EB, NS><<<dim3(gx, (n_exc + EB - 1) / EB), kGridThreads, 0, st>>>(
+        tau, a_r, n_exc, nb, v0, nv, n3, scr, pc, n, acc);
+  };
+  auto with = [&](auto ns) {  // excitations in registers: as few passes over tau as 4 allow, evenly filled
+    const int passes = (n_exc + 3) / 4, eb = (n_exc + passes - 1) / passes;
+    if (eb == 1) go(std::integral_constant<int, 1>{}, ns);
+    else if (eb == 2) go(std::integral_constant<int, 2>{}, ns);
+    else if (eb == 3) go(std::integral_constant<int, 3>{}, ns);
+    else go(std::integral_constant<int, 4>{}, ns);
+  };
+  if (n > 0) with(std::integral_constant<int, kExchScr>{});
+  else with(std::integral_constant<int, 0>{});
 }
 
-void launch_exch_acc(const Z64* tau, const Z64* a_r, int n_exc, int nb, int v, size_t n3, Z64* acc, hipStream_t st) {
-  if (n_exc <= 0 || nb <= 0) return;
-  dim3 grid(grid_blocks(n3, n_exc), n_exc);
-  k_exch_acc<<<grid, kGridThreads, 0, st>>>(tau, a_r, nb, v, n3, acc);
+int scr_proj_stretches(int v0, int nv, int n, size_t n3) {
+  const int groups = (v0 + nv) * ((n + kProjA - 1) / kProjA);  // about 4 workgroups per CU, 4 points a thread or more
+  const size_t want = std::max(1, 1024 / std::max(1, groups));
+  return (int)std::max<size_t>(1, std::min(want, n3 / (4 * kGridThreads)));
+}
+void launch_scr_proj(const Z64* psi_r, const double* scr, const double* c, int n, int v0, int nv, size_t n3,
+                     double scale, Z64* parts, Z64* pc, hipStream_t st) {
+  if (n <= 0 || nv <= 0) return;
+  const int ns = scr_proj_stretches(v0, nv, n, n3), npairs = nv * v0 + nv * (nv + 1) / 2, total = npairs * n;
+  const size_t stretch = (n3 + ns - 1) / ns;
+  k_scr_proj<kExchBands><<<dim3(v0 + nv, ns, (n + kProjA - 1) / kProjA), kGridThreads, 0, st>>>(
+      psi_r, scr, n, v0, nv, n3, stretch, npairs, parts);
+  k_scr_sum<<<(total + 255) / 256, 256, 0, st>>>(parts, ns, total, n, c, scale / (double)n3, pc);
 }
 
 void launch_add(Z64* y, const Z64* x, size_t n, hipStream_t st) {
@@ -198,15 +305,9 @@ void launch_add(Z64* y, const Z64* x, size_t n, hipStream_t st) {
   k_add<<<grid_blocks(n, 1), kGridThreads, 0, st>>>(y, x, n);
 }
 
-void launch_scr_proj(const Z64* rho, const double* w, int n, int nrows, size_t n3, Z64* proj, hipStream_t st) {
+void launch_scr_add(Z64* tau, const double* w, const Z64* pc, int n, int nrows, size_t n3, hipStream_t st) {
   if (n <= 0 || nrows <= 0) return;
-  k_scr_proj<<<dim3(n, nrows), kGridThreads, 0, st>>>(rho, w, n, n3, proj);
-}
-
-void launch_scr_add(Z64* tau, const double* w, const Z64* proj, const double* c, int n, int nrows, size_t n3,
-                    hipStream_t st) {
-  if (n <= 0 || nrows <= 0) return;
-  k_scr_add<<<dim3(grid_blocks(n3, nrows), nrows), kGridThreads, 0, st>>>(tau, w, proj, c, n, n3);
+  k_scr_add<<<dim3(grid_blocks(n3, nrows), nrows), kGridThreads, 0, st>>>(tau, w, pc, n, n3);
 }
 
 }  // namespace stern
