@@ -885,6 +885,239 @@ __global__ __launch_bounds__((PlaneHCfg<N, T>::NT), (PlaneHCfg<N, T>::WPS)) void
   }
 }
 
+// ---- products into pencils and sums out of them, with lines in registers (even N) ----
+//
+// Real-space arrays have z fastest, so these run the plane the other way round: along y on all N values of z,
+// lanes on consecutive z, and along z on the active n_y lines, whose columns are consecutive in n_z.
+
+// columns of (n_y, n_z = 0) and the largest |n_z| there, by line f of n_y = 0..nm, -nm..-1 (the disk of
+// columns is symmetric in y and z, so g.ymax serves both ways)
+template <int N>
+__device__ __forceinline__ void line_columns(int* cy, int* zm, const FftGeom& g, const int* __restrict__ ycol,
+                                             int tid, int nt) {
+  const int nm = g.zact_lo;
+  for (int f = tid; f < g.nza; f += nt) {
+    const int ny = f <= nm ? f : f - g.nza;
+    cy[f] = ycol[(size_t)(ny < 0 ? ny + N : ny) * g.nza];
+    zm[f] = g.ymax[f];
+  }
+}
+template <int N>
+constexpr size_t planem_lds_bytes(int nv, int nza) {
+  using C = PlaneHCfg<N, double>;
+  return ((size_t)nv * nza * C::QLD + 2 * HalfFft<N, double>::TW) * sizeof(Z64) + 2 * (size_t)nza * sizeof(int);
+}
+
+// Pencils of vector i nb + b = forward planes of psi_r[v0 + b] * mul[i] (mul real: the right-hand sides of a
+// batch of bands and fields; complex: V psi of the Liouville apply). Workgroup (ix, b) takes nv fields i at a
+// time, as k_plane_half does with its vectors. 72^3, 128 bands x 16 fields: 3.05 -> 2.85 ms (full planes in
+// LDS before); 128^3, 256 x 4: 17.1 -> 12.9 ms (four stages through LDS). V psi of 8 excitations x 128 bands at
+// 72^3: 1.83 ms, against 2.44 for the products on full grids and 2.13 for their transforms.
+template <int N, class MUL>
+__global__ __launch_bounds__((PlaneHCfg<N, double>::NT), (PlaneHCfg<N, double>::WPS)) void k_plane_mul_half(
+    const Z64* __restrict__ psi_r, const MUL* __restrict__ mul, int v0, int nb, int ni, int nv,
+    Z64* __restrict__ pen, const int* __restrict__ ycol, FftGeom g) {
+  using C = PlaneHCfg<N, double>;
+  using H = HalfFft<N, double>;
+  constexpr int M = H::M, K = H::K, QLD = C::QLD;
+  extern __shared__ unsigned char smem_raw[];
+  const int nza = g.nza, nm = g.zact_lo, tid = threadIdx.x;
+  Z64* Q = reinterpret_cast<Z64*>(smem_raw);
+  Z64* tws = Q + (size_t)nv * nza * QLD;
+  int* cy = reinterpret_cast<int*>(tws + 2 * H::TW);
+  int* zm = cy + nza;
+  H::twiddles(tws, g.tw64, nm, tid, C::NT);
+  line_columns<N>(cy, zm, g, ycol, tid, C::NT);
+  __syncthreads();
+  const int odd = tid & 1;
+  const Z64* tl = tws + odd * H::TW;
+  const int ix = blockIdx.x, b = blockIdx.y;
+  const Z64* __restrict__ ps = psi_r + ((size_t)(v0 + b) * N + ix) * N * N;
+  const int yw = (2 * nv * nza + 63) / 64, zw = (2 * nv * N + 63) / 64;
+  int ry = 0, rz = 0;  // as in k_plane_half
+  for (int i0 = 0; i0 < ni; i0 += nv) {
+    ry = (ry + yw) % C::W;
+    rz = (rz + zw) % C::W;
+    int tq = (tid + 64 * ry) % C::NT, tz = (tid + 64 * rz) % C::NT;
+    asm volatile("" : "+v"(tq), "+v"(tz));
+    for (int it = tz; it < 2 * nv * N; it += C::NT) {
+      const int z = (it >> 1) % N, i = min(i0 + (it >> 1) / N, ni - 1);
+      const int at = odd * N + z;
+      const Z64* __restrict__ pr = ps + at;
+      const MUL* __restrict__ mr = mul + ((size_t)i * N + ix) * N * N + at;
+      Z64 v[M];
+#pragma unroll
+      for (int k = 0; k < M; ++k) {
+        if constexpr (sizeof(MUL) == 8)
+          v[k] = zscale(pr[2 * k * N], mr[2 * k * N]);
+        else
+          v[k] = pr[2 * k * N] * mr[2 * k * N];
+        if (k % 8 == 7) __builtin_amdgcn_sched_barrier(0);
+      }
+      Z64* qr = Q + (size_t)((it >> 1) / N) * nza * QLD + z;
+      Z64* qn = qr + (size_t)nza * QLD;
+      // n > nm writes to a line of the other sign, which a later (smaller) n overwrites
+      Z64* qw = odd ? qn - (K + 1) * QLD : qr + (K + 1) * QLD;
+      const int step = odd ? QLD : -QLD;
+      H::to_freqs(v, tl, odd, [&](int n, Z64 x) {
+        qw += step;
+        if (n == 0) qw = qr;
+        *qw = x;
+      });
+    }
+    __syncthreads();
+    for (int it = tq; it < 2 * nv * nza; it += C::NT) {
+      const int f = (it >> 1) % nza, i = i0 + (it >> 1) / nza;
+      const int lim = i < ni ? zm[f] : -1;
+      Z64* __restrict__ tp = pen + ((size_t)(min(i, ni - 1) * nb + b) * N + ix) * g.ncol_pad;
+      const Z64* q0 = Q + (size_t)(it >> 1) * QLD + odd;
+      int c = odd ? cy[f] - (K + 1) : cy[f] + (K + 1);
+      const int step = odd ? 1 : -1;
+      Z64 v[M];
+#pragma unroll
+      for (int k = 0; k < M; ++k) v[k] = q0[2 * k];
+      // outside the disk: the second padding column, which nothing reads
+      H::to_freqs(v, tl, odd, [&](int n, Z64 x) {
+        c += step;
+        tp[n <= lim ? c : g.ncol + 1] = x;
+      });
+    }
+    __syncthreads();  // the next fields rewrite Q
+  }
+}
+
+// Sums over the bands of conj(psi_v(r)) x_v(r) from the pencils of x: real part into out[pert_out[p]] (the
+// density response), or CPLX the whole (the transition densities). Workgroup (ix, p) takes NB bands at a time,
+// a lane a quarter of a y line with its sums in registers (QuarterFft), each of the NB in lanes of its own; their
+// sums are added in band order at the end. Bound by FP64 issue, with the waves of a band spread unevenly over
+// the SIMDs. Density response, 128^3, 256 bands x 4 fields: 25.3 -> 9.4 ms; 48^3, 54 x 5: 253 -> 143 us. Transition
+// densities, 72^3, 8 excitations x 128 bands: 2.50 ms, against 2.85 for the transforms to full grids and 1.95 for
+// the sums over them.
+template <int N, bool CPLX>
+struct PlaneQCfg {
+  using F = QuarterFft<N, double>;
+  static constexpr int NB = N <= 16 ? 4 : N <= 24 ? 2 : 1;  // for whole waves on small grids
+  static constexpr int NT = (4 * NB * N + 63) / 64 * 64;
+  // waves per SIMD that the line and its sums leave room for, two or more workgroups to a CU up to N = 72
+  static constexpr int WPS = CPLX ? (F::M <= 9 ? 4 : F::M <= 12 ? 3 : 2) : F::M <= 12 ? 4 : F::M <= 18 ? 3 : 2;
+  // lines Q[f][.] are written by groups of four lanes, f apart: 4 mod 8 spreads them over the banks
+  static constexpr int QLD = N + (12 - N % 8) % 8;
+};
+template <int N, bool CPLX>
+constexpr size_t planeq_lds_bytes(int nza, int ncol) {
+  using C = PlaneQCfg<N, CPLX>;
+  const size_t q = (size_t)C::NB * (nza * C::QLD + ncol + 1) * sizeof(Z64);
+  const size_t sums = (size_t)(C::NB - 1) * N * N * (CPLX ? sizeof(Z64) : sizeof(double));
+  return (q > sums ? q : sums) + 4 * (size_t)C::F::TW * sizeof(Z64) + 2 * (size_t)nza * sizeof(int);
+}
+
+template <int N, bool CPLX>
+__global__ __launch_bounds__((PlaneQCfg<N, CPLX>::NT), (PlaneQCfg<N, CPLX>::WPS)) void k_plane_sum_quarter(
+    const Z64* __restrict__ pen, const Z64* __restrict__ psi_r, int band0, int nb, const int* __restrict__ pert_out,
+    double scale, void* __restrict__ out, int np, int seg, const int* __restrict__ ycol, FftGeom g) {
+  using C = PlaneQCfg<N, CPLX>;
+  using F = QuarterFft<N, double>;
+  constexpr int M = F::M, QLD = C::QLD, NB = C::NB, NT = C::NT;
+  extern __shared__ unsigned char smem_raw[];
+  // Workgroup L runs on XCD L mod 8: the np sums of one plane get consecutive slots of one XCD, which so
+  // fetches each band's plane of psi once for all of them.
+  constexpr int NX = (N + 7) / 8;
+  const int slot = blockIdx.x >> 3, ix = (slot / np % NX) * 8 + (blockIdx.x & 7), pl = slot % np, sg = slot / np / NX;
+  if (ix >= N) return;  // whole workgroup, before any barrier
+  const int nza = g.nza, nm = g.zact_lo, tid = threadIdx.x;
+  Z64* tws = reinterpret_cast<Z64*>(smem_raw);
+  Z64* Q = tws + 4 * F::TW;
+  Z64* S = Q + (size_t)NB * nza * QLD;
+  int* cy = reinterpret_cast<int*>(smem_raw + planeq_lds_bytes<N, CPLX>(nza, g.ncol) - 2 * (size_t)nza * sizeof(int));
+  int* zm = cy + nza;
+  F::twiddles(tws, g.tw64, nm, tid, NT);
+  line_columns<N>(cy, zm, g, ycol, tid, NT);
+  __syncthreads();
+  const int p = tid & 3;
+  const Z64* tl = tws + p * F::TW;
+  const int bend = min(nb, (sg + 1) * seg);  // this workgroup's bands: [sg seg, bend)
+  const int z = (tid >> 2) % N, bl = (tid >> 2) / N;  // this lane's z and band slot (bl = NB: none)
+  double re[M], im[CPLX ? M : 1];
+#pragma unroll
+  for (int k = 0; k < M; ++k) {
+    re[k] = 0.0;
+    if (CPLX) im[k] = 0.0;
+  }
+  for (int b0 = sg * seg; b0 < bend; b0 += NB) {
+    int tq = tid;
+    asm volatile("" : "+v"(tq));  // what hangs on it would otherwise be kept in registers
+    // the plane's pencils of each band with the zero column behind the last, in LDS: the lanes below walk
+    // rows of columns that lie apart, and from memory each 128-byte line would be fetched for each of its 8
+    for (int b = 0; b < NB; ++b) {
+      const Z64* __restrict__ tp = pen + ((size_t)(pl * nb + min(b0 + b, bend - 1)) * N + ix) * g.ncol_pad;
+      for (int c = tq; c <= g.ncol; c += NT) S[b * (g.ncol + 1) + c] = tp[c];
+    }
+    __syncthreads();
+    if (tq < 4 * NB * nza) {  // inverse z on the n_y lines
+      const int f = (tq >> 2) % nza, b = (tq >> 2) / nza;
+      const int lim = b0 + b < bend ? zm[f] : -1, c0 = cy[f];
+      const Z64* sp = S + b * (g.ncol + 1);
+      Z64 v[M];
+      F::to_points(v, tl, [&](int n) { return sp[(n < 0 ? -n : n) <= lim ? c0 + n : g.ncol]; });
+      Z64* q0 = Q + (size_t)(tq >> 2) * QLD + p;
+#pragma unroll
+      for (int k = 0; k < M; ++k) q0[4 * k] = v[k];
+    }
+    __syncthreads();
+    if (bl < NB && b0 + bl < bend) {  // inverse y, times conj(psi)
+      const Z64* qr = Q + (size_t)bl * nza * QLD + z;
+      const Z64* qn = qr + (size_t)nza * QLD;
+      const Z64* __restrict__ ps = psi_r + ((size_t)(band0 + b0 + bl) * N + ix) * N * N + p * N + z;
+      Z64 v[M];
+      F::to_points(v, tl, [&](int n) { return n < 0 ? qn[n * QLD] : qr[n * QLD]; });
+#pragma unroll
+      for (int k = 0; k < M; ++k) {
+        const Z64 w = ps[4 * k * N];
+        re[k] += w.re * v[k].re + w.im * v[k].im;
+        if (CPLX) im[k] += w.re * v[k].im - w.im * v[k].re;
+        if (k % 8 == 7) __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    __syncthreads();  // the next bands rewrite Q
+  }
+  using E = std::conditional_t<CPLX, Z64, double>;
+  auto val = [&](int k) {
+    if constexpr (CPLX) return zmk(re[k], im[k]);
+    else return re[k];
+  };
+  E* sums = reinterpret_cast<E*>(Q);
+  if (bl > 0 && bl < NB) {
+#pragma unroll
+    for (int k = 0; k < M; ++k) sums[(size_t)(bl - 1) * N * N + (p + 4 * k) * N + z] = val(k);
+  }
+  __syncthreads();
+  if (bl != 0) return;
+  const size_t row = pert_out ? pert_out[pl] : (size_t)sg * np + pl;
+  E* __restrict__ dp = reinterpret_cast<E*>(out) + (row * N + ix) * N * N;
+#pragma unroll
+  for (int k = 0; k < M; ++k) {
+    E t = val(k);
+    for (int b = 1; b < NB; ++b) {
+      if constexpr (CPLX) t = t + sums[(size_t)(b - 1) * N * N + (p + 4 * k) * N + z];
+      else t += sums[(size_t)(b - 1) * N * N + (p + 4 * k) * N + z];
+    }
+    if constexpr (CPLX) dp[(p + 4 * k) * N + z] = zscale(t, scale);
+    else dp[(p + 4 * k) * N + z] = scale * t;
+  }
+}
+
+// out[pert_out[p]][j] = sum over the segments s of part[s][p][j], in order (doubles; a complex grid is two)
+__global__ __launch_bounds__(256) void k_sum_segments(const double* __restrict__ part, int ns, int np, size_t n,
+                                                      const int* __restrict__ pert_out, double* __restrict__ out) {
+  const int p = blockIdx.y;
+  double* __restrict__ o = out + (pert_out ? pert_out[p] : (size_t)p) * n;
+  for (size_t j = (size_t)blockIdx.x * 256 + threadIdx.x; j < n; j += (size_t)gridDim.x * 256) {
+    double t = 0.0;
+    for (int s = 0; s < ns; ++s) t += part[((size_t)s * np + p) * n + j];
+    o[j] = t;
+  }
+}
+
 // Right-hand sides of one band for every field of a batch: workgroup (ix, bb) keeps
 // plane ix of psi_{v0 + bb}(r) in registers (the items of its first stage) and, for
 // each field pl, forms psi * dv, transforms the plane and writes the pencils of solve
@@ -1526,11 +1759,99 @@ size_t cw_lds_bytes(int nza) {
   return ((size_t)nza * (N + 1) + N + (size_t)CwCfg<N>::W * N * CwCfg<N>::ZR) * sizeof(Z64);
 }
 
+namespace {
+template <int NN, class MUL>
+void plane_mul_half_n(const FftGeom& g, const Z64* psi_r, const MUL* mul, int v0, int nb, int ni, Z64* pen,
+                      hipStream_t st) {
+  const int nv = std::min(PlaneHCfg<NN, double>::NV, ni);
+  const size_t lds = planem_lds_bytes<NN>(nv, g.nza);
+  set_lds((const void*)k_plane_mul_half<NN, MUL>, 160 * 1024);
+  k_plane_mul_half<NN, MUL><<<dim3(NN, nb), PlaneHCfg<NN, double>::NT, lds, st>>>(psi_r, mul, v0, nb, ni, nv, pen,
+                                                                                 g.ycol, g);
+}
+// segments of the bands whose sums run in workgroups of their own: enough workgroups for four rounds over the card,
+// of 8 bands or more, and a scratch of the sums (a grid per segment and sum) within 512 MiB
+template <int NN, bool CPLX>
+int sum_segments(const FftGeom& g, int nb, int np) {
+  const long slots = (long)g.n_cu * blocks_per_cu((const void*)k_plane_sum_quarter<NN, CPLX>, PlaneQCfg<NN, CPLX>::NT,
+                                                  planeq_lds_bytes<NN, CPLX>(g.nza, g.ncol));
+  const long wgs = (long)NN * np, grid = (long)NN * NN * NN * (CPLX ? 16 : 8) * np;
+  return (int)std::max<long>(1, std::min<long>({(4 * slots + wgs - 1) / wgs, nb / 8, (512l << 20) / grid}));
+}
+template <int NN, bool CPLX>
+void plane_sum_quarter_n(const FftGeom& g, const Z64* pen, const Z64* psi_r, int band0, int nb, int np,
+                         const int* pert_out, double scale, double* part, double* out, hipStream_t st) {
+  using C = PlaneQCfg<NN, CPLX>;
+  const size_t lds = planeq_lds_bytes<NN, CPLX>(g.nza, g.ncol), n = (size_t)NN * NN * NN * (CPLX ? 2 : 1);
+  const int want = part ? sum_segments<NN, CPLX>(g, nb, np) : 1, seg = (nb + want - 1) / want;
+  const int ns = (nb + seg - 1) / seg;
+  k_plane_sum_quarter<NN, CPLX><<<(unsigned)((NN + 7) / 8 * 8 * np * ns), C::NT, lds, st>>>(
+      pen, psi_r, band0, nb, ns > 1 ? nullptr : pert_out, scale, ns > 1 ? part : out, np, seg, g.ycol, g);
+  if (ns > 1)
+    k_sum_segments<<<dim3((unsigned)std::min<size_t>((n + 255) / 256, 1024), np), 256, 0, st>>>(part, ns, np, n,
+                                                                                              pert_out, out);
+}
+template <int NN>
+constexpr bool quarter_grid() {
+  return NN % 4 == 0;
+}
+// Whether k_plane_sum_quarter runs on this geometry. The density response at N = 72 stays with the full plane
+// in LDS: 4 N lanes are 5 waves there, so one SIMD does twice the others' work (128 bands x 16 fields: 5.9
+// against 4.75 ms); the transition densities still gain, as they take the place of two passes over full grids.
+template <int NN, bool CPLX>
+bool quarter_plane(const FftGeom& g) {
+  if constexpr (!quarter_grid<NN>() || (!CPLX && PlaneQCfg<NN, CPLX>::NT == 320)) return false;
+  else return half_plane<NN, double>(g.zact_lo) && planeq_lds_bytes<NN, CPLX>(g.nza, g.ncol) <= 160 * 1024;
+}
+}  // namespace
+
+bool plane_products_fit(const FftGeom& g) {
+  bool ok = false;
+  STERN_DISPATCH_N(g.N, (ok = NN <= 96 && quarter_plane<NN, true>(g)));
+  return ok;
+}
+
+void launch_plane_mul_fwd(const FftGeom& g, const Z64* psi_r, const Z64* v_r, int nb, int n_exc, Z64* pen,
+                          hipStream_t st) {
+  if (nb <= 0 || n_exc <= 0) return;
+  STERN_DISPATCH_N(g.N, ({
+                     if constexpr (half_grid<NN, double>() && NN <= 96)
+                       plane_mul_half_n<NN, Z64>(g, psi_r, v_r, 0, nb, n_exc, pen, st);
+                   }));
+}
+
+size_t plane_sum_scratch(const FftGeom& g, int nb, int np, bool cplx) {
+  int ns = 1;
+  STERN_DISPATCH_N(g.N, ({
+                     if constexpr (quarter_grid<NN>() && NN <= 96) {
+                       if (cplx && quarter_plane<NN, true>(g)) ns = sum_segments<NN, true>(g, nb, np);
+                     }
+                     if constexpr (quarter_grid<NN>()) {
+                       if (!cplx && quarter_plane<NN, false>(g)) ns = sum_segments<NN, false>(g, nb, np);
+                     }
+                   }));
+  return ns > 1 ? (size_t)ns * np * g.N * g.N * g.N * (cplx ? 16 : 8) : 0;
+}
+
+void launch_plane_rho(const FftGeom& g, const Z64* pen, const Z64* psi_r, int nb, int n_exc, double scale,
+                      double* part, Z64* rho, hipStream_t st) {
+  if (nb <= 0 || n_exc <= 0) return;
+  STERN_DISPATCH_N(g.N, ({
+                     if constexpr (quarter_grid<NN>() && NN <= 96)
+                       plane_sum_quarter_n<NN, true>(g, pen, psi_r, 0, nb, n_exc, nullptr, scale, part,
+                                                      reinterpret_cast<double*>(rho), st);
+                   }));
+}
+
 void launch_plane_rhs(const FftGeom& g, const Z64* psi_r, const double* dv, int v0, int nb, int i0, int npert,
                       const int* band, const int* pert, Z64* pen, hipStream_t st) {
   if (nb <= 0 || npert <= 0) return;
   STERN_DISPATCH_N(g.N, ({
-                     if constexpr (full_plane_fits<NN>()) {
+                     if (half_plane<NN, double>(g.zact_lo)) {
+                       if constexpr (half_grid<NN, double>())
+                         plane_mul_half_n<NN, double>(g, psi_r, dv + (size_t)i0 * NN * NN * NN, v0, nb, npert, pen,
+                                                      st);
+                     } else if constexpr (full_plane_fits<NN>()) {
                        const size_t lds = plane_lds_bytes(NN, sizeof(Z64));
                        set_lds((const void*)k_plane_rhs_bands<NN>, lds);
                        k_plane_rhs_bands<NN><<<dim3(NN, nb), plane_nt<NN>(), lds, st>>>(psi_r, dv, v0, nb, i0,
@@ -1580,11 +1901,14 @@ void launch_plane_pair_fwd(const FftGeom& g, const Z64* psi_r, int v0, int npair
 }
 
 void launch_plane_dn(const FftGeom& g, const Z64* pen, const Z64* psi_r, int band0, int nb, int npert,
-                     const int* pert_out, double scale, double* dn, hipStream_t st) {
+                     const int* pert_out, double scale, double* part, double* dn, hipStream_t st) {
   if (npert <= 0 || nb <= 0) return;
   dim3 grid(g.N, npert);
   STERN_DISPATCH_N(g.N, ({
-                     if constexpr (full_plane_fits<NN>()) {
+                     if (quarter_plane<NN, false>(g)) {
+                       if constexpr (quarter_grid<NN>())
+                         plane_sum_quarter_n<NN, false>(g, pen, psi_r, band0, nb, npert, pert_out, scale, part, dn, st);
+                     } else if constexpr (full_plane_fits<NN>()) {
                        const size_t lds = plane_lds_bytes(NN, sizeof(Z64));
                        set_lds((const void*)k_plane_dn<NN>, lds);
                        k_plane_dn<NN><<<grid, plane_nt<NN>(), lds, st>>>(pen, psi_r, band0, nb, pert_out, scale,

@@ -71,9 +71,19 @@ void launch_plane_rhs(const FftGeom& g, const Z64* psi_r, const double* dv, int 
                       const int* band, const int* pert, Z64* pen, hipStream_t st);
 // yz planes, inverse to a full real-space grid: out[vec] = [N][N][N] complex.
 void launch_plane_full_inv(const FftGeom& g, const Z64* pen, int nvec, Z64* out, hipStream_t st);
+// Products and sums of the Liouville apply with lines in registers, on grids up to 96 where plane_products_fit:
+// pencils of vector e nb + v = forward planes of v_r[e] psi_r[v] (complex grids v_r), and
+// rho[e] = scale sum_v conj(psi_r[v]) a_{e nb + v}(r) from the pencils of a
+bool plane_products_fit(const FftGeom& g);
+void launch_plane_mul_fwd(const FftGeom& g, const Z64* psi_r, const Z64* v_r, int nb, int n_exc, Z64* pen,
+                          hipStream_t st);
+// (part: scratch of plane_sum_scratch bytes, as for launch_plane_dn)
+void launch_plane_rho(const FftGeom& g, const Z64* pen, const Z64* psi_r, int nb, int n_exc, double scale,
+                      double* part, Z64* rho, hipStream_t st);
+size_t plane_sum_scratch(const FftGeom& g, int nb, int np, bool cplx);
 // dn[pert_out[p]] = scale * Re sum_{b < nb} conj(psi_r[band0 + b]) * x_r[p * nb + b], from pencils.
 void launch_plane_dn(const FftGeom& g, const Z64* pen, const Z64* psi_r, int band0, int nb, int npert,
-                     const int* pert_out, double scale, double* dn, hipStream_t st);
+                     const int* pert_out, double scale, double* part, double* dn, hipStream_t st);
 
 // C[n][m] = sum_k conj(A[m][k]) X[xidx[n]][k]; partial sums per K split, rows m < M (rounded up to 16).
 // A: [M_pad][K] (M_pad multiple of 64, rows from M on zero), X rows of length ldx, K multiple of 64.

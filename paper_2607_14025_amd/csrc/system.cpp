@@ -179,6 +179,7 @@ struct stern_system {
   DBuf wx, wr, wp, wq, wz, wb, pen, cpart, cpart2, cmat, sv_eps, sv_invT, sv_band, sv_pert, sv_bb, sv_rz, sv_rr, sv_flag,
       sv_iters, sv_tres, list_act, list_f, pert_out, dv_dev, dn_dev, tmp_in, tmp_out;
   DBuf m_d, m_r, m_p, m_q, m_z, m_rz, m_rr0, m_beta, m_flag, m_part;  // mixed inner solve
+  DBuf sum_part;              // segments of the band sums (density response, transition densities)
   DBuf m_cnt;                 // device count of the inner solve's active list (list_f)
   DBuf negk;                  // [npw_pad] index of -G of each coefficient (column order)
   DBuf sv_rzi;                // [nbatch] imaginary parts of the shifted solves' (r, z)_J
@@ -296,7 +297,7 @@ struct stern_system {
                    &sv_rr,     &sv_flag,  &sv_iters, &sv_tres, &list_act, &list_f,  &pert_out, &dv_dev,   &dn_dev,
                    &tmp_in,    &tmp_out,  &psi_hi,  &psi_lo,   &psiT_hi, &psiT_lo,  &kb_hi,    &kb_lo,
                    &kbT_hi,    &kbT_lo,   &m_d,     &m_r,      &m_p,     &m_q,      &m_z,      &m_rz,  &m_beta,
-                   &m_rr0,     &m_flag, &m_part,   &c_col_start, &c_col_len, &c_col_xmin, &c_col_pos, &c_zl, &c_ycol,
+                   &m_rr0,     &m_flag, &m_part, &sum_part,   &c_col_start, &c_col_len, &c_col_xmin, &c_col_pos, &c_zl, &c_ycol,
                    &c_tw64,    &psi_c,    &c_pen,   &c_field,  &net_a0,  &net_a1,   &net_a2,   &net_out,
                    &g_rej,     &net_feat, &net_coef, &kprec,  &v_t,     &v_t32,    &band_eps, &band_invT,
                    &band_feat, &projT_hi, &projT_lo, &cpart2, &m_cnt, &negk, &sv_rzi, &xkeep,
@@ -608,6 +609,12 @@ int ensure_workspace32(stern_system* S, int ns) {
     S->ws32_solves = ns;
   }
   return 0;
+}
+
+// scratch of the band sums' segments; null (one segment) where none is needed or the memory is not there
+double* sum_scratch(stern_system* S, int nb, int np, bool cplx) {
+  const size_t bytes = plane_sum_scratch(S->geom(), nb, np, cplx);
+  return bytes == 0 || S->sum_part.ensure(bytes) < 0 ? nullptr : S->sum_part.as<double>();
 }
 
 Cg32State cg32_state(stern_system* S, int* iters) {
@@ -1599,6 +1606,11 @@ static int exch_bands(const stern_system* S) {
   return (int)std::max<size_t>(1, std::min<size_t>({(size_t)kExchBands, ((size_t)3 << 29) / grids, (size_t)S->n_occ}));
 }
 
+// whether the Hartree part runs without full grids of a_v(r) (the direct term needs them)
+static bool liouville_fused(const stern_system* S) {
+  return S->lv_alpha == 0.0 && S->n_scr == 0 && plane_products_fit(S->geom());
+}
+
 // out = L A for n_exc excitations of n_occ band rows each (column order, stride npw_pad; A in
 // range(P_c)): out_v = P_c [ (H - eps_v) a_v + 2 V[rho_A] psi_v - alpha sum_w tau_{wv} a_w ],
 // rho_A = sum_v conj(psi_v) a_v, tau_{wv} = V[conj(psi_w) psi_v] (eq. tau_u),
@@ -1610,11 +1622,13 @@ static int liouville_rows(stern_system* S, const Z64* A, Z64* out, int n_exc) {
   hipStream_t st = S->stream;
   const FftGeom g = S->geom();
   const int Kd = S->hbd.npw_pad;
-  const int ce = liouville_chunk(S, n_exc);
+  const bool fused = liouville_fused(S);
+  // excitations at a time: what the pencils hold, or the full grids
+  const int ce = fused ? std::max(1, std::min({n_exc, S->ws_solves / nb, 65535 / nb})) : liouville_chunk(S, n_exc);
   const bool exch = S->lv_alpha != 0.0 || S->n_scr > 0;
   const int vb = exch ? exch_bands(S) : 0;
   const int np = std::max(ce, vb * nb);  // grids through the potential stage at once
-  CHECKED(S->lv_ar.ensure((size_t)ce * nb * n3 * sizeof(Z64)));
+  if (!fused) CHECKED(S->lv_ar.ensure((size_t)ce * nb * n3 * sizeof(Z64)));
   CHECKED(S->lv_rho.ensure((size_t)ce * n3 * sizeof(Z64)));
   CHECKED(S->lv_rhog.ensure((size_t)np * Kd * sizeof(Z64)));
   CHECKED(S->lv_pend.ensure((size_t)np * N * S->hbd.ncol_pad * sizeof(Z64)));
@@ -1642,16 +1656,25 @@ static int liouville_rows(stern_system* S, const Z64* A, Z64* out, int n_exc) {
   Z64* ar = S->lv_ar.as<Z64>();
   Z64* rho = S->lv_rho.as<Z64>();
   Z64* kt = S->lv_k.as<Z64>();
-  launch_fill_zero(kt, (size_t)n * K, st);  // the padding entries are added to out below
+  if (!fused) launch_fill_zero(kt, (size_t)n * K, st);  // the padding entries are added to out below
   for (int e0 = 0; e0 < n_exc; e0 += ce) {
     const int c = std::min(ce, n_exc - e0), m = c * nb;
     const Z64* Ae = A + (size_t)e0 * nb * K;
+    constexpr double kPi = 3.14159265358979323846;
+    if (fused) {  // densities from the pencils of a, and the products into pencils: no full grids of a
+      launch_xinv(g, Ae, nullptr, m, S->pen.as<Z64>(), st);
+      launch_plane_rho(g, S->pen.as<Z64>(), S->psi_r.as<Z64>(), nb, c, 1.0 / hb.omega, sum_scratch(S, nb, c, true), rho, st);
+      potential_grids(S, rho, c, 4.0 * kPi);  // the factor 2 of the singlet exchange term folded in
+      launch_plane_mul_fwd(g, S->psi_r.as<Z64>(), rho, nb, c, S->pen.as<Z64>(), st);
+      launch_xfwd<double>(g, S->pen.as<Z64>(), nullptr, m, kt + (size_t)e0 * nb * K, 2, nullptr, nullptr,
+                          1.0 / (double)n3, st);
+      continue;
+    }
     for (int r0 = 0; r0 < m; r0 += S->ws_solves) {  // pencils hold ws_solves rows
       const int rm = std::min(S->ws_solves, m - r0);
       launch_xinv(g, Ae + (size_t)r0 * K, nullptr, rm, S->pen.as<Z64>(), st);
       launch_plane_full_inv(g, S->pen.as<Z64>(), rm, ar + (size_t)r0 * n3, st);
     }
-    constexpr double kPi = 3.14159265358979323846;
     if (exch) {
       // sum_w tau_{wv} a_w of every band v: the potentials of the pairs w <= v, a block of bands at a time
       Z64 *tau = S->lv_tau.as<Z64>(), *acc = S->lv_acc.as<Z64>(), *pc = S->scr_proj.as<Z64>();
@@ -2330,11 +2353,12 @@ static int apply_chi0_impl(stern_system* S, int n_pert, const double* dv_r, doub
     // dn_i = 4/Omega Re sum_v conj(psi_v(r)) x_{v,i}(r)
     CHECKED(timed(S, STERN_K_XINV, ns * (vecb + (double)N * hb.ncol * 16.0), 0.0,
                   [&] { launch_xinv(g, cs.x, nullptr, ns, S->pen.as<Z64>(), st); }));
+    double* part = sum_scratch(S, nb, i1 - i0, false);
     CHECKED(timed(S, STERN_K_DN,
                   ns * (double)N * hb.ncol * 16.0 + (double)(i1 - i0) * nb * n3 * 16.0 + (double)(i1 - i0) * n3 * 8.0,
                   0.0, [&] {
                     launch_plane_dn(g, S->pen.as<Z64>(), S->psi_r.as<Z64>(), v0, nb, i1 - i0,
-                                    S->pert_out.as<int>() + i0, 4.0 / hb.omega, dn_dev, st);
+                                    S->pert_out.as<int>() + i0, 4.0 / hb.omega, part, dn_dev, st);
                   }));
     CHECKED(launch_check());
     // per-solve statistics
