@@ -531,7 +531,8 @@ __global__ __launch_bounds__(256) void k_sum_proj(const Z32* __restrict__ cp_a, 
 int choose_nsplit_bf16(int M_pad, int ncols, int K, int target) {
   if (target <= 0) target = kBf16TargetGroups;
   const int base = ((M_pad + kWM - 1) / kWM) * ((ncols + kWN - 1) / kWN);
-  int ns = (target + base - 1) / base;
+  // at most `target` workgroups: one fills a CU (128 KiB of LDS), so 515 for 512 would be a third round
+  int ns = target / base;
   // chunks of 128 k or more: 4 steps, after which splitting further costs more in the sums than it saves
   const int maxs = K / 128 > 0 ? K / 128 : 1;
   if (ns > maxs) ns = maxs;
