@@ -150,20 +150,17 @@ __global__ __launch_bounds__(kCgThreads) void k_cg_init2(CgState S, const int* _
   if (threadIdx.x == 0) S.rz[s] = rz;
 }
 
-// alpha = <r,z> / <p,q>; x += alpha p; r -= alpha q; z = K r; flag on ||r|| <= tol ||b||
-template <bool LK>
-__global__ __launch_bounds__(kCgThreads) void k_cg_alpha(CgState S, const int* __restrict__ act, double tol2) {
-  __shared__ double sh[kCgThreads / 64];
-  const int s = act ? act[blockIdx.x] : blockIdx.x;
-  if (S.flag[s] != 0) return;
-  const size_t o = (size_t)s * S.npw_pad;
-  const int n = S.npw_pad;
+// alpha = <r,z> / <p,q>; x += alpha p; r -= alpha q; z = K r; flag on ||r|| <= tol ||b||; the new (r, z) and
+// beta = (r, z) new / old for the direction update that follows. (r, z) is taken with z before its projection:
+// r stays in range(P_c), so it equals (r, P_c z), and the projection of z and p = P_c z + beta p run as one.
+// A row of the stretch [k0, n): the parts of (p, q), and of ||r||^2 and (r, z) after the update.
+__device__ __forceinline__ double cg_pq(const CgState& S, size_t o, int k0, int n) {
   double pq = 0.0;
-  for (int k0 = threadIdx.x; k0 < n; k0 += kCgThreads * kU) {
+  for (int k1 = k0 + threadIdx.x; k1 < n; k1 += kCgThreads * kU) {
     Z64 p[kU], q[kU];
 #pragma unroll
     for (int u = 0; u < kU; ++u) {
-      const int k = k0 + u * kCgThreads;
+      const int k = k1 + u * kCgThreads;
       if (k < n) {
         p[u] = S.p[o + k];
         q[u] = S.q[o + k];
@@ -171,18 +168,19 @@ __global__ __launch_bounds__(kCgThreads) void k_cg_alpha(CgState S, const int* _
     }
 #pragma unroll
     for (int u = 0; u < kU; ++u)
-      if (k0 + u * kCgThreads < n) pq += p[u].re * q[u].re + p[u].im * q[u].im;
+      if (k1 + u * kCgThreads < n) pq += p[u].re * q[u].re + p[u].im * q[u].im;
   }
-  pq = block_sum(pq, sh);
-  const double alpha = (pq > 0.0) ? S.rz[s] / pq : 0.0;
-  const double iT = S.invT[s];
-  double rr = 0.0;
-  for (int k0 = threadIdx.x; k0 < n; k0 += kCgThreads * kU) {
+  return pq;
+}
+template <bool LK>
+__device__ __forceinline__ void cg_update(const CgState& S, int s, size_t o, int k0, int n, double alpha, double iT,
+                                          double& rr, double& rz) {
+  for (int k1 = k0 + threadIdx.x; k1 < n; k1 += kCgThreads * kU) {
     Z64 p[kU], q[kU], x[kU], r[kU];
     double t[kU];
 #pragma unroll
     for (int u = 0; u < kU; ++u) {
-      const int k = k0 + u * kCgThreads;
+      const int k = k1 + u * kCgThreads;
       if (k < n) {
         p[u] = S.p[o + k];
         q[u] = S.q[o + k];
@@ -193,66 +191,86 @@ __global__ __launch_bounds__(kCgThreads) void k_cg_alpha(CgState S, const int* _
     }
 #pragma unroll
     for (int u = 0; u < kU; ++u) {
-      const int k = k0 + u * kCgThreads;
+      const int k = k1 + u * kCgThreads;
       if (k < n) {
         const Z64 xn = zmk(x[u].re + alpha * p[u].re, x[u].im + alpha * p[u].im);
         const Z64 rn = zmk(r[u].re - alpha * q[u].re, r[u].im - alpha * q[u].im);
+        const Z64 z = zscale(rn, precond_eval<LK>(t[u], iT));
         S.x[o + k] = xn;
         S.r[o + k] = rn;
+        S.z[o + k] = z;
         rr += rn.re * rn.re + rn.im * rn.im;
-        S.z[o + k] = zscale(rn, precond_eval<LK>(t[u], iT));
+        rz += rn.re * z.re + rn.im * z.im;
       }
     }
   }
-  rr = block_sum(rr, sh);
-  if (threadIdx.x == 0) {
-    S.rr[s] = rr;
-    S.iters[s] += 1;
-    if (rr <= tol2 * S.bb[s] || !(pq > 0.0)) S.flag[s] = 1;
-  }
+}
+__device__ __forceinline__ void cg_scalars(const CgState& S, int s, double pq, double rr, double rz, double tol2) {
+  const double rz_old = S.rz[s];
+  S.rr[s] = rr;
+  S.iters[s] += 1;
+  if (rr <= tol2 * S.bb[s] || !(pq > 0.0)) S.flag[s] = 1;
+  S.beta[s] = rz_old != 0.0 ? rz / rz_old : 0.0;
+  S.rz[s] = rz;
 }
 
-// beta = <r,z>_new / <r,z>_old; p = z + beta p
-__global__ __launch_bounds__(kCgThreads) void k_cg_beta(CgState S, const int* __restrict__ act) {
+template <bool LK>
+__global__ __launch_bounds__(kCgThreads) void k_cg_alpha(CgState S, const int* __restrict__ act, double tol2) {
   __shared__ double sh[kCgThreads / 64];
   const int s = act ? act[blockIdx.x] : blockIdx.x;
   if (S.flag[s] != 0) return;
   const size_t o = (size_t)s * S.npw_pad;
-  const int n = S.npw_pad;
-  double rz = 0.0;
-  for (int k0 = threadIdx.x; k0 < n; k0 += kCgThreads * kU) {
-    Z64 r[kU], z[kU];
-#pragma unroll
-    for (int u = 0; u < kU; ++u) {
-      const int k = k0 + u * kCgThreads;
-      if (k < n) {
-        r[u] = S.r[o + k];
-        z[u] = S.z[o + k];
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < kU; ++u)
-      if (k0 + u * kCgThreads < n) rz += r[u].re * z[u].re + r[u].im * z[u].im;
-  }
+  const double pq = block_sum(cg_pq(S, o, 0, S.npw_pad), sh);
+  double rr = 0.0, rz = 0.0;
+  cg_update<LK>(S, s, o, 0, S.npw_pad, (pq > 0.0) ? S.rz[s] / pq : 0.0, S.invT[s], rr, rz);
+  rr = block_sum(rr, sh);
   rz = block_sum(rz, sh);
-  const double beta = rz / S.rz[s];
-  for (int k0 = threadIdx.x; k0 < n; k0 += kCgThreads * kU) {
-    Z64 z[kU], p[kU];
-#pragma unroll
-    for (int u = 0; u < kU; ++u) {
-      const int k = k0 + u * kCgThreads;
-      if (k < n) {
-        z[u] = S.z[o + k];
-        p[u] = S.p[o + k];
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < kU; ++u) {
-      const int k = k0 + u * kCgThreads;
-      if (k < n) S.p[o + k] = zmk(z[u].re + beta * p[u].re, z[u].im + beta * p[u].im);
-    }
+  if (threadIdx.x == 0) cg_scalars(S, s, pq, rr, rz, tol2);
+}
+
+// The same for long rows, kCgChunk coefficients to a workgroup, the sums in parts added in order by the next
+// kernel: a few late rows in one workgroup each would leave the card idle (16,896 coefficients: 45 us a
+// launch for one row).
+constexpr int kCgChunk = 2048;
+__global__ __launch_bounds__(kCgThreads) void k_cg_pq(CgState S, const int* __restrict__ act) {
+  __shared__ double sh[kCgThreads / 64];
+  const int s = act ? act[blockIdx.y] : blockIdx.y;
+  if (S.flag[s] != 0) return;
+  const int k0 = blockIdx.x * kCgChunk;
+  const double pq = block_sum(cg_pq(S, (size_t)s * S.npw_pad, k0, min(S.npw_pad, k0 + kCgChunk)), sh);
+  if (threadIdx.x == 0) S.part[((size_t)s * gridDim.x + blockIdx.x) * 3] = pq;
+}
+template <bool LK>
+__global__ __launch_bounds__(kCgThreads) void k_cg_chunk(CgState S, const int* __restrict__ act) {
+  __shared__ double sh[kCgThreads / 64];
+  const int s = act ? act[blockIdx.y] : blockIdx.y;
+  if (S.flag[s] != 0) return;
+  double* part = S.part + (size_t)s * gridDim.x * 3;
+  double pq = 0.0, rr = 0.0, rz = 0.0;
+  for (int c = 0; c < (int)gridDim.x; ++c) pq += part[c * 3];
+  const int k0 = blockIdx.x * kCgChunk;
+  cg_update<LK>(S, s, (size_t)s * S.npw_pad, k0, min(S.npw_pad, k0 + kCgChunk), (pq > 0.0) ? S.rz[s] / pq : 0.0,
+                S.invT[s], rr, rz);
+  rr = block_sum(rr, sh);
+  rz = block_sum(rz, sh);
+  if (threadIdx.x == 0) {
+    part[blockIdx.x * 3 + 1] = rr;
+    part[blockIdx.x * 3 + 2] = rz;
   }
-  if (threadIdx.x == 0) S.rz[s] = rz;
+}
+__global__ void k_cg_finish(CgState S, const int* __restrict__ act, int nrows, int nchunk, double tol2) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= nrows) return;
+  const int s = act ? act[i] : i;
+  if (S.flag[s] != 0) return;
+  const double* part = S.part + (size_t)s * nchunk * 3;
+  double pq = 0.0, rr = 0.0, rz = 0.0;
+  for (int c = 0; c < nchunk; ++c) {
+    pq += part[c * 3];
+    rr += part[c * 3 + 1];
+    rz += part[c * 3 + 2];
+  }
+  cg_scalars(S, s, pq, rr, rz, tol2);
 }
 
 __global__ void k_copy_rows(const Z64* __restrict__ src, Z64* __restrict__ dst, int ld, const int* __restrict__ act) {
@@ -910,15 +928,21 @@ void launch_to32(const Z64* x, Z32* y, size_t n, hipStream_t st) {
 void launch_cg_init2(const CgState& s, const int* act, int n, hipStream_t st) {
   if (n > 0) k_cg_init2<<<n, kCgThreads, 0, st>>>(s, act);
 }
+int cg_chunks(int npw_pad) { return npw_pad <= 2 * kCgChunk ? 0 : (npw_pad + kCgChunk - 1) / kCgChunk; }
 void launch_cg_alpha(const CgState& s, const int* act, int n, double tol2, hipStream_t st) {
   if (n <= 0) return;
-  if (s.kprec)
+  if (const int nc = cg_chunks(s.npw_pad)) {
+    k_cg_pq<<<dim3(nc, n), kCgThreads, 0, st>>>(s, act);
+    if (s.kprec)
+      k_cg_chunk<true><<<dim3(nc, n), kCgThreads, 0, st>>>(s, act);
+    else
+      k_cg_chunk<false><<<dim3(nc, n), kCgThreads, 0, st>>>(s, act);
+    k_cg_finish<<<(n + 255) / 256, 256, 0, st>>>(s, act, n, nc, tol2);
+  } else if (s.kprec) {
     k_cg_alpha<true><<<n, kCgThreads, 0, st>>>(s, act, tol2);
-  else
+  } else {
     k_cg_alpha<false><<<n, kCgThreads, 0, st>>>(s, act, tol2);
-}
-void launch_cg_beta(const CgState& s, const int* act, int n, hipStream_t st) {
-  if (n > 0) k_cg_beta<<<n, kCgThreads, 0, st>>>(s, act);
+  }
 }
 void launch_copy_rows(const Z64* src, Z64* dst, int ld, const int* act, int n, hipStream_t st) {
   if (n > 0) k_copy_rows<<<n, 256, 0, st>>>(src, dst, ld, act);

@@ -26,13 +26,18 @@ __device__ __forceinline__ v4d mfma(double a, double b, v4d c) {
 constexpr int kGemmThreads = 256;  // 4 waves, 2 x 2 arrangement of 32 x 32 wave tiles
 
 // C[n][m] (partial over the K range of this split) = sum_k conj(A[m][k]) X[xidx[n]][k]
-__global__ __launch_bounds__(kGemmThreads) void k_zgemm_reduce(const Z64* __restrict__ A, int M_pad,
-                                                               const Z64* __restrict__ X, int ldx,
+// for one operand, or two with rows X of their own (blocks of 64 rows m from mb0 on belong to the second)
+__global__ __launch_bounds__(kGemmThreads) void k_zgemm_reduce(ZRows s0, ZRows s1, int mb0, int ldx,
                                                                const int* __restrict__ xidx, int ncols, int K,
-                                                               int kchunk, Z64* __restrict__ cpart, int M) {
+                                                               int kchunk) {
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int l16 = lane & 15, g = lane >> 4;
-  const int m0 = blockIdx.x * 64 + (wave & 1) * 32;
+  const bool second = (int)blockIdx.x >= mb0;
+  const Z64* __restrict__ A = second ? s1.A : s0.A;
+  const Z64* __restrict__ X = second ? s1.X : s0.X;
+  Z64* __restrict__ cpart = second ? s1.part : s0.part;
+  const int M_pad = second ? s1.M_pad : s0.M_pad, M = second ? s1.M : s0.M;
+  const int m0 = ((int)blockIdx.x - (second ? mb0 : 0)) * 64 + (wave & 1) * 32;
   const int n0 = blockIdx.y * 64 + (wave >> 1) * 32;
   if (m0 >= M || n0 >= ncols) return;  // padding only (no barrier, no LDS)
   const int split = blockIdx.z;
@@ -120,13 +125,17 @@ __global__ __launch_bounds__(kGemmThreads) void k_zgemm_reduce(const Z64* __rest
 // steps ahead. M = 16 (64 with padding), 7 columns, K = 576: 48 -> 7 us; M = 128, 16 columns, K = 16,896:
 // 48 -> 13 us.
 template <int BJ>
-__global__ __launch_bounds__(kGemmThreads) void k_zgemm_reduce_cols(const Z64* __restrict__ A, int M_pad,
-                                                                    const Z64* __restrict__ X, int ldx,
+__global__ __launch_bounds__(kGemmThreads) void k_zgemm_reduce_cols(ZRows s0, ZRows s1, int mb0, int ldx,
                                                                     const int* __restrict__ xidx, int ncols, int K,
-                                                                    int kchunk, Z64* __restrict__ cpart, int M) {
+                                                                    int kchunk) {
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int l16 = lane & 15, g = lane >> 4;
-  const int m0 = blockIdx.x * 64 + wave * 16;
+  const bool second = (int)blockIdx.x >= mb0;
+  const Z64* __restrict__ A = second ? s1.A : s0.A;
+  const Z64* __restrict__ X = second ? s1.X : s0.X;
+  Z64* __restrict__ cpart = second ? s1.part : s0.part;
+  const int M_pad = second ? s1.M_pad : s0.M_pad, M = second ? s1.M : s0.M;
+  const int m0 = ((int)blockIdx.x - (second ? mb0 : 0)) * 64 + wave * 16;
   const int split = blockIdx.z;
   const int kb = split * kchunk, ke = min(K, kb + kchunk);  // a multiple of 16 apart
   if (m0 >= M) return;  // padding only (no barrier, no LDS)
@@ -192,12 +201,16 @@ __global__ __launch_bounds__(kGemmThreads) void k_zgemm_reduce_cols(const Z64* _
 // many splits, so that a few outputs of many splits are still read by many threads): each sums every P-th
 // split and the parts are added in order. 16 columns of M = 128 in 132 splits: 18 -> 6 us.
 template <int P>
-__global__ __launch_bounds__(256) void k_sum_parts(const Z64* __restrict__ cpart, int nsplit, int ncols, int M_pad,
-                                                   int M, double scale, Z64* __restrict__ C) {
-  constexpr int O = 256 / P;  // outputs per workgroup
+__global__ __launch_bounds__(256) void k_sum_parts(ZRows s0, ZRows s1, int nb0, int nsplit, int ncols) {
+  constexpr int O = 256 / P;  // outputs per workgroup; workgroups from nb0 on belong to the second operand
   __shared__ Z64 part[P > 1 ? P : 1][P > 1 ? O : 1];
+  const bool second = (int)blockIdx.x >= nb0;
+  const Z64* __restrict__ cpart = second ? s1.part : s0.part;
+  Z64* __restrict__ C = second ? s1.C : s0.C;
+  const int M_pad = second ? s1.M_pad : s0.M_pad, M = ((second ? s1.M : s0.M) + 7) / 8 * 8;
+  const double scale = second ? s1.scale : s0.scale;
   const int o = threadIdx.x % O, q = threadIdx.x / O;
-  const int i = blockIdx.x * O + o;
+  const int i = ((int)blockIdx.x - (second ? nb0 : 0)) * O + o;
   const bool live = i < ncols * M;
   const size_t at = live ? (size_t)(i / M) * M_pad + i % M : 0, total = (size_t)ncols * M_pad;
   double re = 0.0, im = 0.0;
@@ -220,13 +233,23 @@ __global__ __launch_bounds__(256) void k_sum_parts(const Z64* __restrict__ cpart
   if (live) C[at] = zmk(scale * re, scale * im);
 }
 
-// Y[yidx[n]][k] += sum_m A[m][k] C[n][m]. Bounded to 4 waves per SIMD: the compiler then keeps the
-// accumulators in VGPRs (114 in all) instead of 104 VGPRs + 64 AGPRs at 3 waves; 59 -> 70 TFLOP/s at
-// M = 1,024, 4,096 columns, K = 91,072.
-__global__ __launch_bounds__(kGemmThreads, 4) void k_zgemm_expand(const Z64* __restrict__ A, int M_pad, int K,
-                                                               const Z64* __restrict__ C, Z64* __restrict__ Y,
+// Y[yidx[n]][k] += sum_m A[m][k] C[n][m], over the rows of one operand or of two. PUPD: Y is left as it is and the
+// sum goes into the search direction, P[s] = (Y[s] + A C) + beta[s] P[s] (s = yidx[n]). Bounded to 4 waves per
+// SIMD: the compiler then keeps the accumulators in VGPRs instead of 104 VGPRs + 64 AGPRs at 3 waves; 59 -> 70
+// TFLOP/s at M = 1,024, 4,096 columns, K = 91,072.
+__device__ __forceinline__ void put_row(Z64* y, Z64* p, double b, double re, double im) {
+  const Z64 old = *y, t = zmk(old.re + re, old.im + im);
+  if (p) {
+    const Z64 q = *p;
+    *p = zmk(t.re + b * q.re, t.im + b * q.im);
+  } else {
+    *y = t;
+  }
+}
+template <bool PUPD>
+__global__ __launch_bounds__(kGemmThreads, 4) void k_zgemm_expand(ZRows s0, ZRows s1, int K, Z64* __restrict__ Y,
                                                                int ldy, const int* __restrict__ yidx, int ncols,
-                                                               int M) {
+                                                               Z64* __restrict__ P, const double* __restrict__ beta) {
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int l16 = lane & 15, g = lane >> 4;
   const int k0 = blockIdx.x * 64 + (wave & 1) * 32;
@@ -249,59 +272,65 @@ __global__ __launch_bounds__(kGemmThreads, 4) void k_zgemm_expand(const Z64* __r
     }
   // next step's fragments loaded before this step's products; columns past ncols read column 0
   Z64 na0[2], na1[2], nc0[2], nc1[2];
-  auto load = [&](int m) {
-    const int mm = m + 2 * g;
+  for (int seg = 0; seg < 2; ++seg) {
+    const Z64* __restrict__ A = seg ? s1.A : s0.A;
+    const Z64* __restrict__ C = seg ? s1.C : s0.C;
+    const int M_pad = seg ? s1.M_pad : s0.M_pad, M = ((seg ? s1.M : s0.M) + 7) / 8 * 8;
+    if (M == 0) continue;
+    auto load = [&](int m) {
+      const int mm = m + 2 * g;
 #pragma unroll
-    for (int bi = 0; bi < 2; ++bi) {
-      const int kk = k0 + 16 * bi + l16;
-      na0[bi] = A[(size_t)mm * K + kk];
-      na1[bi] = A[(size_t)(mm + 1) * K + kk];
-    }
-#pragma unroll
-    for (int bj = 0; bj < 2; ++bj) {
-      const size_t o = (size_t)(nv[bj] ? nn[bj] : 0) * M_pad + mm;
-      nc0[bj] = C[o];
-      nc1[bj] = C[o + 1];
-    }
-  };
-  load(0);
-  for (int m = 0; m < M; m += 8) {
-    Z64 a0[2], a1[2], c0[2], c1[2];
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      a0[u] = na0[u];
-      a1[u] = na1[u];
-      c0[u] = nc0[u];
-      c1[u] = nc1[u];
-    }
-    load(min(m + 8, M - 8));  // the last step reloads itself, unused
-#pragma unroll
-    for (int bi = 0; bi < 2; ++bi)
+      for (int bi = 0; bi < 2; ++bi) {
+        const int kk = k0 + 16 * bi + l16;
+        na0[bi] = A[(size_t)mm * K + kk];
+        na1[bi] = A[(size_t)(mm + 1) * K + kk];
+      }
 #pragma unroll
       for (int bj = 0; bj < 2; ++bj) {
-        // Re a c = a.re c.re - a.im c.im ; Im a c = a.re c.im + a.im c.re
-        dre[bi][bj] = mfma(a0[bi].re, c0[bj].re, dre[bi][bj]);
-        dre[bi][bj] = mfma(a0[bi].im, -c0[bj].im, dre[bi][bj]);
-        dre[bi][bj] = mfma(a1[bi].re, c1[bj].re, dre[bi][bj]);
-        dre[bi][bj] = mfma(a1[bi].im, -c1[bj].im, dre[bi][bj]);
-        dim_[bi][bj] = mfma(a0[bi].re, c0[bj].im, dim_[bi][bj]);
-        dim_[bi][bj] = mfma(a0[bi].im, c0[bj].re, dim_[bi][bj]);
-        dim_[bi][bj] = mfma(a1[bi].re, c1[bj].im, dim_[bi][bj]);
-        dim_[bi][bj] = mfma(a1[bi].im, c1[bj].re, dim_[bi][bj]);
+        const size_t o = (size_t)(nv[bj] ? nn[bj] : 0) * M_pad + mm;
+        nc0[bj] = C[o];
+        nc1[bj] = C[o + 1];
       }
+    };
+    load(0);
+    for (int m = 0; m < M; m += 8) {
+      Z64 a0[2], a1[2], c0[2], c1[2];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        a0[u] = na0[u];
+        a1[u] = na1[u];
+        c0[u] = nc0[u];
+        c1[u] = nc1[u];
+      }
+      load(min(m + 8, M - 8));  // the last step reloads itself, unused
+#pragma unroll
+      for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+        for (int bj = 0; bj < 2; ++bj) {
+          // Re a c = a.re c.re - a.im c.im ; Im a c = a.re c.im + a.im c.re
+          dre[bi][bj] = mfma(a0[bi].re, c0[bj].re, dre[bi][bj]);
+          dre[bi][bj] = mfma(a0[bi].im, -c0[bj].im, dre[bi][bj]);
+          dre[bi][bj] = mfma(a1[bi].re, c1[bj].re, dre[bi][bj]);
+          dre[bi][bj] = mfma(a1[bi].im, -c1[bj].im, dre[bi][bj]);
+          dim_[bi][bj] = mfma(a0[bi].re, c0[bj].im, dim_[bi][bj]);
+          dim_[bi][bj] = mfma(a0[bi].im, c0[bj].re, dim_[bi][bj]);
+          dim_[bi][bj] = mfma(a1[bi].re, c1[bj].im, dim_[bi][bj]);
+          dim_[bi][bj] = mfma(a1[bi].im, c1[bj].re, dim_[bi][bj]);
+        }
+    }
   }
 #pragma unroll
   for (int bj = 0; bj < 2; ++bj) {
     if (!nv[bj]) continue;
     const int row = yidx ? yidx[nn[bj]] : nn[bj];
     Z64* y = Y + (size_t)row * ldy;
+    const double bt = PUPD ? beta[row] : 0.0;
 #pragma unroll
     for (int bi = 0; bi < 2; ++bi) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int k = k0 + 16 * bi + g + 4 * r;
-        const Z64 old = y[k];
-        y[k] = zmk(old.re + dre[bi][bj][r], old.im + dim_[bi][bj][r]);
+        put_row(y + k, PUPD ? P + (size_t)row * ldy + k : nullptr, bt, dre[bi][bj][r], dim_[bi][bj][r]);
       }
     }
   }
@@ -309,71 +338,76 @@ __global__ __launch_bounds__(kGemmThreads, 4) void k_zgemm_expand(const Z64* __r
 
 // The expand for few columns: a wave takes 16 k and 16 BJ columns (see k_zgemm_reduce_cols), the loads of a
 // step two steps ahead. M = 16, 7 columns, K = 576: 12 -> 5 us; M = 128, 16 columns, K = 16,896: 43 -> 14 us.
-template <int BJ>
-__global__ __launch_bounds__(kGemmThreads) void k_zgemm_expand_cols(const Z64* __restrict__ A, int M_pad, int K,
-                                                                    const Z64* __restrict__ C, Z64* __restrict__ Y,
+template <int BJ, bool PUPD>
+__global__ __launch_bounds__(kGemmThreads) void k_zgemm_expand_cols(ZRows s0, ZRows s1, int K, Z64* __restrict__ Y,
                                                                     int ldy, const int* __restrict__ yidx, int ncols,
-                                                                    int M) {
+                                                                    Z64* __restrict__ P,
+                                                                    const double* __restrict__ beta) {
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int l16 = lane & 15, g = lane >> 4;
   const int k0 = blockIdx.x * 64 + wave * 16;
-  const Z64* ar = A + (size_t)(2 * g) * K + k0 + l16;
-  const Z64* cr[BJ];
-#pragma unroll
-  for (int bj = 0; bj < BJ; ++bj) cr[bj] = C + (size_t)min(16 * bj + l16, ncols - 1) * M_pad + 2 * g;
   v4d dre[BJ], dim_[BJ];
 #pragma unroll
   for (int bj = 0; bj < BJ; ++bj) dre[bj] = dim_[bj] = v4d{0.0, 0.0, 0.0, 0.0};
   Z64 a[2][2], c[2][BJ][2];
-  auto load = [&](int b, int m) {
-    const int mm = min(m, M - 8);  // steps past the end read the last one, unused
-    a[b][0] = ar[(size_t)mm * K];
-    a[b][1] = ar[(size_t)(mm + 1) * K];
+  for (int seg = 0; seg < 2; ++seg) {
+    const int M_pad = seg ? s1.M_pad : s0.M_pad, M = ((seg ? s1.M : s0.M) + 7) / 8 * 8;
+    if (M == 0) continue;
+    const Z64* __restrict__ ar = (seg ? s1.A : s0.A) + (size_t)(2 * g) * K + k0 + l16;
+    const Z64* __restrict__ C = seg ? s1.C : s0.C;
+    const Z64* cr[BJ];
 #pragma unroll
-    for (int bj = 0; bj < BJ; ++bj) {
-      c[b][bj][0] = cr[bj][mm];
-      c[b][bj][1] = cr[bj][mm + 1];
-    }
-  };
-  auto step = [&](int b, int m) {
-    const Z64 a0 = a[b][0], a1 = a[b][1];
-    Z64 c0[BJ], c1[BJ];
+    for (int bj = 0; bj < BJ; ++bj) cr[bj] = C + (size_t)min(16 * bj + l16, ncols - 1) * M_pad + 2 * g;
+    auto load = [&](int b, int m) {
+      const int mm = min(m, M - 8);  // steps past the end read the last one, unused
+      a[b][0] = ar[(size_t)mm * K];
+      a[b][1] = ar[(size_t)(mm + 1) * K];
 #pragma unroll
-    for (int bj = 0; bj < BJ; ++bj) {
-      c0[bj] = c[b][bj][0];
-      c1[bj] = c[b][bj][1];
-    }
-    load(b, m + 16);
+      for (int bj = 0; bj < BJ; ++bj) {
+        c[b][bj][0] = cr[bj][mm];
+        c[b][bj][1] = cr[bj][mm + 1];
+      }
+    };
+    auto step = [&](int b, int m) {
+      const Z64 a0 = a[b][0], a1 = a[b][1];
+      Z64 c0[BJ], c1[BJ];
 #pragma unroll
-    for (int bj = 0; bj < BJ; ++bj) {
-      dre[bj] = mfma(a0.re, c0[bj].re, dre[bj]);
-      dim_[bj] = mfma(a0.re, c0[bj].im, dim_[bj]);
-      dre[bj] = mfma(a0.im, -c0[bj].im, dre[bj]);
-      dim_[bj] = mfma(a0.im, c0[bj].re, dim_[bj]);
-      dre[bj] = mfma(a1.re, c1[bj].re, dre[bj]);
-      dim_[bj] = mfma(a1.re, c1[bj].im, dim_[bj]);
-      dre[bj] = mfma(a1.im, -c1[bj].im, dre[bj]);
-      dim_[bj] = mfma(a1.im, c1[bj].re, dim_[bj]);
+      for (int bj = 0; bj < BJ; ++bj) {
+        c0[bj] = c[b][bj][0];
+        c1[bj] = c[b][bj][1];
+      }
+      load(b, m + 16);
+#pragma unroll
+      for (int bj = 0; bj < BJ; ++bj) {
+        dre[bj] = mfma(a0.re, c0[bj].re, dre[bj]);
+        dim_[bj] = mfma(a0.re, c0[bj].im, dim_[bj]);
+        dre[bj] = mfma(a0.im, -c0[bj].im, dre[bj]);
+        dim_[bj] = mfma(a0.im, c0[bj].re, dim_[bj]);
+        dre[bj] = mfma(a1.re, c1[bj].re, dre[bj]);
+        dim_[bj] = mfma(a1.re, c1[bj].im, dim_[bj]);
+        dre[bj] = mfma(a1.im, -c1[bj].im, dre[bj]);
+        dim_[bj] = mfma(a1.im, c1[bj].re, dim_[bj]);
+      }
+    };
+    load(0, 0);
+    load(1, 8);
+    int m = 0;
+    for (; m + 16 <= M; m += 16) {
+      step(0, m);
+      step(1, m + 8);
     }
-  };
-  load(0, 0);
-  load(1, 8);
-  int m = 0;
-  for (; m + 16 <= M; m += 16) {
-    step(0, m);
-    step(1, m + 8);
+    if (m < M) step(0, m);
   }
-  if (m < M) step(0, m);
 #pragma unroll
   for (int bj = 0; bj < BJ; ++bj) {
     const int n = 16 * bj + l16;
     if (n >= ncols) continue;
-    Z64* y = Y + (size_t)(yidx ? yidx[n] : n) * ldy + k0 + g;
+    const int row = yidx ? yidx[n] : n;
+    const size_t o = (size_t)row * ldy + k0 + g;
+    const double bt = PUPD ? beta[row] : 0.0;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const Z64 old = y[4 * r];
-      y[4 * r] = zmk(old.re + dre[bj][r], old.im + dim_[bj][r]);
-    }
+    for (int r = 0; r < 4; ++r)
+      put_row(Y + o + 4 * r, PUPD ? P + o + 4 * r : nullptr, bt, dre[bj][r], dim_[bj][r]);
   }
 }
 
@@ -424,51 +458,72 @@ int choose_nsplit(int M_pad, int ncols, int K, int target) {
   return ns;
 }
 
-void launch_zgemm_reduce(const Z64* A, int M_pad, const Z64* X, int ldx, const int* xidx, int ncols, int K,
-                         Z64* cpart, int nsplit, hipStream_t st, int M) {
+void launch_zgemm_reduce2(const ZRows& s0, const ZRows& s1, int ldx, const int* xidx, int ncols, int K, int nsplit,
+                          hipStream_t st) {
   if (ncols <= 0) return;
   int kchunk = (K + nsplit - 1) / nsplit;
   kchunk = (kchunk + 15) / 16 * 16;
+  const int mb0 = (s0.M + 63) / 64, mb = mb0 + (s1.M + 63) / 64;
   if (ncols <= kFewCols) {
-    const dim3 grid((M + 63) / 64, 1, nsplit);
+    const dim3 grid(mb, 1, nsplit);
     if (ncols <= 16)
-      k_zgemm_reduce_cols<1><<<grid, kGemmThreads, 0, st>>>(A, M_pad, X, ldx, xidx, ncols, K, kchunk, cpart, M);
+      k_zgemm_reduce_cols<1><<<grid, kGemmThreads, 0, st>>>(s0, s1, mb0, ldx, xidx, ncols, K, kchunk);
     else if (ncols <= 32)
-      k_zgemm_reduce_cols<2><<<grid, kGemmThreads, 0, st>>>(A, M_pad, X, ldx, xidx, ncols, K, kchunk, cpart, M);
+      k_zgemm_reduce_cols<2><<<grid, kGemmThreads, 0, st>>>(s0, s1, mb0, ldx, xidx, ncols, K, kchunk);
     else
-      k_zgemm_reduce_cols<3><<<grid, kGemmThreads, 0, st>>>(A, M_pad, X, ldx, xidx, ncols, K, kchunk, cpart, M);
+      k_zgemm_reduce_cols<3><<<grid, kGemmThreads, 0, st>>>(s0, s1, mb0, ldx, xidx, ncols, K, kchunk);
     return;
   }
-  dim3 grid((M + 63) / 64, (ncols + 63) / 64, nsplit);
-  k_zgemm_reduce<<<grid, kGemmThreads, 0, st>>>(A, M_pad, X, ldx, xidx, ncols, K, kchunk, cpart, M);
+  k_zgemm_reduce<<<dim3(mb, (ncols + 63) / 64, nsplit), kGemmThreads, 0, st>>>(s0, s1, mb0, ldx, xidx, ncols, K,
+                                                                              kchunk);
 }
 
+void launch_sum_parts2(const ZRows& s0, const ZRows& s1, int nsplit, int ncols, hipStream_t st) {
+  const int t0 = ncols * ((s0.M + 7) / 8 * 8), t1 = ncols * ((s1.M + 7) / 8 * 8);
+  if (t0 + t1 <= 0) return;
+  const int O = nsplit >= 8 ? 32 : 256, nb0 = (t0 + O - 1) / O, nb = nb0 + (t1 + O - 1) / O;
+  if (nsplit >= 8)
+    k_sum_parts<8><<<nb, 256, 0, st>>>(s0, s1, nb0, nsplit, ncols);
+  else
+    k_sum_parts<1><<<nb, 256, 0, st>>>(s0, s1, nb0, nsplit, ncols);
+}
+
+namespace {
+template <bool PUPD>
+void expand2(const ZRows& s0, const ZRows& s1, Z64* Y, int ldy, const int* yidx, int ncols, int K, hipStream_t st,
+             Z64* P, const double* beta) {
+  if (ncols <= 16)
+    k_zgemm_expand_cols<1, PUPD><<<K / 64, kGemmThreads, 0, st>>>(s0, s1, K, Y, ldy, yidx, ncols, P, beta);
+  else if (ncols <= 32)
+    k_zgemm_expand_cols<2, PUPD><<<K / 64, kGemmThreads, 0, st>>>(s0, s1, K, Y, ldy, yidx, ncols, P, beta);
+  else if (ncols <= kFewCols)
+    k_zgemm_expand_cols<3, PUPD><<<K / 64, kGemmThreads, 0, st>>>(s0, s1, K, Y, ldy, yidx, ncols, P, beta);
+  else
+    k_zgemm_expand<PUPD><<<dim3(K / 64, (ncols + 63) / 64), kGemmThreads, 0, st>>>(s0, s1, K, Y, ldy, yidx, ncols, P,
+                                                                                  beta);
+}
+}  // namespace
+void launch_zgemm_expand2(const ZRows& s0, const ZRows& s1, Z64* Y, int ldy, const int* yidx, int ncols, int K,
+                          hipStream_t st, Z64* P, const double* beta) {
+  if (ncols <= 0) return;
+  if (P)
+    expand2<true>(s0, s1, Y, ldy, yidx, ncols, K, st, P, beta);
+  else
+    expand2<false>(s0, s1, Y, ldy, yidx, ncols, K, st, P, beta);
+}
+
+void launch_zgemm_reduce(const Z64* A, int M_pad, const Z64* X, int ldx, const int* xidx, int ncols, int K,
+                         Z64* cpart, int nsplit, hipStream_t st, int M) {
+  launch_zgemm_reduce2(ZRows{A, X, cpart, nullptr, M_pad, M, 0.0}, ZRows{}, ldx, xidx, ncols, K, nsplit, st);
+}
 void launch_sum_parts(const Z64* cpart, int nsplit, int ncols, int M_pad, double scale, Z64* C, hipStream_t st,
                       int M) {
-  M = (M + 7) / 8 * 8;  // the expand reads whole steps of 8
-  const int total = ncols * M;
-  if (total <= 0) return;
-  if (nsplit >= 8)
-    k_sum_parts<8><<<(total + 31) / 32, 256, 0, st>>>(cpart, nsplit, ncols, M_pad, M, scale, C);
-  else
-    k_sum_parts<1><<<(total + 255) / 256, 256, 0, st>>>(cpart, nsplit, ncols, M_pad, M, scale, C);
+  launch_sum_parts2(ZRows{nullptr, nullptr, const_cast<Z64*>(cpart), C, M_pad, M, scale}, ZRows{}, nsplit, ncols, st);
 }
-
 void launch_zgemm_expand(const Z64* A, int M_pad, const Z64* C, Z64* Y, int ldy, const int* yidx, int ncols, int K,
                          hipStream_t st, int M) {
-  if (ncols <= 0) return;
-  M = (M + 7) / 8 * 8;
-  if (ncols <= kFewCols) {
-    if (ncols <= 16)
-      k_zgemm_expand_cols<1><<<K / 64, kGemmThreads, 0, st>>>(A, M_pad, K, C, Y, ldy, yidx, ncols, M);
-    else if (ncols <= 32)
-      k_zgemm_expand_cols<2><<<K / 64, kGemmThreads, 0, st>>>(A, M_pad, K, C, Y, ldy, yidx, ncols, M);
-    else
-      k_zgemm_expand_cols<3><<<K / 64, kGemmThreads, 0, st>>>(A, M_pad, K, C, Y, ldy, yidx, ncols, M);
-    return;
-  }
-  dim3 grid(K / 64, (ncols + 63) / 64);
-  k_zgemm_expand<<<grid, kGemmThreads, 0, st>>>(A, M_pad, K, C, Y, ldy, yidx, ncols, M);
+  launch_zgemm_expand2(ZRows{A, nullptr, nullptr, const_cast<Z64*>(C), M_pad, M, 0.0}, ZRows{}, Y, ldy, yidx, ncols,
+                       K, st, nullptr, nullptr);
 }
 
 }  // namespace stern

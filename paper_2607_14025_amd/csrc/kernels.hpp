@@ -95,6 +95,19 @@ void launch_sum_parts(const Z64* cpart, int nsplit, int ncols, int M_pad, double
 // Y[yidx[n]][k] += sum_m A[m][k] C[n][m], k < K (multiple of 64), m < M rounded up to 8.
 void launch_zgemm_expand(const Z64* A, int M_pad, const Z64* C, Z64* Y, int ldy, const int* yidx, int ncols, int K,
                          hipStream_t st, int M);
+// One operand of a reduce, sum and expand over two (M = 0: none): rows A, the rows X its reduce takes, partials,
+// coefficients C and their scale. Y may take the sum, or P = (Y + A C) + beta P per row (P not null).
+struct ZRows {
+  const Z64 *A = nullptr, *X = nullptr;
+  Z64 *part = nullptr, *C = nullptr;
+  int M_pad = 0, M = 0;
+  double scale = 0.0;
+};
+void launch_zgemm_reduce2(const ZRows& s0, const ZRows& s1, int ldx, const int* xidx, int ncols, int K, int nsplit,
+                          hipStream_t st);
+void launch_sum_parts2(const ZRows& s0, const ZRows& s1, int nsplit, int ncols, hipStream_t st);
+void launch_zgemm_expand2(const ZRows& s0, const ZRows& s1, Z64* Y, int ldy, const int* yidx, int ncols, int K,
+                          hipStream_t st, Z64* P, const double* beta);
 // split-K factor for a reduce of ncols columns aiming at `target` workgroups (<= 0: default), and the factor
 // of the 64-column tile, by which the allocation-free entry point states its limit
 int choose_nsplit(int M_pad, int ncols, int K, int target);
@@ -112,7 +125,10 @@ struct CgState {
   const double* g2h;           // [npw_pad]
   const float* kprec;          // [nbatch][npw_pad] learned diagonal preconditioner, or null for Teter
   int npw_pad;
+  double* beta;                // [nbatch] (r, z) new / old, set with rz by the alpha step
+  double* part;                // [nbatch][cg_chunks(npw_pad)][3] partial sums of the alpha step of long rows
 };
+int cg_chunks(int npw_pad);  // workgroups a long row's alpha step is split into, 0: it runs in one
 void launch_cg_init(const CgState& s, const int* act, int n, bool keep, hipStream_t st);
 // r = b - A x + i u x for a guess x (A x in q, or q32 when not null); rejects guesses with ||r|| >= ||b||;
 // with tol2 >= 0, marks a guess with ||r||^2 <= tol2 ||b||^2 converged (flag 2)
@@ -121,7 +137,6 @@ void launch_guess_resid(const CgState& s, const int* act, int n, const Z32* q32,
 void launch_to32(const Z64* x, Z32* y, size_t n, hipStream_t st);
 void launch_cg_init2(const CgState& s, const int* act, int n, hipStream_t st);
 void launch_cg_alpha(const CgState& s, const int* act, int n, double tol2, hipStream_t st);
-void launch_cg_beta(const CgState& s, const int* act, int n, hipStream_t st);
 void launch_copy_rows(const Z64* src, Z64* dst, int ld, const int* act, int n, hipStream_t st);
 void launch_true_resid(const CgState& s, const int* act, int n, double tol, hipStream_t st);
 void launch_cg_restart(const CgState& s, const int* act, int n, hipStream_t st);

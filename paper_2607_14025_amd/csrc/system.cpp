@@ -179,6 +179,8 @@ struct stern_system {
   DBuf wx, wr, wp, wq, wz, wb, pen, cpart, cpart2, cmat, sv_eps, sv_invT, sv_band, sv_pert, sv_bb, sv_rz, sv_rr, sv_flag,
       sv_iters, sv_tres, list_act, list_f, pert_out, dv_dev, dn_dev, tmp_in, tmp_out;
   DBuf m_d, m_r, m_p, m_q, m_z, m_rz, m_rr0, m_beta, m_flag, m_part;  // mixed inner solve
+  DBuf pkb;                   // [natoms_pad][npw_pad] P_c beta_a (FP64)
+  DBuf sv_beta, sv_part;      // FP64 alpha step: beta, and the partial sums of long rows
   DBuf sum_part;              // segments of the band sums (density response, transition densities)
   DBuf m_cnt;                 // device count of the inner solve's active list (list_f)
   DBuf negk;                  // [npw_pad] index of -G of each coefficient (column order)
@@ -297,7 +299,7 @@ struct stern_system {
                    &sv_rr,     &sv_flag,  &sv_iters, &sv_tres, &list_act, &list_f,  &pert_out, &dv_dev,   &dn_dev,
                    &tmp_in,    &tmp_out,  &psi_hi,  &psi_lo,   &psiT_hi, &psiT_lo,  &kb_hi,    &kb_lo,
                    &kbT_hi,    &kbT_lo,   &m_d,     &m_r,      &m_p,     &m_q,      &m_z,      &m_rz,  &m_beta,
-                   &m_rr0,     &m_flag, &m_part, &sum_part,   &c_col_start, &c_col_len, &c_col_xmin, &c_col_pos, &c_zl, &c_ycol,
+                   &m_rr0,     &m_flag, &m_part, &sum_part, &pkb, &sv_beta, &sv_part,   &c_col_start, &c_col_len, &c_col_xmin, &c_col_pos, &c_zl, &c_ycol,
                    &c_tw64,    &psi_c,    &c_pen,   &c_field,  &net_a0,  &net_a1,   &net_a2,   &net_out,
                    &g_rej,     &net_feat, &net_coef, &kprec,  &v_t,     &v_t32,    &band_eps, &band_invT,
                    &band_feat, &projT_hi, &projT_lo, &cpart2, &m_cnt, &negk, &sv_rzi, &xkeep,
@@ -388,8 +390,7 @@ double plane_flops(const stern_system* S) {
   return N * ((2.0 * nza + 2.0 * N) * 5.0 * N * std::log2(N) + 2.0 * N * N);
 }
 
-// out = (H - eps_s) in on rows list (without projection); eps per row index
-int apply_h_rows(stern_system* S, const Z64* in, Z64* out, const int* list, int n, const double* eps_rows) {
+int apply_local_rows(stern_system* S, const Z64* in, Z64* out, const int* list, int n, const double* eps_rows) {
   if (n <= 0) return 0;
   const FftGeom g = S->geom();
   const int K = S->hb.npw_pad;
@@ -406,6 +407,15 @@ int apply_h_rows(stern_system* S, const Z64* in, Z64* out, const int* list, int 
                 }));
   CHECKED(timed(S, STERN_K_XFWD, n * (pen + 2.0 * npw * zb), 0.0,
                 [&] { launch_xfwd(g, S->pen.as<Z64>(), list, n, out, 1, in, eps_rows, 0.0, S->stream); }));
+  return 0;
+}
+
+// out = (H - eps_s) in on rows list (without projection); eps per row index
+int apply_h_rows(stern_system* S, const Z64* in, Z64* out, const int* list, int n, const double* eps_rows) {
+  if (n <= 0) return 0;
+  CHECKED(apply_local_rows(S, in, out, list, n, eps_rows));
+  const int K = S->hb.npw_pad;
+  const double zb = sizeof(Z64), npw = S->hb.npw;
   if (S->n_atoms > 0) {
     const double na = S->n_atoms;
     const int ns = choose_nsplit(S->natoms_pad, n, K, S->gemm64_wg);
@@ -422,6 +432,48 @@ int apply_h_rows(stern_system* S, const Z64* in, Z64* out, const int* list, int 
                           S->n_atoms);
     }));
   }
+  return 0;
+}
+
+// P <- P_c Z + beta P on rows list: the projection and the CG direction update in one expand; Z is left as it is
+int apply_pc_update(stern_system* S, Z64* Z, Z64* P, const double* beta, const int* list, int n) {
+  if (n <= 0) return 0;
+  const int K = S->hb.npw_pad;
+  const double npw = S->hb.npw, m = S->n_occ, zb = sizeof(Z64);
+  const int ns = choose_nsplit(S->nocc_pad, n, K, S->gemm64_wg);
+  const ZRows r{S->psi.as<Z64>(), Z, S->cpart.as<Z64>(), S->cmat.as<Z64>(), S->nocc_pad, S->n_occ, -1.0};
+  CHECKED(timed(S, STERN_K_PC_REDUCE, zb * npw * (n + m), 8.0 * m * npw * n,
+                [&] { launch_zgemm_reduce2(r, ZRows{}, K, list, n, K, ns, S->stream); }));
+  CHECKED(timed(S, STERN_K_SUM_PARTS, zb * m * n * (ns + 1), 0.0,
+                [&] { launch_sum_parts2(r, ZRows{}, ns, n, S->stream); }));
+  CHECKED(timed(S, STERN_K_PC_EXPAND, zb * npw * (3.0 * n + m), 8.0 * m * npw * n,
+                [&] { launch_zgemm_expand2(r, ZRows{}, Z, K, list, n, K, S->stream, P, beta); }));
+  return 0;
+}
+
+// the FFT stage of the H apply: out = (|G|^2/2 + V_loc - eps_s) in on rows list
+int apply_local_rows(stern_system* S, const Z64* in, Z64* out, const int* list, int n, const double* eps_rows);
+
+// out = P_c (H - eps_s) in on rows list: out_loc + sum_a P_c beta_a D <beta_a|in> - sum_b psi_b <psi_b|out_loc>, with
+// P_c beta_a formed once per occupied set, so the two reduces are independent of each other and one reduce,
+// one sum and one expand over both operands do what the H apply's projectors and P_c took two of each for
+int apply_hproj_rows(stern_system* S, const Z64* in, Z64* out, const int* list, int n, const double* eps_rows) {
+  if (n <= 0) return 0;
+  CHECKED(apply_local_rows(S, in, out, list, n, eps_rows));
+  if (S->n_atoms == 0) return apply_pc_rows(S, out, list, n);
+  const int K = S->hb.npw_pad, Ma = S->natoms_pad, Mb = S->nocc_pad;
+  const double npw = S->hb.npw, na = S->n_atoms, m = S->n_occ, zb = sizeof(Z64);
+  const int ns = choose_nsplit(Ma + Mb, n, K, S->gemm64_wg);
+  Z64 *cp = S->cpart.as<Z64>(), *cm = S->cmat.as<Z64>();
+  ZRows a{S->kb.as<Z64>(), in, cp, cm, Ma, S->n_atoms, S->cell.D};
+  const ZRows b{S->psi.as<Z64>(), out, cp + (size_t)ns * n * Ma, cm + (size_t)n * Ma, Mb, S->n_occ, -1.0};
+  CHECKED(timed(S, STERN_K_PC_REDUCE, zb * npw * (2.0 * n + na + m), 8.0 * (na + m) * npw * n,
+                [&] { launch_zgemm_reduce2(a, b, K, list, n, K, ns, S->stream); }));
+  CHECKED(timed(S, STERN_K_SUM_PARTS, zb * (na + m) * n * (ns + 1), 0.0,
+                [&] { launch_sum_parts2(a, b, ns, n, S->stream); }));
+  a.A = S->pkb.as<Z64>();
+  CHECKED(timed(S, STERN_K_PC_EXPAND, zb * npw * (2.0 * n + na + m), 8.0 * (na + m) * npw * n,
+                [&] { launch_zgemm_expand2(a, b, out, K, list, n, K, S->stream, nullptr, nullptr); }));
   return 0;
 }
 
@@ -578,12 +630,13 @@ int ensure_workspace(stern_system* S, int ns) {
   const size_t vec = (size_t)ns * K * sizeof(Z64);
   for (DBuf* d : {&S->wx, &S->wr, &S->wp, &S->wq, &S->wz, &S->wb}) CHECKED(d->ensure(vec));
   CHECKED(S->pen.ensure((size_t)ns * S->hb.N * S->hb.ncol_pad * sizeof(Z64)));
-  const int mp = std::max(S->nocc_pad, S->natoms_pad);
-  CHECKED(S->cpart.ensure(std::max(cpart_capacity(S, std::max(S->nocc_pad, 64), ns, (int)K),
-                                   cpart_capacity(S, S->natoms_pad, ns, (int)K))));
+  const int mo = std::max(S->nocc_pad, 64), mp = mo + S->natoms_pad;  // one operand, or both in one buffer
+  CHECKED(S->cpart.ensure(std::max({cpart_capacity(S, mo, ns, (int)K), cpart_capacity(S, S->natoms_pad, ns, (int)K),
+                                    cpart_capacity(S, mp, ns, (int)K)})));
   CHECKED(S->cmat.ensure((size_t)ns * mp * sizeof(Z64)));
+  if (const int nc = cg_chunks((int)K)) CHECKED(S->sv_part.ensure((size_t)ns * nc * 3 * sizeof(double)));
   CHECKED(S->cpart2.ensure(cpart_capacity(S, std::max(S->nocc_pad, 64), ns, (int)K)));
-  for (DBuf* d : {&S->sv_eps, &S->sv_invT, &S->sv_bb, &S->sv_rz, &S->sv_rr, &S->sv_tres, &S->sv_rzi})
+  for (DBuf* d : {&S->sv_eps, &S->sv_invT, &S->sv_bb, &S->sv_rz, &S->sv_rr, &S->sv_tres, &S->sv_rzi, &S->sv_beta})
     CHECKED(d->ensure((size_t)ns * sizeof(double)));
   for (DBuf* d : {&S->sv_band, &S->sv_pert, &S->sv_flag, &S->sv_iters, &S->list_act, &S->list_f})
     CHECKED(d->ensure((size_t)ns * sizeof(int)));
@@ -655,6 +708,8 @@ CgState cg_state(stern_system* S) {
   c.invT = S->sv_invT.as<double>();
   c.g2h = S->g2h.as<double>();
   c.kprec = nullptr;
+  c.beta = S->sv_beta.as<double>();
+  c.part = S->sv_part.as<double>();
   c.npw_pad = S->hb.npw_pad;
   return c;
 }
@@ -663,8 +718,7 @@ CgState cg_state(stern_system* S) {
 int true_residual(stern_system* S, const CgState& cs, const int* list, int n, double tol) {
   launch_copy_rows(cs.x, cs.z, S->hb.npw_pad, list, n, S->stream);
   CHECKED(apply_pc_rows(S, cs.z, list, n));
-  CHECKED(apply_h_rows(S, cs.z, cs.q, list, n, cs.eps));
-  CHECKED(apply_pc_rows(S, cs.q, list, n));
+  CHECKED(apply_hproj_rows(S, cs.z, cs.q, list, n, cs.eps));
   launch_true_resid(cs, list, n, tol, S->stream);
   return 0;
 }
@@ -801,8 +855,7 @@ int learned_guess(stern_system* S, const stern_model* M, CgState& cs, int ns, in
     CHECKED(apply_pc32_rows(S, q32, nullptr, ns));
     launch_guess_resid(cs, nullptr, ns, q32, S->g_rej.as<int>(), st);
   } else {
-    CHECKED(apply_h_rows(S, cs.x, cs.q, nullptr, ns, cs.eps));
-    CHECKED(apply_pc_rows(S, cs.q, nullptr, ns));
+    CHECKED(apply_hproj_rows(S, cs.x, cs.q, nullptr, ns, cs.eps));
     launch_guess_resid(cs, nullptr, ns, nullptr, S->g_rej.as<int>(), st);
   }
   CHECKED(launch_check());
@@ -823,8 +876,7 @@ int warm_start(stern_system* S, const CgState& cs, size_t row0, int ns, double u
   HIPOK(hipMemcpyAsync(cs.x, S->xkeep.as<Z64>() + row0 * K, (size_t)ns * K * sizeof(Z64), hipMemcpyDeviceToDevice,
                        st));
   CHECKED(apply_pc_rows(S, cs.x, nullptr, ns));
-  CHECKED(apply_h_rows(S, cs.x, cs.q, nullptr, ns, cs.eps));
-  CHECKED(apply_pc_rows(S, cs.q, nullptr, ns));
+  CHECKED(apply_hproj_rows(S, cs.x, cs.q, nullptr, ns, cs.eps));
   launch_guess_resid(cs, nullptr, ns, nullptr, S->g_rej.as<int>(), st, u, tol * tol);
   CHECKED(launch_check());
   std::vector<int> rej(ns);
@@ -935,11 +987,9 @@ int run_pcg64(stern_system* S, const CgState& cs, const std::vector<int>& list, 
     const int* L = S->list_act.as<int>();
     const int nsteps = std::min(check_every, max_iter - it);
     CHECKED(run_steps(S, nsteps, use_graph && it > 0, [&]() -> int {
-      CHECKED(apply_h_rows(S, cs.p, cs.q, L, na, cs.eps));
-      CHECKED(apply_pc_rows(S, cs.q, L, na));
+      CHECKED(apply_hproj_rows(S, cs.p, cs.q, L, na, cs.eps));
       CHECKED(timed(S, STERN_K_CG, vecb * na * 7.0, 0.0, [&] { launch_cg_alpha(cs, L, na, tol * tol, st); }));
-      CHECKED(apply_pc_rows(S, cs.z, L, na));
-      CHECKED(timed(S, STERN_K_CG, vecb * na * 4.0, 0.0, [&] { launch_cg_beta(cs, L, na, st); }));
+      CHECKED(apply_pc_update(S, cs.z, cs.p, cs.beta, L, na));  // p = P_c z + beta p
       return 0;
     }));
     it += nsteps;
@@ -1009,8 +1059,7 @@ int run_cocg64(stern_system* S, const CgState& cs, const std::vector<int>& list,
     const int* L = S->list_act.as<int>();
     const int nsteps = std::min(check_every, max_iter - it);
     for (int k = 0; k < nsteps; ++k) {
-      CHECKED(apply_h_rows(S, cs.p, cs.q, L, na, cs.eps));
-      CHECKED(apply_pc_rows(S, cs.q, L, na));
+      CHECKED(apply_hproj_rows(S, cs.p, cs.q, L, na, cs.eps));
       CHECKED(timed(S, STERN_K_CG, vecb * na * 8.0, 0.0,
                     [&] { launch_cocg_alpha(cs, negk, rzi, u, L, na, tol * tol, st); }));
       CHECKED(apply_pc_rows(S, cs.z, L, na));
@@ -1031,8 +1080,7 @@ int run_cocg64(stern_system* S, const CgState& cs, const std::vector<int>& list,
       if (last) launch_set_flag(cs.flag, F, nf, 1, st);  // final check on everything still running
       launch_copy_rows(cs.x, cs.z, S->hb.npw_pad, F, nf, st);
       CHECKED(apply_pc_rows(S, cs.z, F, nf));
-      CHECKED(apply_h_rows(S, cs.z, cs.q, F, nf, cs.eps));
-      CHECKED(apply_pc_rows(S, cs.q, F, nf));
+      CHECKED(apply_hproj_rows(S, cs.z, cs.q, F, nf, cs.eps));
       launch_cocg_true(cs, u, F, nf, tol, st);
       if (!last) {
         CHECKED(apply_pc_rows(S, cs.z, F, nf));
@@ -1147,8 +1195,7 @@ int run_mixed(stern_system* S, const CgState& cs, const std::vector<int>& list, 
     // = 0 up to the ground state's eigen-residual, so the residual needs no projection of x, which
     // is projected once after the last step.
     CHECKED(timed(S, STERN_K_CG, na * (2.0 * vecb + vec32), 0.0, [&] { launch_add_d(cs.x, c32.d, K, L, na, st); }));
-    CHECKED(apply_h_rows(S, cs.x, cs.q, L, na, cs.eps));
-    CHECKED(apply_pc_rows(S, cs.q, L, na));
+    CHECKED(apply_hproj_rows(S, cs.x, cs.q, L, na, cs.eps));
     CHECKED(timed(S, STERN_K_CG, na * 3.0 * vecb, 0.0, [&] { launch_outer_resid(cs, L, na, tol, st); }));
     CHECKED(launch_check());
     HIPOK(hipMemcpyAsync(h_flag.data(), cs.flag, ns_all * sizeof(int), hipMemcpyDeviceToHost, st));
@@ -1443,8 +1490,7 @@ int stern_set_occupied(stern_system* S, int n_occ, const double* psi, const doub
   CHECKED(upload(S->band_eps, S->eps.data(), n_occ * sizeof(double), st));
   CHECKED(upload(S->band_invT, S->invT.data(), n_occ * sizeof(double), st));
   CHECKED(S->psi.ensure((size_t)S->nocc_pad * K * sizeof(Z64)));
-  // tmp_in also holds P_c KB below
-  CHECKED(S->tmp_in.ensure(std::max((size_t)n_occ * npw, (size_t)S->natoms_pad * K) * sizeof(Z64)));
+  CHECKED(S->tmp_in.ensure((size_t)n_occ * npw * sizeof(Z64)));
   HIPOK(hipMemcpyAsync(S->tmp_in.p, hp, (size_t)n_occ * npw * sizeof(Z64), hipMemcpyHostToDevice, st));
   launch_rows_gather(S->tmp_in.as<Z64>(), npw, S->psi.as<Z64>(), K, S->iperm.as<int>(), K, n_occ, st);
   launch_fill_zero(S->psi.as<Z64>() + (size_t)n_occ * K, (size_t)(S->nocc_pad - n_occ) * K, st);
@@ -1458,7 +1504,8 @@ int stern_set_occupied(stern_system* S, int n_occ, const double* psi, const doub
     const size_t tn = (size_t)Mt * K * 2 * sizeof(__bf16);
     for (DBuf* d : {&S->projT_hi, &S->projT_lo}) CHECKED(d->ensure(tn));
     __bf16 *th = S->projT_hi.as<__bf16>(), *tl = S->projT_lo.as<__bf16>();
-    Z64* pkb = S->tmp_in.as<Z64>();
+    CHECKED(S->pkb.ensure((size_t)Ma * K * sizeof(Z64)));
+    Z64* pkb = S->pkb.as<Z64>();
     HIPOK(hipMemcpyAsync(pkb, S->kb.p, (size_t)Ma * K * sizeof(Z64), hipMemcpyDeviceToDevice, st));
     const int ns = choose_nsplit(Mb, Ma, K, S->gemm64_wg);
     CHECKED(S->cpart.ensure((size_t)ns * Ma * Mb * sizeof(Z64)));
