@@ -9,6 +9,7 @@
 // on which k each lane group carries.
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "kernels.hpp"
 #include "stern.h"
@@ -63,47 +64,57 @@ __global__ __launch_bounds__(kGemmThreads) void k_zgemm_reduce(ZRows s0, ZRows s
     }
   // The next step's fragments are loaded before this step's products (every load unconditional:
   // columns past ncols read row 0, whose products are never stored), so they arrive while the
-  // products of this step run.
+  // products of this step run. A last block of 16 columns or fewer runs half the products.
   Z64 na0[2], na1[2], nx0[2], nx1[2];
-  auto load = [&](int kc) {
-    const int k = kc + 2 * g;
+  auto steps = [&](auto nb) {
+    constexpr int NB = decltype(nb)::value;
+    auto load = [&](int kc) {
+      const int k = kc + 2 * g;
 #pragma unroll
-    for (int bi = 0; bi < 2; ++bi) {
-      na0[bi] = ar[bi][k];
-      na1[bi] = ar[bi][k + 1];
-    }
+      for (int bi = 0; bi < 2; ++bi) {
+        na0[bi] = ar[bi][k];
+        na1[bi] = ar[bi][k + 1];
+      }
 #pragma unroll
-    for (int bj = 0; bj < 2; ++bj) {
-      nx0[bj] = xr[bj][k];
-      nx1[bj] = xr[bj][k + 1];
+      for (int bj = 0; bj < NB; ++bj) {
+        nx0[bj] = xr[bj][k];
+        nx1[bj] = xr[bj][k + 1];
+      }
+    };
+    if (kb < ke) load(kb);
+    for (int kc = kb; kc < ke; kc += 8) {
+      Z64 a0[2], a1[2], x0[2], x1[2];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        a0[u] = na0[u];
+        a1[u] = na1[u];
+      }
+#pragma unroll
+      for (int u = 0; u < NB; ++u) {
+        x0[u] = nx0[u];
+        x1[u] = nx1[u];
+      }
+      load(min(kc + 8, ke - 8));  // the last step reloads itself, unused
+#pragma unroll
+      for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+        for (int bj = 0; bj < NB; ++bj) {
+          // Re conj(a) x = a.re x.re + a.im x.im ; Im conj(a) x = a.re x.im - a.im x.re
+          cre[bi][bj] = mfma(a0[bi].re, x0[bj].re, cre[bi][bj]);
+          cre[bi][bj] = mfma(a0[bi].im, x0[bj].im, cre[bi][bj]);
+          cre[bi][bj] = mfma(a1[bi].re, x1[bj].re, cre[bi][bj]);
+          cre[bi][bj] = mfma(a1[bi].im, x1[bj].im, cre[bi][bj]);
+          cim[bi][bj] = mfma(a0[bi].re, x0[bj].im, cim[bi][bj]);
+          cim[bi][bj] = mfma(a0[bi].im, -x0[bj].re, cim[bi][bj]);
+          cim[bi][bj] = mfma(a1[bi].re, x1[bj].im, cim[bi][bj]);
+          cim[bi][bj] = mfma(a1[bi].im, -x1[bj].re, cim[bi][bj]);
+        }
     }
   };
-  if (kb < ke) load(kb);
-  for (int kc = kb; kc < ke; kc += 8) {
-    Z64 a0[2], a1[2], x0[2], x1[2];
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      a0[u] = na0[u];
-      a1[u] = na1[u];
-      x0[u] = nx0[u];
-      x1[u] = nx1[u];
-    }
-    load(min(kc + 8, ke - 8));  // the last step reloads itself, unused
-#pragma unroll
-    for (int bi = 0; bi < 2; ++bi)
-#pragma unroll
-      for (int bj = 0; bj < 2; ++bj) {
-        // Re conj(a) x = a.re x.re + a.im x.im ; Im conj(a) x = a.re x.im - a.im x.re
-        cre[bi][bj] = mfma(a0[bi].re, x0[bj].re, cre[bi][bj]);
-        cre[bi][bj] = mfma(a0[bi].im, x0[bj].im, cre[bi][bj]);
-        cre[bi][bj] = mfma(a1[bi].re, x1[bj].re, cre[bi][bj]);
-        cre[bi][bj] = mfma(a1[bi].im, x1[bj].im, cre[bi][bj]);
-        cim[bi][bj] = mfma(a0[bi].re, x0[bj].im, cim[bi][bj]);
-        cim[bi][bj] = mfma(a0[bi].im, -x0[bj].re, cim[bi][bj]);
-        cim[bi][bj] = mfma(a1[bi].re, x1[bj].im, cim[bi][bj]);
-        cim[bi][bj] = mfma(a1[bi].im, -x1[bj].re, cim[bi][bj]);
-      }
-  }
+  if (n0 + 16 < ncols)
+    steps(std::integral_constant<int, 2>{});
+  else
+    steps(std::integral_constant<int, 1>{});
   // D[i][j] of a 16x16 block: column j = lane % 16, row i = lane / 16 + 4 r in accumulator element r
 #pragma unroll
   for (int bj = 0; bj < 2; ++bj) {
@@ -270,55 +281,66 @@ __global__ __launch_bounds__(kGemmThreads, 4) void k_zgemm_expand(ZRows s0, ZRow
       dre[bi][bj] = v4d{0.0, 0.0, 0.0, 0.0};
       dim_[bi][bj] = v4d{0.0, 0.0, 0.0, 0.0};
     }
-  // next step's fragments loaded before this step's products; columns past ncols read column 0
+  // next step's fragments loaded before this step's products; columns past ncols read column 0; a last block
+  // of 16 columns or fewer runs half the products
   Z64 na0[2], na1[2], nc0[2], nc1[2];
-  for (int seg = 0; seg < 2; ++seg) {
-    const Z64* __restrict__ A = seg ? s1.A : s0.A;
-    const Z64* __restrict__ C = seg ? s1.C : s0.C;
-    const int M_pad = seg ? s1.M_pad : s0.M_pad, M = ((seg ? s1.M : s0.M) + 7) / 8 * 8;
-    if (M == 0) continue;
-    auto load = [&](int m) {
-      const int mm = m + 2 * g;
+  auto steps = [&](auto nb) {
+    constexpr int NB = decltype(nb)::value;
+    for (int seg = 0; seg < 2; ++seg) {
+      const Z64* __restrict__ A = seg ? s1.A : s0.A;
+      const Z64* __restrict__ C = seg ? s1.C : s0.C;
+      const int M_pad = seg ? s1.M_pad : s0.M_pad, M = ((seg ? s1.M : s0.M) + 7) / 8 * 8;
+      if (M == 0) continue;
+      auto load = [&](int m) {
+        const int mm = m + 2 * g;
 #pragma unroll
-      for (int bi = 0; bi < 2; ++bi) {
-        const int kk = k0 + 16 * bi + l16;
-        na0[bi] = A[(size_t)mm * K + kk];
-        na1[bi] = A[(size_t)(mm + 1) * K + kk];
-      }
-#pragma unroll
-      for (int bj = 0; bj < 2; ++bj) {
-        const size_t o = (size_t)(nv[bj] ? nn[bj] : 0) * M_pad + mm;
-        nc0[bj] = C[o];
-        nc1[bj] = C[o + 1];
-      }
-    };
-    load(0);
-    for (int m = 0; m < M; m += 8) {
-      Z64 a0[2], a1[2], c0[2], c1[2];
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        a0[u] = na0[u];
-        a1[u] = na1[u];
-        c0[u] = nc0[u];
-        c1[u] = nc1[u];
-      }
-      load(min(m + 8, M - 8));  // the last step reloads itself, unused
-#pragma unroll
-      for (int bi = 0; bi < 2; ++bi)
-#pragma unroll
-        for (int bj = 0; bj < 2; ++bj) {
-          // Re a c = a.re c.re - a.im c.im ; Im a c = a.re c.im + a.im c.re
-          dre[bi][bj] = mfma(a0[bi].re, c0[bj].re, dre[bi][bj]);
-          dre[bi][bj] = mfma(a0[bi].im, -c0[bj].im, dre[bi][bj]);
-          dre[bi][bj] = mfma(a1[bi].re, c1[bj].re, dre[bi][bj]);
-          dre[bi][bj] = mfma(a1[bi].im, -c1[bj].im, dre[bi][bj]);
-          dim_[bi][bj] = mfma(a0[bi].re, c0[bj].im, dim_[bi][bj]);
-          dim_[bi][bj] = mfma(a0[bi].im, c0[bj].re, dim_[bi][bj]);
-          dim_[bi][bj] = mfma(a1[bi].re, c1[bj].im, dim_[bi][bj]);
-          dim_[bi][bj] = mfma(a1[bi].im, c1[bj].re, dim_[bi][bj]);
+        for (int bi = 0; bi < 2; ++bi) {
+          const int kk = k0 + 16 * bi + l16;
+          na0[bi] = A[(size_t)mm * K + kk];
+          na1[bi] = A[(size_t)(mm + 1) * K + kk];
         }
+#pragma unroll
+        for (int bj = 0; bj < NB; ++bj) {
+          const size_t o = (size_t)(nv[bj] ? nn[bj] : 0) * M_pad + mm;
+          nc0[bj] = C[o];
+          nc1[bj] = C[o + 1];
+        }
+      };
+      load(0);
+      for (int m = 0; m < M; m += 8) {
+        Z64 a0[2], a1[2], c0[2], c1[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          a0[u] = na0[u];
+          a1[u] = na1[u];
+        }
+#pragma unroll
+        for (int u = 0; u < NB; ++u) {
+          c0[u] = nc0[u];
+          c1[u] = nc1[u];
+        }
+        load(min(m + 8, M - 8));  // the last step reloads itself, unused
+#pragma unroll
+        for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+          for (int bj = 0; bj < NB; ++bj) {
+            // Re a c = a.re c.re - a.im c.im ; Im a c = a.re c.im + a.im c.re
+            dre[bi][bj] = mfma(a0[bi].re, c0[bj].re, dre[bi][bj]);
+            dre[bi][bj] = mfma(a0[bi].im, -c0[bj].im, dre[bi][bj]);
+            dre[bi][bj] = mfma(a1[bi].re, c1[bj].re, dre[bi][bj]);
+            dre[bi][bj] = mfma(a1[bi].im, -c1[bj].im, dre[bi][bj]);
+            dim_[bi][bj] = mfma(a0[bi].re, c0[bj].im, dim_[bi][bj]);
+            dim_[bi][bj] = mfma(a0[bi].im, c0[bj].re, dim_[bi][bj]);
+            dim_[bi][bj] = mfma(a1[bi].re, c1[bj].im, dim_[bi][bj]);
+            dim_[bi][bj] = mfma(a1[bi].im, c1[bj].re, dim_[bi][bj]);
+          }
+      }
     }
-  }
+  };
+  if (n0 + 16 < ncols)
+    steps(std::integral_constant<int, 2>{});
+  else
+    steps(std::integral_constant<int, 1>{});
 #pragma unroll
   for (int bj = 0; bj < 2; ++bj) {
     if (!nv[bj]) continue;

@@ -637,8 +637,8 @@ size_t cpart_capacity(const stern_system* S, int M_pad, int nmax, int K) {
 }
 
 // Host staging for n flags and n list entries: copies from and to pinned memory are queued at once, where each of
-// a solve's many small pageable ones waits for a bounce buffer of the runtime's (one-atom FP64 chi0 call of 12
-// solves 3,550 -> 2,875 us; 23 mixed calls of 48 atoms, with the late polls below, 136.2 -> 132.0 ms).
+// a solve's many small pageable ones waits for a bounce buffer of the runtime's (one field of 16 bands, 515 plane
+// waves, FP64: 3,550 -> 2,875 us; 6 uneven cells x 8 fields, mixed, with the late polls below: 136.2 -> 132.0 ms).
 int ensure_pinned(stern_system* S, size_t n) {
   for (hipEvent_t& e : S->poll)
     if (!e) HIPOK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
