@@ -625,10 +625,12 @@ int apply_h32_rows(stern_system* S, const Z32* in, Z32* out, const int* list, in
   return 0;
 }
 
-// bytes of split-K partials for up to nmax columns (FP64 and FP32 partials)
+// bytes of split-K partials for up to nmax columns (FP64 and FP32 partials). Beyond the kernels for few columns
+// the split factors change only with the number of 64-column blocks, so the last column count of each block has
+// the most (trying every count took 0.5 ms of every 1,000-row call).
 size_t cpart_capacity(const stern_system* S, int M_pad, int nmax, int K) {
   size_t best = 0;
-  for (int n = 1; n <= nmax; ++n) {
+  for (int n = 1; n <= nmax; n = n < 64 || n == nmax ? n + 1 : std::min(n + 64, nmax)) {
     const size_t c = std::max((size_t)choose_nsplit(M_pad, n, K, S->gemm64_wg) * sizeof(Z64),
                               (size_t)choose_nsplit_bf16(M_pad, n, K, S->gemm16_wg) * sizeof(Z32)) * n;
     if (c > best) best = c;
@@ -667,11 +669,11 @@ int ensure_workspace(stern_system* S, int ns) {
   for (DBuf* d : {&S->wx, &S->wr, &S->wp, &S->wq, &S->wz, &S->wb}) CHECKED(d->ensure(vec));
   CHECKED(S->pen.ensure((size_t)ns * S->hb.N * S->hb.ncol_pad * sizeof(Z64)));
   const int mo = std::max(S->nocc_pad, 64), mp = mo + S->natoms_pad;  // one operand, or both in one buffer
-  CHECKED(S->cpart.ensure(std::max({cpart_capacity(S, mo, ns, (int)K), cpart_capacity(S, S->natoms_pad, ns, (int)K),
-                                    cpart_capacity(S, mp, ns, (int)K)})));
+  const size_t co = cpart_capacity(S, mo, ns, (int)K);
+  CHECKED(S->cpart.ensure(std::max({co, cpart_capacity(S, S->natoms_pad, ns, (int)K), cpart_capacity(S, mp, ns, (int)K)})));
   CHECKED(S->cmat.ensure((size_t)ns * mp * sizeof(Z64)));
   if (const int nc = cg_chunks((int)K)) CHECKED(S->sv_part.ensure((size_t)ns * nc * 3 * sizeof(double)));
-  CHECKED(S->cpart2.ensure(cpart_capacity(S, std::max(S->nocc_pad, 64), ns, (int)K)));
+  CHECKED(S->cpart2.ensure(co));
   for (DBuf* d : {&S->sv_eps, &S->sv_invT, &S->sv_bb, &S->sv_rz, &S->sv_rr, &S->sv_tres, &S->sv_rzi, &S->sv_beta})
     CHECKED(d->ensure((size_t)ns * sizeof(double)));
   for (DBuf* d : {&S->sv_band, &S->sv_pert, &S->sv_flag, &S->sv_iters, &S->list_act, &S->list_f})
