@@ -403,9 +403,10 @@ int stern_model_fit_step(stern_model* m, int Nc, int n, const float* in, const f
 /* ---- kernel variants and the autotuner ----
  * Tunables of a system (each keeps its value until set again):
  *   STERN_TUNE_PLANE64   yz-plane kernel of the FP64 H apply: 0 the whole plane
- *                        in LDS, 1 only the active z lines in LDS with per-wave
- *                        transforms (the default when its LDS fits), 2 as 1 with
- *                        the next pair's loads issued ahead (more registers)
+ *                        in LDS, 1 only the active z lines in LDS, on even grids
+ *                        with whole lines in registers and else with per-wave
+ *                        transforms (the default when its LDS fits), 2 per-wave
+ *                        transforms with the next pair's loads issued ahead
  *   STERN_TUNE_PLANE32   the same for the FP32 H apply of the mixed inner solve
  *   STERN_TUNE_GEMM64_WG workgroups the split-K FP64 reduces (Psi^H Y, B^H Y) aim
  *                        for; 0 = built-in default (2048)

@@ -229,8 +229,7 @@ __global__ __launch_bounds__(kCgThreads) void k_cg_alpha(CgState S, const int* _
 }
 
 // The same for long rows, kCgChunk coefficients to a workgroup, the sums in parts added in order by the next
-// kernel: a few late rows in one workgroup each would leave the card idle (16,896 coefficients: 45 us a
-// launch for one row).
+// kernel: a few late rows in one workgroup each would leave the card idle.
 constexpr int kCgChunk = 2048;
 __global__ __launch_bounds__(kCgThreads) void k_cg_pq(CgState S, const int* __restrict__ act) {
   __shared__ double sh[kCgThreads / 64];
@@ -331,7 +330,7 @@ __global__ __launch_bounds__(kCgThreads) void k_cg_restart(CgState S, const int*
 // and column order, padding included. Bound by memory (32 B a coefficient plus the index): the writes are
 // consecutive and the reads gather 16-byte coefficients from all over one row, so all blocks of a row get
 // consecutive slots of one XCD (workgroup L runs on XCD L mod 8) and its lines are fetched into one L2 once.
-// 1,000 rows of 16,879 coefficients: 128 us a direction, against 1,000 launches of 3 us, one per row, and a
+// 1,000 rows of 16,879 coefficients: 148 us a direction, against 1,000 launches of 3 us, one per row, and a
 // copy of all rows before.
 constexpr int kRowsPer = 4;  // coefficients per thread
 __global__ __launch_bounds__(256) void k_rows_gather(const Z64* __restrict__ src, int ld_src, Z64* __restrict__ dst,
@@ -426,8 +425,8 @@ __global__ __launch_bounds__(kCgThreads) void k_cg32_init2(Cg32State S, const in
 // flag 1 once ||r||^2 <= tol2 ||r0||^2. (r, z) is taken with z before any
 // projection: r stays in range(P_c), so it equals (r, P_c z).
 // Rows longer than one workgroup's registers: kAlphaChunk coefficients to a workgroup, the two sums in
-// parts added in order by the next kernel. (One workgroup to a whole row left all but a few CUs idle
-// once the list had shrunk: 91,072 coefficients took 150 us a launch for one row as for 200.)
+// parts added in order by the next kernel. (One workgroup to a whole row leaves all but a few CUs idle
+// once the list has shrunk: 91,072 coefficients, average over a solve of 1,024 rows: 385 us a launch, 248 in chunks.)
 constexpr int kAlphaChunk = 4096;  // 16 per thread
 
 __global__ __launch_bounds__(kCgThreads) void k_cg32_pq(Cg32State S, const int* __restrict__ act,

@@ -133,8 +133,8 @@ __global__ __launch_bounds__(kGemmThreads) void k_zgemm_reduce(ZRows s0, ZRows s
 // 16 BJ columns, so that 16 BJ columns cost the matrix cores what they hold and not the 64 of the tile
 // above, and K is split much finer, as one wave's chain over a long chunk is what such a reduce waits for
 // (64 cycles a product, 8 BJ products and one load latency a step). The loads of a step are issued two
-// steps ahead. M = 16 (64 with padding), 7 columns, K = 576: 48 -> 7 us; M = 128, 16 columns, K = 16,896:
-// 48 -> 13 us.
+// steps ahead. M = 16 (64 with padding), up to 16 columns, K = 576: 48 -> 5.6 us; M = 128, up to 16 columns,
+// K = 16,896: 48 -> 11.4 us, both averages over a solve.
 template <int BJ>
 __global__ __launch_bounds__(kGemmThreads) void k_zgemm_reduce_cols(ZRows s0, ZRows s1, int mb0, int ldx,
                                                                     const int* __restrict__ xidx, int ncols, int K,
@@ -210,7 +210,8 @@ __global__ __launch_bounds__(kGemmThreads) void k_zgemm_reduce_cols(ZRows s0, ZR
 
 // C[n][m] = scale * sum over the splits, m < M. P threads to an output (1, or 8 where there are at least as
 // many splits, so that a few outputs of many splits are still read by many threads): each sums every P-th
-// split and the parts are added in order. 16 columns of M = 128 in 132 splits: 18 -> 6 us.
+// split and the parts are added in order. M = 128 at K = 16,896, average over an FP64 solve:
+// 18 -> 10 us.
 template <int P>
 __global__ __launch_bounds__(256) void k_sum_parts(ZRows s0, ZRows s1, int nb0, int nsplit, int ncols) {
   constexpr int O = 256 / P;  // outputs per workgroup; workgroups from nb0 on belong to the second operand
@@ -359,7 +360,8 @@ __global__ __launch_bounds__(kGemmThreads, 4) void k_zgemm_expand(ZRows s0, ZRow
 }
 
 // The expand for few columns: a wave takes 16 k and 16 BJ columns (see k_zgemm_reduce_cols), the loads of a
-// step two steps ahead. M = 16, 7 columns, K = 576: 12 -> 5 us; M = 128, 16 columns, K = 16,896: 43 -> 14 us.
+// step two steps ahead. Up to 16 columns, averages over a solve: M = 16, K = 576: 12 -> 4.3 us;
+// M = 128, K = 16,896: 43 -> 15 us.
 template <int BJ, bool PUPD>
 __global__ __launch_bounds__(kGemmThreads) void k_zgemm_expand_cols(ZRows s0, ZRows s1, int K, Z64* __restrict__ Y,
                                                                     int ldy, const int* __restrict__ yidx, int ncols,
@@ -452,7 +454,8 @@ int nsplit_bound(int M_pad, int ncols, int K, int target) {
 
 // A split-K reduce's workgroups all take the same time, and kGemm64Resident of them run at once (4 waves
 // per SIMD): a factor that leaves the last round nearly empty wastes it. 517 columns of M = 1,024, K = 91,072 in 15
-// splits are 2,160 workgroups, three rounds for 2.1; in 14 they are 2,016, two: 8.3 -> 6.4 ms.
+// splits are 2,160 workgroups, three rounds for 2.1; in 14 they are 2,016, two: 8.3 -> 7.6 ms (7.2 ms with the last block of columns
+// at half its products).
 constexpr int kGemm64Resident = 1024;
 
 int choose_nsplit(int M_pad, int ncols, int K, int target) {

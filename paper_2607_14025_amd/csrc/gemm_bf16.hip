@@ -247,7 +247,7 @@ __host__ __device__ __forceinline__ size_t blk_index(int m, int row, int nrows) 
 // Sum over the splits of the 256 / P outputs of a workgroup, P threads to an output (each every P-th split,
 // the parts added in order), valid in the threads of part 0. at(s): element of split s. P = 8 where there
 // are as many splits: a few live columns of hundreds of splits left most of the card waiting on one
-// thread's chain of loads (128^3 cell, 256 bands: 102 -> 20 us a launch over a solve).
+// thread's chain of loads (128^3 cell, 256 bands: 102 -> 26 us a launch over a solve).
 template <int P, class At>
 __device__ __forceinline__ Z32 sum_splits(bool on, int nsplit, Z32* sh, At at) {
   constexpr int O = 256 / P;

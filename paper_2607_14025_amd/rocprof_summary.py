@@ -229,7 +229,7 @@ def mfma(csv_path: str, title: str, cmd: str, simds: int = 1024, xcds: int = 8, 
             d = per.setdefault(int(r["Dispatch_Id"]), {"name": short_name(r["Kernel_Name"])})
             d[r["Counter_Name"]] = d.get(r["Counter_Name"], 0.0) + float(r["Counter_Value"])
     order = sorted(per)
-    dn = [i for i in order if per[i]["name"].startswith("k_plane_dn")]
+    dn = [i for i in order if per[i]["name"].startswith(("k_plane_dn", "k_plane_sum_quarter"))]
     if len(dn) < 2:
         raise SystemExit(f"{csv_path}: fewer than two Delta n dispatches")
     last = [i for i in order if dn[-2] < i <= dn[-1]]
@@ -273,7 +273,7 @@ def sq(csv_path: str, title: str, cmd: str, kernel: str) -> str:
             d = per.setdefault(int(r["Dispatch_Id"]), {"name": r["Kernel_Name"]})
             d[r["Counter_Name"]] = d.get(r["Counter_Name"], 0.0) + float(r["Counter_Value"])
     order = sorted(per)
-    dn = [i for i in order if short_name(per[i]["name"]).startswith("k_plane_dn")]
+    dn = [i for i in order if short_name(per[i]["name"]).startswith(("k_plane_dn", "k_plane_sum_quarter"))]
     if len(dn) < 2:
         raise SystemExit(f"{csv_path}: fewer than two Delta n dispatches")
     mine = [per[i] for i in order if dn[-2] < i <= dn[-1] and matches(kernel, per[i]["name"])]
