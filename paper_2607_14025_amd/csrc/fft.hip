@@ -275,18 +275,20 @@ __device__ __forceinline__ void y_inverse_from_pencils(const PlaneCtx<N, T>& c, 
   __syncthreads();
 }
 
-// forward DFT along y on the active z lines (in LDS) -> pencils of one plane
-template <int N, class T>
+// forward DFT along y on the active z lines (in LDS) -> pencils of one plane. MAXF: the most active lines that
+// the geometry may have; the first stage holds all of its items in registers, so lines beyond it would be left out.
+// The wave functions' sphere has N / 2 + 1 at most, the 4 Ecut sphere up to N.
+template <int N, class T, int MAXF = N / 2 + 1>
 __device__ __forceinline__ void y_forward_to_pencils(const PlaneCtx<N, T>& c, Z<T>* __restrict__ tp) {
   constexpr int LD = PlaneCtx<N, T>::LD, R1 = PlaneCtx<N, T>::R1, R2 = PlaneCtx<N, T>::R2, NT = PlaneCtx<N, T>::NT;
   Z<T>* P = c.P;
   const int* zl = c.zl;
   const int* yc = c.yc;
-  stage<N, R1, -1, false, true, true, NT, N / 2 + 1>(
+  stage<N, R1, -1, false, true, true, NT, MAXF>(
       c.nza, [&](int f, int j, int r) { return P[(j + r * R2) * LD + zl[f]]; },
       [&](int f, int j, int r, Z<T> v) { P[(j * R1 + r) * LD + zl[f]] = v; }, c.tw);
   __syncthreads();
-  stage<N, R2, -1, true, false, true, NT, N / 2 + 1>(
+  stage<N, R2, -1, true, false, true, NT, MAXF>(
       c.nza, [&](int f, int j, int r) { return P[(j + r * R1) * LD + zl[f]]; },
       [&](int f, int j, int r, Z<T> v) {
         const int col = yc[(j + r * R1) * c.nza + f];
@@ -1233,7 +1235,7 @@ __global__ __launch_bounds__(plane_nt<N>()) void k_plane_full_fwd(const Z64* __r
       },
       c.tw);
   __syncthreads();
-  y_forward_to_pencils<N, double>(c, pen + ((size_t)vec * N + ix) * g.ncol_pad);
+  y_forward_to_pencils<N, double, N>(c, pen + ((size_t)vec * N + ix) * g.ncol_pad);
 }
 
 // One workgroup per (plane ix, perturbation p): for the nb bands of p in band
