@@ -1196,7 +1196,10 @@ int run_mixed(stern_system* S, const CgState& cs, const std::vector<int>& list, 
     // check_every iterations (eager, or captured once into a hipGraph and replayed)
     // needs one read of the count at its end and no other host round trip. The host
     // reads it one window late, while the next one runs: the count only bounds grids,
-    // and a window after the last solve has converged finds no live entry.
+    // and a window after the last solve has converged finds no live entry. With the
+    // per-launch profile it reads the window's own count, as the work that is credited
+    // to each launch is that of the count.
+    const bool late = !S->prof_on;
     int ni = (int)iact.size();
     int* F = S->list_f.as<int>();
     int* cnt = S->m_cnt.as<int>();
@@ -1232,9 +1235,10 @@ int run_mixed(stern_system* S, const CgState& cs, const std::vector<int>& list, 
       const int slot = win & 1;
       HIPOK(hipMemcpyAsync(S->pin + slot, cnt, sizeof(int), hipMemcpyDeviceToHost, st));
       HIPOK(hipEventRecord(S->poll[slot], st));
-      if (win == 0) continue;
-      HIPOK(hipEventSynchronize(S->poll[slot ^ 1]));
-      ni = S->pin[slot ^ 1];
+      if (late && win == 0) continue;
+      const int got = late ? slot ^ 1 : slot;
+      HIPOK(hipEventSynchronize(S->poll[got]));
+      ni = S->pin[got];
       cap = std::min(cap, ni);
     }
     // FP64 update and true residual. x keeps the occupied components the inner solves leave (at
