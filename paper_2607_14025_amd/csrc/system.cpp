@@ -702,10 +702,23 @@ int ensure_workspace32(stern_system* S, int ns) {
   return 0;
 }
 
+// Memory that a call can do without: false where it is not there, with no error left behind (the runtime keeps a
+// failed allocation as its last error, which the next launch check would report; one that was there before stays).
+template <class F>
+bool optional_memory(F&& alloc) {
+  const bool clean = hipPeekAtLastError() == hipSuccess;
+  const std::string before = g_err;
+  if (alloc() >= 0) return true;
+  g_err = before;
+  if (clean) (void)hipGetLastError();
+  return false;
+}
+
 // scratch of the band sums' segments; null (one segment) where none is needed or the memory is not there
 double* sum_scratch(stern_system* S, int nb, int np, bool cplx) {
   const size_t bytes = plane_sum_scratch(S->geom(), nb, np, cplx);
-  return bytes == 0 || S->sum_part.ensure(bytes) < 0 ? nullptr : S->sum_part.as<double>();
+  if (bytes == 0 || !optional_memory([&] { return S->sum_part.ensure(bytes); })) return nullptr;
+  return S->sum_part.as<double>();
 }
 
 Cg32State cg32_state(stern_system* S, int* iters) {
