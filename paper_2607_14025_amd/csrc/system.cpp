@@ -1737,22 +1737,27 @@ static int liouville_rows(stern_system* S, const Z64* A, Z64* out, int n_exc) {
   // excitations at a time: what the pencils hold, or the full grids
   const int ce = fused ? std::max(1, std::min({n_exc, S->ws_solves / nb, 65535 / nb})) : liouville_chunk(S, n_exc);
   const bool exch = S->lv_alpha != 0.0 || S->n_scr > 0;
-  const int vb = exch ? exch_bands(S) : 0;
-  const int np = std::max(ce, vb * nb);  // grids through the potential stage at once
   if (!fused) CHECKED(S->lv_ar.ensure((size_t)ce * nb * n3 * sizeof(Z64)));
   CHECKED(S->lv_rho.ensure((size_t)ce * n3 * sizeof(Z64)));
-  CHECKED(S->lv_rhog.ensure((size_t)np * Kd * sizeof(Z64)));
-  CHECKED(S->lv_pend.ensure((size_t)np * N * S->hbd.ncol_pad * sizeof(Z64)));
-  if (exch) {
+  if (exch) CHECKED(S->lv_acc.ensure((size_t)ce * nb * n3 * sizeof(Z64)));
+  // grids through the potential stage at once: the excitations' densities, or the pairs of vb bands
+  auto potential_buffers = [&](int vb) -> int {
+    const size_t np = std::max(ce, vb * nb);
+    CHECKED(S->lv_rhog.ensure(np * Kd * sizeof(Z64)));
+    CHECKED(S->lv_pend.ensure(np * N * S->hbd.ncol_pad * sizeof(Z64)));
+    if (!exch) return 0;
     CHECKED(S->lv_tau.ensure((size_t)vb * nb * n3 * sizeof(Z64)));
-    CHECKED(S->lv_acc.ensure((size_t)ce * nb * n3 * sizeof(Z64)));
     if (S->n_scr > 0) {  // the pairs' coefficients, then the partial sums they come from
       size_t parts = 0;
       for (int v0 = 0; v0 < nb; v0 += vb)
         parts = std::max(parts, (size_t)scr_proj_stretches(v0, std::min(vb, nb - v0), S->n_scr, n3));
       CHECKED(S->scr_proj.ensure((parts + 1) * vb * nb * S->n_scr * sizeof(Z64)));
     }
-  }
+    return 0;
+  };
+  int vb = exch ? exch_bands(S) : 0;
+  while (vb > 1 && !optional_memory([&] { return potential_buffers(vb); })) --vb;  // fewer bands where they do not fit
+  if (vb <= 1) CHECKED(potential_buffers(vb));
   CHECKED(S->lv_k.ensure((size_t)n * K * sizeof(Z64)));
   CHECKED(S->lv_eps.ensure((size_t)n * sizeof(double)));
   {

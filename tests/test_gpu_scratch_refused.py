@@ -68,3 +68,34 @@ def test_transition_densities_without_segment_scratch(tiny_system, refusing):
         s.close()
     assert len(refusing["seen"]) == 1
     assert abs(out[0] - out[1]).max() <= 1e-13 * abs(out[0]).max()
+
+
+@pytest.mark.parametrize("limit", [1, 2, 3])
+def test_direct_term_in_smaller_blocks(refusing, limit):
+    """The pairs' potentials of `limit` bands at most fit: the direct term takes fewer bands at a time."""
+    import numpy as np
+    from oracle import OracleCell
+    from oracle.liouville import liouville_apply
+    from paper_2607_14025_amd import System
+    from synth.cells import CellSpec, place_atoms
+    L, ecut, nocc, n_scr = 8.0, 6.0, 9, 5
+    pos = place_atoms(CellSpec("exchange_blocks", 7, L, ecut, 3, 4, 1))
+    cell = OracleCell(L, ecut, pos)
+    rng = np.random.default_rng(3)
+    psi = np.ascontiguousarray(np.linalg.qr(rng.standard_normal((cell.npw, nocc)) +
+                                            1j * rng.standard_normal((cell.npw, nocc)))[0].T)
+    eps = np.linspace(-0.8, -0.1, nocc)
+    screen = (rng.standard_normal((n_scr, cell.N, cell.N, cell.N)), rng.uniform(-0.8, 0.2, n_scr))
+    a = rng.standard_normal((1, nocc, cell.npw)) + 1j * rng.standard_normal((1, nocc, cell.npw))
+    s = System(L, ecut, pos, torch_allocator=True)
+    mil = s.miller()
+    s.set_occupied(cell.give(psi, mil), eps)
+    s.liouville_set_kernel(1.0)
+    s.liouville_set_screening(*screen)
+    refusing["sizes"] = lambda n: limit * nocc * cell.N ** 3 * 16 < n <= 4 * nocc * cell.N ** 3 * 16
+    out = s.liouville_apply(cell.give(a.reshape(-1, cell.npw), mil).reshape(a.shape))
+    s.close()
+    assert refusing["seen"]
+    out = cell.take(out.reshape(-1, cell.npw), mil).reshape(a.shape)
+    ref = liouville_apply(cell, psi, eps, a, 1.0, screen)
+    assert np.abs(out - ref).max() <= 1e-12 * np.abs(ref).max()
