@@ -72,7 +72,9 @@ extern "C" {
    tolerance after a loose one. FP64, mixed and imaginary-frequency solves. */
 #define STERN_GUESS_PREVIOUS 3
 
-/* where pointer arguments live */
+/* where pointer arguments live. STERN_MEM_DEVICE: memory of the system's own device. Rows of
+   stern_apply_h, stern_apply_pc and the Liouville calls may also lie in another device's memory (they are
+   copied); stern_apply_pc_noalloc and the fields of stern_apply_chi0 are used in place. */
 #define STERN_MEM_HOST 0
 #define STERN_MEM_DEVICE 1
 

@@ -20,6 +20,7 @@
 #include "../../include/stern.h"
 #include "basis.hpp"
 #include "hostla.hpp"
+#include "rows.hpp"
 #include "kernels.hpp"
 
 using namespace stern;
@@ -1601,16 +1602,22 @@ int stern_set_occupied(stern_system* S, int n_occ, const double* psi, const doub
   return STERN_OK;
 }
 
-// the callers' device arrays are read and written in place when 16-byte loads may be used on them
-static bool direct_rows(const void* p, int mem_kind) {
-  return mem_kind == STERN_MEM_DEVICE && (reinterpret_cast<uintptr_t>(p) & (alignof(Z64) - 1)) == 0;
+// whether a caller's device array is read and written in place (rows.hpp)
+static bool direct_rows(const stern_system* S, const void* p, int mem_kind) {
+  if (mem_kind != STERN_MEM_DEVICE) return false;
+  const bool clean = hipPeekAtLastError() == hipSuccess;
+  hipPointerAttribute_t a{};
+  const bool known = hipPointerGetAttributes(&a, p) == hipSuccess;
+  if (!known && clean) (void)hipGetLastError();  // memory that the runtime does not know: copied
+  return rows_in_place(known && a.type == hipMemoryTypeDevice && !a.isManaged, a.device, S->device,
+                       reinterpret_cast<std::uintptr_t>(p));
 }
 
 static int rows_in(stern_system* S, int n_vec, const double* c, int mem_kind, DBuf& dst) {
   const int npw = S->hb.npw, K = S->hb.npw_pad;
   CHECKED(dst.ensure((size_t)n_vec * K * sizeof(Z64)));
   const Z64* src = reinterpret_cast<const Z64*>(c);
-  if (!direct_rows(c, mem_kind)) {
+  if (!direct_rows(S, c, mem_kind)) {
     CHECKED(S->tmp_out.ensure((size_t)n_vec * npw * sizeof(Z64)));
     HIPOK(hipMemcpyAsync(S->tmp_out.p, c, (size_t)n_vec * npw * sizeof(Z64),
                          mem_kind == STERN_MEM_DEVICE ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, S->stream));
@@ -1623,7 +1630,7 @@ static int rows_in(stern_system* S, int n_vec, const double* c, int mem_kind, DB
 static int rows_out(stern_system* S, int n_vec, const Z64* src, double* out, int mem_kind) {
   const int npw = S->hb.npw, K = S->hb.npw_pad;
   Z64* dst = reinterpret_cast<Z64*>(out);
-  const bool direct = direct_rows(out, mem_kind);
+  const bool direct = direct_rows(S, out, mem_kind);
   if (!direct) {
     CHECKED(S->tmp_out.ensure((size_t)n_vec * npw * sizeof(Z64)));
     dst = S->tmp_out.as<Z64>();
