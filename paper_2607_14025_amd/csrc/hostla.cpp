@@ -1,5 +1,5 @@
 // Cyclic Jacobi eigensolvers (Golub and Van Loan, Matrix Computations, ch. 8) for the projected
-// matrices of the PDEP and Liouville Davidson iterations.
+// matrices of the PDEP and Liouville Davidson iterations, and normal deviates for their starts.
 #include "hostla.hpp"
 
 #include <algorithm>
@@ -116,6 +116,22 @@ void jacobi_zheev(std::vector<std::complex<double>> A, int n, std::vector<double
     for (int k = 0; k < n; ++k) Vs[(size_t)k * n + j] = V[(size_t)k * n + ord[j]];
   }
   V.swap(Vs);
+}
+
+void fill_normal(std::mt19937_64& rng, double* x, std::size_t n) {
+  constexpr double below_one = 1.0 - 0x1p-53;
+  auto uniform = [&] { return std::min((double)rng() * 0x1p-64, below_one); };  // in [0, 1)
+  for (std::size_t i = 0; i < n; i += 2) {
+    double a, b, r2;
+    do {
+      a = 2.0 * uniform() - 1.0;
+      b = 2.0 * uniform() - 1.0;
+      r2 = a * a + b * b;
+    } while (r2 > 1.0 || r2 == 0.0);
+    const double m = std::sqrt(-2.0 * std::log(r2) / r2);
+    x[i] = b * m;
+    if (i + 1 < n) x[i + 1] = a * m;
+  }
 }
 
 }  // namespace stern

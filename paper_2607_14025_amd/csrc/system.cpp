@@ -2094,9 +2094,8 @@ int stern_liouville_davidson(stern_system* S, int n_eig, int block, int max_basi
   // seeded random start, shaped by P_c K
   {
     std::mt19937_64 rng(seed);
-    std::normal_distribution<double> nd;
     std::vector<double> h((size_t)n_start * nb * npw * 2);
-    for (auto& x : h) x = nd(rng);
+    fill_normal(rng, h.data(), h.size());
     CHECKED(rows_in(S, n_start * nb, h.data(), STERN_MEM_HOST, S->wr));
     CHECKED(precond_rows(S, S->wr.as<Z64>(), T, n_start * nb));
   }
@@ -3043,11 +3042,10 @@ int stern_autotune(stern_system* S, int n_vec, const char* cache_path, int* chos
   CHECKED(ensure_workspace32(S, n_vec));
   {
     std::mt19937_64 rng(12345);
-    std::normal_distribution<double> nd(0.0, 1.0);
     std::vector<Z64> h((size_t)n_vec * K, zmk(0.0, 0.0));
     std::vector<double> e(n_vec);
     for (int v = 0; v < n_vec; ++v) {
-      for (int k = 0; k < npw; ++k) h[(size_t)v * K + k] = zmk(nd(rng), nd(rng));
+      fill_normal(rng, &h[(size_t)v * K].re, 2 * (size_t)npw);
       e[v] = S->eps[v % S->n_occ];
     }
     HIPOK(hipMemcpyAsync(S->wp.p, h.data(), h.size() * sizeof(Z64), hipMemcpyHostToDevice, st));
