@@ -1845,12 +1845,24 @@ void launch_plane_rho(const FftGeom& g, const Z64* pen, const Z64* psi_r, int nb
                    }));
 }
 
+// Grids whose right-hand sides stay with the full plane in LDS, where that is the faster of the two: the kernel with lines
+// in registers runs one wave per SIMD at 96 (256 registers and more, and the z pass has work for 3 of 4 waves), two at 54
+// with a sixth of the z pass's lanes and 60% of the y pass's idle. Microseconds, full plane against lines in registers:
+//     54, 64 bands x 1, 8, 32 fields:   56, 271, 1,030    68, 285, 1,038
+//     96, 96 bands x 1, 8, 16 fields:  519, 2,617, 4,985   782, 4,782, 9,965
+// and on the grids beside them 48, 54 x 8: 220, 164; 64, 64 x 8: 489, 413; 72, 128 x 8: 1,509, 1,376; beyond 96 the full
+// plane does not fit and the kernel in its place takes 7,814 us for 108, 96 x 8, against 5,958.
+template <int NN>
+constexpr bool rhs_full_plane() {
+  return NN == 54 || NN == 96;
+}
+
 void launch_plane_rhs(const FftGeom& g, const Z64* psi_r, const double* dv, int v0, int nb, int i0, int npert,
                       const int* band, const int* pert, Z64* pen, hipStream_t st) {
   if (nb <= 0 || npert <= 0) return;
   STERN_DISPATCH_N(g.N, ({
-                     if (half_plane<NN, double>(g.zact_lo)) {
-                       if constexpr (half_grid<NN, double>())
+                     if (half_plane<NN, double>(g.zact_lo) && !rhs_full_plane<NN>()) {
+                       if constexpr (half_grid<NN, double>() && !rhs_full_plane<NN>())
                          plane_mul_half_n<NN, double>(g, psi_r, dv + (size_t)i0 * NN * NN * NN, v0, nb, npert, pen,
                                                       st);
                      } else if constexpr (full_plane_fits<NN>()) {
