@@ -1797,12 +1797,22 @@ template <int NN>
 constexpr bool quarter_grid() {
   return NN % 4 == 0;
 }
-// Whether k_plane_sum_quarter runs on this geometry. The density response at N = 72 stays with the full plane
-// in LDS: 4 N lanes are 5 waves there, so one SIMD does twice the others' work (128 bands x 16 fields: 5.9
-// against 4.75 ms); the transition densities still gain, as they take the place of two passes over full grids.
+// Whether the waves of a workgroup of k_plane_sum_quarter spread so unevenly over the 4 SIMDs that the density response
+// is faster with the full plane in LDS: where the busiest SIMD has more than one and a half times the average. That is
+// five waves (N = 72; 128 bands x 16 fields: 5.9 against 4.69 ms). Six (N = 96; 96 x 8: 3.04 against 3.38 ms) and seven
+// (N = 108; 96 x 8: 4.2 against 15.0 ms for the kernel that runs where the full plane does not fit) gain, and with
+// fewer than four the SIMDs take waves of several workgroups. The transition densities gain at 72 too, as they take the
+// place of two passes over full grids.
+template <int NN>
+constexpr bool uneven_waves() {
+  constexpr int W = PlaneQCfg<NN, false>::NT / 64;
+  return W > 4 && 2 * (4 * ((W + 3) / 4)) > 3 * W;
+}
+// whether k_plane_sum_quarter runs on this geometry
 template <int NN, bool CPLX>
 bool quarter_plane(const FftGeom& g) {
-  if constexpr (!quarter_grid<NN>() || (!CPLX && PlaneQCfg<NN, CPLX>::NT == 320)) return false;
+  if constexpr (!quarter_grid<NN>()) return false;
+  else if constexpr (!CPLX && uneven_waves<NN>()) return false;
   else return half_plane<NN, double>(g.zact_lo) && planeq_lds_bytes<NN, CPLX>(g.nza, g.ncol) <= 160 * 1024;
 }
 }  // namespace
