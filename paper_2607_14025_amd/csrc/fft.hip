@@ -1736,14 +1736,22 @@ void launch_plane_hw(const FftGeom& g, Z<T>* pen, const int* vidx, int nvec, con
                        launch_plane_hw_n<NN, T, false>(g, pen, vidx, nvec, vt, st);
                    }));
 }
+// LDS of one workgroup of the kernels that variants 1 and 2 of the H apply choose from on grid N
+template <int NN, class T>
+constexpr size_t plane_variants_lds(int nza) {
+  using S = PlaneShape<NN, T>;
+  size_t r = planew_lds_bytes<NN, T, S::W, S::ZR>(nza);
+  if constexpr (half_grid<NN, T>()) {
+    const size_t h = planeh_lds_bytes<NN, T>(PlaneHCfg<NN, T>::NV, nza);
+    r = h > r ? h : r;
+    // the kernel fits with as many active lines as a grid can have
+    static_assert(planeh_lds_bytes<NN, T>(PlaneHCfg<NN, T>::NV, 2 * HalfFft<NN, T>::K + 1) <= 160 * 1024);
+  }
+  return r;
+}
 size_t plane_hw_lds(int N, int nza, bool fp64) {
   size_t r = 0;
-  STERN_DISPATCH_N(N, ({
-                     using S64 = PlaneShape<NN, double>;
-                     using S32 = PlaneShape<NN, float>;
-                     r = fp64 ? planew_lds_bytes<NN, double, S64::W, S64::ZR>(nza)
-                              : planew_lds_bytes<NN, float, S32::W, S32::ZR>(nza);
-                   }));
+  STERN_DISPATCH_N(N, (r = fp64 ? plane_variants_lds<NN, double>(nza) : plane_variants_lds<NN, float>(nza)));
   return r;
 }
 template void launch_plane_hw<double>(const FftGeom&, Z64*, const int*, int, const double*, bool, hipStream_t);
@@ -1945,7 +1953,8 @@ void launch_plane_dn(const FftGeom& g, const Z64* pen, const Z64* psi_r, int ban
                    }));
 }
 
-// LDS of the FP64 plane kernels of the RHS, psi_v(r) and dn for grid N
+// LDS of one workgroup of the FP64 plane kernels of the RHS, psi_v(r) and dn on grid N (k_plane_sum_quarter asks for
+// its own room where it is chosen)
 size_t plane_fp64_lds(int N, int nza) {
   size_t r = 0;
   STERN_DISPATCH_N(N, ({
@@ -1953,6 +1962,11 @@ size_t plane_fp64_lds(int N, int nza) {
                        r = plane_lds_bytes(NN, sizeof(Z64));
                      else
                        r = cw_lds_bytes<NN>(nza);
+                     if constexpr (half_grid<NN, double>() && !rhs_full_plane<NN>()) {
+                       constexpr int NV = PlaneHCfg<NN, double>::NV;
+                       static_assert(planem_lds_bytes<NN>(NV, 2 * HalfFft<NN, double>::K + 1) <= 160 * 1024);
+                       r = std::max(r, planem_lds_bytes<NN>(NV, nza));
+                     }
                    }));
   return r;
 }

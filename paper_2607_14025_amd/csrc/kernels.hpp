@@ -43,7 +43,8 @@ static_assert(kColPad % 32 == 0 && kColPad % 16 == 0, "column padding must hold 
 
 bool fft_size_supported(int N);
 size_t plane_lds_bytes(int N, int elem_bytes);
-// LDS of the FP64 RHS / psi_v(r) / dn plane kernels (full plane, or the compact layout when that does not fit)
+// LDS of the FP64 RHS / psi_v(r) / dn plane kernels (full plane, or the compact layout when that does not fit; the RHS
+// with lines in registers)
 size_t plane_fp64_lds(int N, int nza);
 
 // x pass, inverse: sphere coefficients of vectors vidx[b] (b < nvec) -> pencils.
@@ -59,11 +60,12 @@ void launch_xfwd(const FftGeom& g, const Z<T>* pen, const int* vidx, int nvec, Z
 // yz planes of the H apply: inverse, multiply by v_r (pre-scaled by 1/N^3), forward; in place.
 template <class T>
 void launch_plane_vloc(const FftGeom& g, Z<T>* pen, const int* vidx, int nvec, const T* v_r, hipStream_t st);
-// same operation, compact-LDS wave-local kernel; vt = V_loc as [x][z][y]
+// same operation with only the active z lines in LDS; vt = V_loc as [x][z][y]. Whole lines in registers on even grids whose
+// sphere reaches far enough, else (and with prefetch) per-wave transforms
 template <class T>
 void launch_plane_hw(const FftGeom& g, Z<T>* pen, const int* vidx, int nvec, const T* vt, bool prefetch,
                      hipStream_t st);
-size_t plane_hw_lds(int N, int nza, bool fp64);  // its LDS bytes per workgroup
+size_t plane_hw_lds(int N, int nza, bool fp64);  // LDS bytes per workgroup of the largest of its kernels
 // yz planes of the right-hand sides of a batch of bands [v0, v0 + nb) x fields [i0, i0 + npert), solve
 // s = (i - i0) nb + (v - v0) (band[s], pert[s] give the same): pencils[s] = forward planes of
 // psi_r[v] * dv[i].

@@ -158,7 +158,8 @@ struct stern_system {
   // static device data
   DBuf col_start, col_len, col_xmin, col_pos, zl, ycol, ymax, g2h, tw64, tw32, v_r, v_r32, v_t, v_t32, kb, perm;
   DBuf iperm;  // [npw_pad] canonical index of each column-order coefficient, -1 in the padding
-  // yz-plane kernel of the H apply per precision: 0 full-plane, 1 compact wave-local
+  // yz-plane kernel of the H apply per precision: 0 the full plane in LDS, 1 the active lines only (whole lines in
+  // registers on even grids, else per-wave transforms), 2 per-wave transforms with the next pair's loads ahead
   int plane_var64 = 1, plane_var32 = 1;
   // split-K workgroup targets of the FP64 and split-BF16 reduces (0 = default)
   int gemm64_wg = 0, gemm16_wg = 0;
@@ -403,6 +404,7 @@ double plane_flops(const stern_system* S) {
   return N * ((2.0 * nza + 2.0 * N) * 5.0 * N * std::log2(N) + 2.0 * N * N);
 }
 
+// the FFT stage of the H apply: out = (|G|^2/2 + V_loc - eps_s) in on rows list
 int apply_local_rows(stern_system* S, const Z64* in, Z64* out, const int* list, int n, const double* eps_rows) {
   if (n <= 0) return 0;
   const FftGeom g = S->geom();
@@ -463,9 +465,6 @@ int apply_pc_update(stern_system* S, Z64* Z, Z64* P, const double* beta, const i
                 [&] { launch_zgemm_expand2(r, ZRows{}, Z, K, list, n, K, S->stream, P, beta); }));
   return 0;
 }
-
-// the FFT stage of the H apply: out = (|G|^2/2 + V_loc - eps_s) in on rows list
-int apply_local_rows(stern_system* S, const Z64* in, Z64* out, const int* list, int n, const double* eps_rows);
 
 // out = P_c (H - eps_s) in on rows list: out_loc + sum_a P_c beta_a D <beta_a|in> - sum_b psi_b <psi_b|out_loc>, with
 // P_c beta_a formed once per occupied set, so the two reduces are independent of each other and one reduce,
