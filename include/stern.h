@@ -411,7 +411,8 @@ int stern_model_fit_step(stern_model* m, int Nc, int n, const float* in, const f
  *                        transforms with the next pair's loads issued ahead
  *   STERN_TUNE_PLANE32   the same for the FP32 H apply of the mixed inner solve
  *   STERN_TUNE_GEMM64_WG workgroups the split-K FP64 reduces (Psi^H Y, B^H Y) aim
- *                        for; 0 = built-in default (2048)
+ *                        for with more than 48 columns (to the nearest split that fills
+ *                        the card's last round); 0 = built-in default (2048)
  *   STERN_TUNE_GEMM16_WG the same for the split-BF16 reduces; 0 = default (512)
  *   STERN_TUNE_GEMM16_EXPAND tile of the split-BF16 expand (Y += Psi C, B D P):
  *                        0 = 256 x 128 per workgroup of 8 waves, 1 = 128 x 128 of

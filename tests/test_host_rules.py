@@ -1,6 +1,7 @@
 """Host rules of the kernel launches, through the library's own functions (no GPU): the LDS that the yz kernels are gated
-by."""
+by, and the split factors of the reduces."""
 import ctypes
+import math
 import os
 
 import pytest
@@ -29,3 +30,27 @@ def test_plane_gate_covers_the_kernel_with_lines_in_registers(N, fp64, vectors):
     assert need <= lds(N, nza, fp64) and need <= 160 * 1024
     if fp64 and N != 96:  # there the right-hand sides take the full plane
         assert rhs(N, nza) >= lines
+
+
+def choose_nsplit(*args):
+    return rule("_ZN5stern13choose_nsplitEiiii", ctypes.c_int, *[ctypes.c_int] * 4)(*args)
+
+
+@pytest.mark.parametrize("target", [256, 1024, 2048, 4096])
+@pytest.mark.parametrize("M,K", [(64, 576), (128, 16896), (1024, 91072)])
+def test_tuned_reduces_keep_the_rules(M, K, target):
+    """A workgroup target fills its last round as the default does, and few columns keep a count of their own."""
+    bound = rule("_ZN5stern12nsplit_boundEiiii", ctypes.c_int, *[ctypes.c_int] * 4)
+
+    def fill(ncols, ns):
+        rounds = (M // 64) * math.ceil(ncols / 64) * ns / 1024
+        return rounds / math.ceil(rounds)
+
+    for n in (1, 16, 17, 48):
+        assert choose_nsplit(M, n, K, target) == choose_nsplit(M, n, K, 0)
+    for n in (49, 64, 200, 517, 1000, 4096):
+        b, ns = bound(M, n, K, target), choose_nsplit(M, n, K, target)
+        assert b // 2 <= ns <= b and ns >= 1
+        assert fill(n, ns) >= max(fill(n, k) for k in range(b, b // 2, -1)) - 0.02 * (b - b // 2)
+        assert fill(n, ns) >= fill(n, b)
+        assert target != 2048 or ns == choose_nsplit(M, n, K, 0)  # the default's target, by name
