@@ -452,20 +452,20 @@ int nsplit_bound(int M_pad, int ncols, int K, int target) {
   return ns;
 }
 
-// A split-K reduce's workgroups all take the same time, and kGemm64Resident of them run at once (4 waves
-// per SIMD): a factor that leaves the last round nearly empty wastes it. 517 columns of M = 1,024, K = 91,072 in 15
+// A split-K reduce's workgroups all take the same time, and kGemm64PerCu of them run at once on a CU (4 waves
+// per SIMD), 1,024 on 256 CUs: a factor that leaves the last round nearly empty wastes it. 517 columns of M = 1,024, K = 91,072 in 15
 // splits are 2,160 workgroups, three rounds for 2.1; in 14 they are 2,016, two: 8.3 -> 7.6 ms (7.2 ms with the last block of columns
 // at half its products).
-constexpr int kGemm64Resident = 1024;
+constexpr int kGemm64PerCu = 4;
 
-int choose_nsplit(int M_pad, int ncols, int K, int target) {
+int choose_nsplit(int M_pad, int ncols, int K, int target, int n_cu) {
   const int bound = nsplit_bound(M_pad, ncols, K, target);
   if (ncols > kFewCols) {
     const int base = (M_pad / 64) * ((ncols + 63) / 64);
     int best = bound;
     double fill = 0.0;
     for (int ns = bound; 2 * ns > bound; --ns) {
-      const double rounds = (double)base * ns / kGemm64Resident, f = rounds / std::ceil(rounds);
+      const double rounds = (double)base * ns / (kGemm64PerCu * n_cu), f = rounds / std::ceil(rounds);
       if (f > fill + 0.02) {
         fill = f;
         best = ns;

@@ -528,7 +528,7 @@ __global__ __launch_bounds__(256) void k_sum_proj(const Z32* __restrict__ cp_a, 
 
 }  // namespace
 
-int choose_nsplit_bf16(int M_pad, int ncols, int K, int target) {
+int choose_nsplit_bf16(int M_pad, int ncols, int K, int target, int) {
   if (target <= 0) target = kBf16TargetGroups;
   const int base = ((M_pad + kWM - 1) / kWM) * ((ncols + kWN - 1) / kWN);
   // at most `target` workgroups: one fills a CU (128 KiB of LDS), so 515 for 512 would be a third round
@@ -584,7 +584,7 @@ void launch_sum_parts32(const Z32* cpart, int nsplit, int ncols, int M_pad, floa
 }
 
 void launch_expand_bf16(const __bf16* ATh, const __bf16* ATl, int M_pad, const __bf16* Cs, Z32* Y, int ldy,
-                        const int* yidx, int ncols, int K, int variant, hipStream_t st, Z32* P, const double* beta,
+                        const int* yidx, int ncols, int K, int variant, int n_cu, hipStream_t st, Z32* P, const double* beta,
                         const int* live) {
   if (ncols <= 0) return;
   // linear grid: ceil(row blocks / 8) groups x 8 XCD slots x column blocks
@@ -602,7 +602,7 @@ void launch_expand_bf16(const __bf16* ATh, const __bf16* ATl, int M_pad, const _
   } else if (ncols <= 64) {  // few columns: 64 x 64 tile, 8 waves of 16 x 32, for 4 times the workgroups
     if (P) go(k_expand_bf16s<1, 2, 2, true>, 64, 64, 512);
     else go(k_expand_bf16s<1, 2, 2, false>, 64, 64, 512);
-  } else if ((long)((K + 255) / 256) * ((ncols + 127) / 128) < 384) {
+  } else if ((long)((K + 255) / 256) * ((ncols + 127) / 128) * 2 < 3 * n_cu) {
     // fewer tiles than 1.5 per CU: 128 x 128, 8 waves of 32 x 64
     if (P) go(k_expand_bf16s<2, 4, 2, true>, 128, 128, 512);
     else go(k_expand_bf16s<2, 4, 2, false>, 128, 128, 512);

@@ -112,7 +112,7 @@ void launch_zgemm_expand2(const ZRows& s0, const ZRows& s1, Z64* Y, int ldy, con
                           hipStream_t st, Z64* P, const double* beta);
 // split-K factor for a reduce of ncols columns aiming at `target` workgroups (<= 0: default), and the factor
 // of the 64-column tile, by which the allocation-free entry point states its limit
-int choose_nsplit(int M_pad, int ncols, int K, int target);
+int choose_nsplit(int M_pad, int ncols, int K, int target, int n_cu);
 int nsplit_bound(int M_pad, int ncols, int K, int target);
 
 // ---- CG vector kernels; one workgroup per solve s = act[b] ----
@@ -240,7 +240,7 @@ void launch_row_norm2(const Z64* y, int ld, int n, double* out, hipStream_t st);
 void launch_outer_init(const CgState& s, const int* act, int n, double cut, hipStream_t st);
 void launch_fill_zero32(Z32* p, size_t n, hipStream_t st);
 
-int choose_nsplit_bf16(int M_pad, int ncols, int K, int target);
+int choose_nsplit_bf16(int M_pad, int ncols, int K, int target, int n_cu);
 // hi/lo BF16 split of complex rows A [M][K] into [M][2K] and transposed [K][2M] layouts
 void launch_split_bf16(const Z64* A, int M, int K, __bf16* hi, __bf16* lo, __bf16* thi, __bf16* tlo, hipStream_t st);
 // the same into rows [row0, row0 + M) of a split matrix of Mt rows (row layout skipped when hi is null)
@@ -262,7 +262,7 @@ void launch_sum_parts32(const Z32* cpart, int nsplit, int ncols, int M_pad, floa
 // variant 0: 256 x 128 tiles of 8 waves, 1: 128 x 128 tiles of 16 waves, 2: 128 x 128 tiles of 8 waves.
 // With P: Y is not written, P[s] = (Y[s] + A C) + beta[s] P[s] for s = yidx[n] instead.
 void launch_expand_bf16(const __bf16* ATh, const __bf16* ATl, int M_pad, const __bf16* Cs, Z32* Y, int ldy,
-                        const int* yidx, int ncols, int K, int variant, hipStream_t st, Z32* P = nullptr,
+                        const int* yidx, int ncols, int K, int variant, int n_cu, hipStream_t st, Z32* P = nullptr,
                         const double* beta = nullptr, const int* live = nullptr);
 
 // ---- TDDFT Liouville apply and its block solve (tddft.hip, cg.hip) ----
@@ -279,10 +279,10 @@ void launch_grid_mul(const Z64* v_r, const Z64* psi_r, int n_exc, int nb, size_t
 constexpr int kExchBands = 4;
 constexpr int kExchScr = 16;  // potentials that launch_exch_block takes in registers
 // pc[pair][a] = scale c[a] N^-3 sum_j w[a][j] conj(psi_w[j]) psi_v[j] for n real potentials w; parts: scratch of
-// scr_proj_stretches(v0, nv, n, n3) * pairs * n values
-void launch_scr_proj(const Z64* psi_r, const double* scr, const double* c, int n, int v0, int nv, size_t n3,
+// scr_proj_stretches(v0, nv, n, n3, n_cu) * pairs * n values
+void launch_scr_proj(const Z64* psi_r, const double* scr, const double* c, int n, int v0, int nv, size_t n3, int n_cu,
                      double scale, Z64* parts, Z64* pc, hipStream_t st);
-int scr_proj_stretches(int v0, int nv, int n, size_t n3);
+int scr_proj_stretches(int v0, int nv, int n, size_t n3, int n_cu);
 // tau[r] += sum_a w[a] pc[r][a]
 void launch_scr_add(Z64* tau, const double* w, const Z64* pc, int n, int nrows, size_t n3, hipStream_t st);
 // for every pair: acc[e nb + v] += tau a_r[e nb + w] and, w < v, acc[e nb + w] += conj(tau) a_r[e nb + v];

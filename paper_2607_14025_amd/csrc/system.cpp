@@ -382,7 +382,7 @@ int apply_pc_rows(stern_system* S, Z64* Y, const int* list, int n) {
   if (n <= 0) return 0;
   const int K = S->hb.npw_pad;
   const double npw = S->hb.npw, m = S->n_occ, zb = sizeof(Z64);
-  const int ns = choose_nsplit(S->nocc_pad, n, K, S->gemm64_wg);
+  const int ns = choose_nsplit(S->nocc_pad, n, K, S->gemm64_wg, S->n_cu);
   CHECKED(timed(S, STERN_K_PC_REDUCE, zb * npw * (n + m), 8.0 * m * npw * n, [&] {
     launch_zgemm_reduce(S->psi.as<Z64>(), S->nocc_pad, Y, K, list, n, K, S->cpart.as<Z64>(), ns, S->stream, S->n_occ);
   }));
@@ -433,7 +433,7 @@ int apply_h_rows(stern_system* S, const Z64* in, Z64* out, const int* list, int 
   const double zb = sizeof(Z64), npw = S->hb.npw;
   if (S->n_atoms > 0) {
     const double na = S->n_atoms;
-    const int ns = choose_nsplit(S->natoms_pad, n, K, S->gemm64_wg);
+    const int ns = choose_nsplit(S->natoms_pad, n, K, S->gemm64_wg, S->n_cu);
     CHECKED(timed(S, STERN_K_KB_REDUCE, zb * npw * (n + na), 8.0 * na * npw * n, [&] {
       launch_zgemm_reduce(S->kb.as<Z64>(), S->natoms_pad, in, K, list, n, K, S->cpart.as<Z64>(), ns, S->stream,
                           S->n_atoms);
@@ -455,7 +455,7 @@ int apply_pc_update(stern_system* S, Z64* Z, Z64* P, const double* beta, const i
   if (n <= 0) return 0;
   const int K = S->hb.npw_pad;
   const double npw = S->hb.npw, m = S->n_occ, zb = sizeof(Z64);
-  const int ns = choose_nsplit(S->nocc_pad, n, K, S->gemm64_wg);
+  const int ns = choose_nsplit(S->nocc_pad, n, K, S->gemm64_wg, S->n_cu);
   const ZRows r{S->psi.as<Z64>(), Z, S->cpart.as<Z64>(), S->cmat.as<Z64>(), S->nocc_pad, S->n_occ, -1.0};
   CHECKED(timed(S, STERN_K_PC_REDUCE, zb * npw * (n + m), 8.0 * m * npw * n,
                 [&] { launch_zgemm_reduce2(r, ZRows{}, K, list, n, K, ns, S->stream); }));
@@ -475,7 +475,7 @@ int apply_hproj_rows(stern_system* S, const Z64* in, Z64* out, const int* list, 
   if (S->n_atoms == 0) return apply_pc_rows(S, out, list, n);
   const int K = S->hb.npw_pad, Ma = S->natoms_pad, Mb = S->nocc_pad;
   const double npw = S->hb.npw, na = S->n_atoms, m = S->n_occ, zb = sizeof(Z64);
-  const int ns = choose_nsplit(Ma + Mb, n, K, S->gemm64_wg);
+  const int ns = choose_nsplit(Ma + Mb, n, K, S->gemm64_wg, S->n_cu);
   Z64 *cp = S->cpart.as<Z64>(), *cm = S->cmat.as<Z64>();
   ZRows a{S->kb.as<Z64>(), in, cp, cm, Ma, S->n_atoms, S->cell.D};
   const ZRows b{S->psi.as<Z64>(), out, cp + (size_t)ns * n * Ma, cm + (size_t)n * Ma, Mb, S->n_occ, -1.0};
@@ -500,7 +500,7 @@ int apply_psi32_rows(stern_system* S, const Z32* X, Z32* Y, const int* list, int
   if (n <= 0) return 0;
   const int K = S->hb.npw_pad;
   const double npw = S->hb.npw, m = S->n_occ;
-  const int ns = choose_nsplit_bf16(S->nocc_pad, n, K, S->gemm16_wg);
+  const int ns = choose_nsplit_bf16(S->nocc_pad, n, K, S->gemm16_wg, S->n_cu);
   Z32* cp = S->cpart.as<Z32>();
   __bf16* cm = S->cmat.as<__bf16>();
   CHECKED(timed(S, STERN_K_GEMM_BF16, 8.0 * npw * (n + m), 8.0 * m * npw * n, [&] {
@@ -511,7 +511,7 @@ int apply_psi32_rows(stern_system* S, const Z32* X, Z32* Y, const int* list, int
                 [&] { launch_sum_parts32(cp, ns, n, S->nocc_pad, scale, cm, S->stream, S->live); }));
   CHECKED(timed(S, STERN_K_GEMM_BF16, 8.0 * npw * (2.0 * n + m), 8.0 * m * npw * n, [&] {
     launch_expand_bf16(S->psiT_hi.as<__bf16>(), S->psiT_lo.as<__bf16>(), S->nocc_pad, cm, Y, K, list, n, K,
-                       S->gemm16_expand, S->stream, nullptr, nullptr, S->live);
+                       S->gemm16_expand, S->n_cu, S->stream, nullptr, nullptr, S->live);
   }));
   return 0;
 }
@@ -522,7 +522,7 @@ int apply_pc32_update(stern_system* S, const Z32* Z, Z32* P, const double* beta,
   if (n <= 0) return 0;
   const int K = S->hb.npw_pad;
   const double npw = S->hb.npw, m = S->n_occ;
-  const int ns = choose_nsplit_bf16(S->nocc_pad, n, K, S->gemm16_wg);
+  const int ns = choose_nsplit_bf16(S->nocc_pad, n, K, S->gemm16_wg, S->n_cu);
   Z32* cp = S->cpart.as<Z32>();
   __bf16* cm = S->cmat.as<__bf16>();
   CHECKED(timed(S, STERN_K_GEMM_BF16, 8.0 * npw * (n + m), 8.0 * m * npw * n, [&] {
@@ -533,7 +533,7 @@ int apply_pc32_update(stern_system* S, const Z32* Z, Z32* P, const double* beta,
                 [&] { launch_sum_parts32(cp, ns, n, S->nocc_pad, -1.f, cm, S->stream, S->live); }));
   CHECKED(timed(S, STERN_K_GEMM_BF16, 8.0 * npw * (3.0 * n + m), 8.0 * m * npw * n, [&] {
     launch_expand_bf16(S->psiT_hi.as<__bf16>(), S->psiT_lo.as<__bf16>(), S->nocc_pad, cm, const_cast<Z32*>(Z), K,
-                       list, n, K, S->gemm16_expand, S->stream, P, beta, S->live);
+                       list, n, K, S->gemm16_expand, S->n_cu, S->stream, P, beta, S->live);
   }));
   return 0;
 }
@@ -567,7 +567,7 @@ int apply_hproj32_rows(stern_system* S, const Z32* in, Z32* out, const int* list
   CHECKED(timed(S, STERN_K_X32, n * (pen + 2.0 * npw * zb), 0.0,
                 [&] { launch_xfwd<float>(g, pen32, list, n, out, 1, in, eps_rows, 0.0, S->stream); }));
   const int Ma = S->natoms_pad, Mb = S->nocc_pad;
-  const int ns_a = choose_nsplit_bf16(Ma, n, K, S->gemm16_wg), ns_b = choose_nsplit_bf16(Mb, n, K, S->gemm16_wg);
+  const int ns_a = choose_nsplit_bf16(Ma, n, K, S->gemm16_wg, S->n_cu), ns_b = choose_nsplit_bf16(Mb, n, K, S->gemm16_wg, S->n_cu);
   Z32 *cpa = S->cpart.as<Z32>(), *cpb = S->cpart2.as<Z32>();
   __bf16* cm = S->cmat.as<__bf16>();
   CHECKED(timed(S, STERN_K_GEMM_BF16, zb * npw * (n + na), 8.0 * na * npw * n, [&] {
@@ -583,7 +583,7 @@ int apply_hproj32_rows(stern_system* S, const Z32* in, Z32* out, const int* list
   }));
   CHECKED(timed(S, STERN_K_GEMM_BF16, zb * npw * (2.0 * n + na + m), 8.0 * (na + m) * npw * n, [&] {
     launch_expand_bf16(S->projT_hi.as<__bf16>(), S->projT_lo.as<__bf16>(), S->proj_m, cm, out, K, list, n, K,
-                       S->gemm16_expand, S->stream, nullptr, nullptr, S->live);
+                       S->gemm16_expand, S->n_cu, S->stream, nullptr, nullptr, S->live);
   }));
   return 0;
 }
@@ -608,7 +608,7 @@ int apply_h32_rows(stern_system* S, const Z32* in, Z32* out, const int* list, in
                 [&] { launch_xfwd<float>(g, pen32, list, n, out, 1, in, eps_rows, 0.0, S->stream); }));
   if (S->n_atoms > 0) {
     const double na = S->n_atoms;
-    const int ns = choose_nsplit_bf16(S->natoms_pad, n, K, S->gemm16_wg);
+    const int ns = choose_nsplit_bf16(S->natoms_pad, n, K, S->gemm16_wg, S->n_cu);
     Z32* cp = S->cpart.as<Z32>();
     __bf16* cm = S->cmat.as<__bf16>();
     CHECKED(timed(S, STERN_K_GEMM_BF16, zb * npw * (n + na), 8.0 * na * npw * n, [&] {
@@ -619,7 +619,7 @@ int apply_h32_rows(stern_system* S, const Z32* in, Z32* out, const int* list, in
                   [&] { launch_sum_parts32(cp, ns, n, S->natoms_pad, (float)S->cell.D, cm, S->stream, S->live); }));
     CHECKED(timed(S, STERN_K_GEMM_BF16, zb * npw * (2.0 * n + na), 8.0 * na * npw * n, [&] {
       launch_expand_bf16(S->kbT_hi.as<__bf16>(), S->kbT_lo.as<__bf16>(), S->natoms_pad, cm, out, K, list, n, K,
-                         S->gemm16_expand, S->stream, nullptr, nullptr, S->live);
+                         S->gemm16_expand, S->n_cu, S->stream, nullptr, nullptr, S->live);
     }));
   }
   return 0;
@@ -631,8 +631,8 @@ int apply_h32_rows(stern_system* S, const Z32* in, Z32* out, const int* list, in
 size_t cpart_capacity(const stern_system* S, int M_pad, int nmax, int K) {
   size_t best = 0;
   for (int n = 1; n <= nmax; n = n < 64 || n == nmax ? n + 1 : std::min(n + 64, nmax)) {
-    const size_t c = std::max((size_t)choose_nsplit(M_pad, n, K, S->gemm64_wg) * sizeof(Z64),
-                              (size_t)choose_nsplit_bf16(M_pad, n, K, S->gemm16_wg) * sizeof(Z32)) * n;
+    const size_t c = std::max((size_t)choose_nsplit(M_pad, n, K, S->gemm64_wg, S->n_cu) * sizeof(Z64),
+                              (size_t)choose_nsplit_bf16(M_pad, n, K, S->gemm16_wg, S->n_cu) * sizeof(Z32)) * n;
     if (c > best) best = c;
   }
   return best * M_pad;
@@ -1571,7 +1571,7 @@ int stern_set_occupied(stern_system* S, int n_occ, const double* psi, const doub
     CHECKED(S->pkb.ensure((size_t)Ma * K * sizeof(Z64)));
     Z64* pkb = S->pkb.as<Z64>();
     HIPOK(hipMemcpyAsync(pkb, S->kb.p, (size_t)Ma * K * sizeof(Z64), hipMemcpyDeviceToDevice, st));
-    const int ns = choose_nsplit(Mb, Ma, K, S->gemm64_wg);
+    const int ns = choose_nsplit(Mb, Ma, K, S->gemm64_wg, S->n_cu);
     CHECKED(S->cpart.ensure((size_t)ns * Ma * Mb * sizeof(Z64)));
     CHECKED(S->cmat.ensure((size_t)Ma * Mb * sizeof(Z64)));
     launch_zgemm_reduce(S->psi.as<Z64>(), Mb, S->kb.as<Z64>(), K, nullptr, Ma, K, S->cpart.as<Z64>(), ns, st, Mb);
@@ -1756,7 +1756,7 @@ static int liouville_rows(stern_system* S, const Z64* A, Z64* out, int n_exc) {
     if (S->n_scr > 0) {  // the pairs' coefficients, then the partial sums they come from
       size_t parts = 0;
       for (int v0 = 0; v0 < nb; v0 += vb)
-        parts = std::max(parts, (size_t)scr_proj_stretches(v0, std::min(vb, nb - v0), S->n_scr, n3));
+        parts = std::max(parts, (size_t)scr_proj_stretches(v0, std::min(vb, nb - v0), S->n_scr, n3, S->n_cu));
       CHECKED(S->scr_proj.ensure((parts + 1) * vb * nb * S->n_scr * sizeof(Z64)));
     }
     return 0;
@@ -1807,7 +1807,7 @@ static int liouville_rows(stern_system* S, const Z64* A, Z64* out, int n_exc) {
         launch_plane_pair_fwd(S->geom_d(), S->psi_r.as<Z64>(), v0, pairs, 1.0 / hb.omega, S->lv_pend.as<Z64>(), st);
         potential_of_pencils(S, tau, pairs, 2.0 * kPi * S->lv_alpha);  // alpha V[rho]
         if (S->n_scr > 0) {
-          launch_scr_proj(S->psi_r.as<Z64>(), S->scr_w.as<double>(), S->scr_c.as<double>(), S->n_scr, v0, nv, n3,
+          launch_scr_proj(S->psi_r.as<Z64>(), S->scr_w.as<double>(), S->scr_c.as<double>(), S->n_scr, v0, nv, n3, S->n_cu,
                           1.0 / hb.omega, pc + (size_t)vb * nb * S->n_scr, pc, st);
           if (!scr_regs) launch_scr_add(tau, S->scr_w.as<double>(), pc, S->n_scr, pairs, n3, st);
         }
@@ -1994,7 +1994,7 @@ int stern_liouville_solve(stern_system* S, int n_exc, const double* b, double* z
 // reduce), on the host
 static int dav_vh_x(stern_system* S, const Z64* V, int cap, const Z64* X, int nx, int Lt, std::vector<Z64>& C) {
   hipStream_t st = S->stream;
-  const int ns = choose_nsplit(cap, nx, Lt, S->gemm64_wg);
+  const int ns = choose_nsplit(cap, nx, Lt, S->gemm64_wg, S->n_cu);
   CHECKED(S->dv_part.ensure((size_t)ns * nx * cap * sizeof(Z64)));
   CHECKED(S->dv_cm.ensure((size_t)nx * cap * sizeof(Z64)));
   launch_zgemm_reduce(V, cap, X, Lt, nullptr, nx, Lt, S->dv_part.as<Z64>(), ns, st, cap);
@@ -2282,7 +2282,7 @@ int stern_apply_pc_noalloc(stern_system* S, int n_vec, const double* c, double* 
   if (n_vec == 0) return STERN_OK;
   if (!c || !out) return fail(STERN_ERR_INVALID_ARG, "NULL array");
   const int npw = S->hb.npw, K = S->hb.npw_pad, M = S->nocc_pad;
-  const int ns = choose_nsplit(M, n_vec, K, S->gemm64_wg);
+  const int ns = choose_nsplit(M, n_vec, K, S->gemm64_wg, S->n_cu);
   // scratch: rows in column order [n][K], split-K partials [ns][n][M], C [n][M]
   const size_t rows_b = (size_t)n_vec * K * sizeof(Z64);
   const size_t part_b = (size_t)ns * n_vec * M * sizeof(Z64);

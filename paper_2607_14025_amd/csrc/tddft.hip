@@ -285,15 +285,15 @@ void launch_exch_block(const Z64* tau, const Z64* a_r, int n_exc, int nb, int v0
   else with(std::integral_constant<int, 0>{});
 }
 
-int scr_proj_stretches(int v0, int nv, int n, size_t n3) {
+int scr_proj_stretches(int v0, int nv, int n, size_t n3, int n_cu) {
   const int groups = (v0 + nv) * ((n + kProjA - 1) / kProjA);  // about 4 workgroups per CU, 4 points a thread or more
-  const size_t want = std::max(1, 1024 / std::max(1, groups));
+  const size_t want = std::max(1, 4 * n_cu / std::max(1, groups));
   return (int)std::max<size_t>(1, std::min(want, n3 / (4 * kGridThreads)));
 }
-void launch_scr_proj(const Z64* psi_r, const double* scr, const double* c, int n, int v0, int nv, size_t n3,
+void launch_scr_proj(const Z64* psi_r, const double* scr, const double* c, int n, int v0, int nv, size_t n3, int n_cu,
                      double scale, Z64* parts, Z64* pc, hipStream_t st) {
   if (n <= 0 || nv <= 0) return;
-  const int ns = scr_proj_stretches(v0, nv, n, n3), npairs = nv * v0 + nv * (nv + 1) / 2, total = npairs * n;
+  const int ns = scr_proj_stretches(v0, nv, n, n3, n_cu), npairs = nv * v0 + nv * (nv + 1) / 2, total = npairs * n;
   const size_t stretch = (n3 + ns - 1) / ns;
   k_scr_proj<kExchBands><<<dim3(v0 + nv, ns, (n + kProjA - 1) / kProjA), kGridThreads, 0, st>>>(
       psi_r, scr, n, v0, nv, n3, stretch, npairs, parts);

@@ -32,8 +32,8 @@ def test_plane_gate_covers_the_kernel_with_lines_in_registers(N, fp64, vectors):
         assert rhs(N, nza) >= lines
 
 
-def choose_nsplit(*args):
-    return rule("_ZN5stern13choose_nsplitEiiii", ctypes.c_int, *[ctypes.c_int] * 4)(*args)
+def choose_nsplit(*args, n_cu=256):
+    return rule("_ZN5stern13choose_nsplitEiiiii", ctypes.c_int, *[ctypes.c_int] * 5)(*args, n_cu)
 
 
 @pytest.mark.parametrize("target", [256, 1024, 2048, 4096])
@@ -54,3 +54,16 @@ def test_tuned_reduces_keep_the_rules(M, K, target):
         assert fill(n, ns) >= max(fill(n, k) for k in range(b, b // 2, -1)) - 0.02 * (b - b // 2)
         assert fill(n, ns) >= fill(n, b)
         assert target != 2048 or ns == choose_nsplit(M, n, K, 0)  # the default's target, by name
+
+
+@pytest.mark.parametrize("n_cu", [32, 64, 128])
+def test_rounds_are_those_of_the_device(n_cu):
+    """A device of fewer CUs (a partition) runs fewer workgroups at once: the split fills the last round there."""
+    M, K = 1024, 91072
+    for n in (64, 200, 517, 1000):
+        base = (M // 64) * math.ceil(n / 64)
+        fill = lambda ns: base * ns / (4 * n_cu) / math.ceil(base * ns / (4 * n_cu))
+        assert fill(choose_nsplit(M, n, K, 0, n_cu=n_cu)) >= fill(choose_nsplit(M, n, K, 0)) - 0.02
+    stretches = rule("_ZN5stern18scr_proj_stretchesEiiimi", ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_size_t,
+                     ctypes.c_int)
+    assert stretches(0, 1, 8, 48 ** 3, n_cu) == max(1, min(4 * n_cu, 48 ** 3 // 1024))
