@@ -528,16 +528,17 @@ __global__ __launch_bounds__(256) void k_sum_proj(const Z32* __restrict__ cp_a, 
 
 }  // namespace
 
-int choose_nsplit_bf16(int M_pad, int ncols, int K, int target, int) {
+int choose_nsplit_bf16(int M_pad, int ncols, int K, int target, int n_cu) {
   if (target <= 0) target = kBf16TargetGroups;
   const int base = ((M_pad + kWM - 1) / kWM) * ((ncols + kWN - 1) / kWN);
   // at most `target` workgroups: one fills a CU (128 KiB of LDS), so 515 for 512 would be a third round
   int ns = target / base;
-  // chunks of 128 k or more: 4 steps, after which splitting further costs more in the sums than it saves
-  const int maxs = K / 128 > 0 ? K / 128 : 1;
-  if (ns > maxs) ns = maxs;
-  if (ns < 1) ns = 1;
-  return ns;
+  // chunks of 256 k or more; finer ones, down to 128 k (4 steps), where they run in the same rounds over the CUs. A
+  // round more costs more than the shorter chunks save: 512 columns of M = 64, K = 12,352 (averages over an
+  // iteration's reduces) in 192 workgroups 27.3 us, in 384 37.0, in 256 25.6.
+  const int coarse = std::max(1, K / 256), rounds = (base * coarse + n_cu - 1) / n_cu;
+  ns = std::min(ns, std::min(std::max(1, K / 128), std::max(coarse, rounds * n_cu / base)));
+  return std::max(1, ns);
 }
 
 void launch_split_bf16(const Z64* A, int M, int K, __bf16* hi, __bf16* lo, __bf16* thi, __bf16* tlo, hipStream_t st) {
@@ -583,6 +584,11 @@ void launch_sum_parts32(const Z32* cpart, int nsplit, int ncols, int M_pad, floa
     k_sum_split<1><<<(total + 255) / 256, 256, 0, st>>>(cpart, nsplit, ncols, M_pad, scale, Cs, live);
 }
 
+// Whether tiles of 128 rows end sooner than `tiles` of 256, which take 1.8 times as long each: a round of 256 x 128 for two
+// of 128 x 128 is a loss, a round less of the same size a gain. M = 64, 512 columns, K = 12,352, 196 tiles: 37.4 us
+// against 40.2; 102 tiles: 33.6 against 21.7; 343: 69.8 against 60.8; 462: 104.7 against 106.4.
+static bool half_tiles(long tiles, int n_cu) { return 2 * tiles <= n_cu || (tiles > n_cu && 2 * tiles < 3 * n_cu); }
+
 void launch_expand_bf16(const __bf16* ATh, const __bf16* ATl, int M_pad, const __bf16* Cs, Z32* Y, int ldy,
                         const int* yidx, int ncols, int K, int variant, int n_cu, hipStream_t st, Z32* P, const double* beta,
                         const int* live) {
@@ -602,8 +608,7 @@ void launch_expand_bf16(const __bf16* ATh, const __bf16* ATl, int M_pad, const _
   } else if (ncols <= 64) {  // few columns: 64 x 64 tile, 8 waves of 16 x 32, for 4 times the workgroups
     if (P) go(k_expand_bf16s<1, 2, 2, true>, 64, 64, 512);
     else go(k_expand_bf16s<1, 2, 2, false>, 64, 64, 512);
-  } else if ((long)((K + 255) / 256) * ((ncols + 127) / 128) * 2 < 3 * n_cu) {
-    // fewer tiles than 1.5 per CU: 128 x 128, 8 waves of 32 x 64
+  } else if (half_tiles((long)((K + 255) / 256) * ((ncols + 127) / 128), n_cu)) {  // 128 x 128, 8 waves of 32 x 64
     if (P) go(k_expand_bf16s<2, 4, 2, true>, 128, 128, 512);
     else go(k_expand_bf16s<2, 4, 2, false>, 128, 128, 512);
   } else {  // 256 x 128 tile, 8 waves of 64 x 64

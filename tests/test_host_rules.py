@@ -67,3 +67,22 @@ def test_rounds_are_those_of_the_device(n_cu):
     stretches = rule("_ZN5stern18scr_proj_stretchesEiiimi", ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_size_t,
                      ctypes.c_int)
     assert stretches(0, 1, 8, 48 ** 3, n_cu) == max(1, min(4 * n_cu, 48 ** 3 // 1024))
+
+
+@pytest.mark.parametrize("n_cu", [256, 64])
+def test_bf16_reduces_add_no_round(n_cu):
+    """Chunks finer than 256 k, 128 k at the finest, only where they run in the rounds over the CUs that chunks of 256 k
+    take, and never more workgroups than the target."""
+    nsplit = rule("_ZN5stern18choose_nsplit_bf16Eiiiii", ctypes.c_int, *[ctypes.c_int] * 5)
+    finer = 0
+    for M in (64, 128, 256, 1024):
+        for K in (64, 576, 5504, 7488, 12352, 16896, 27136, 38912, 91072):
+            for n in (1, 96, 128, 129, 240, 512, 640, 864, 1024, 4096):
+                base, ns = math.ceil(M / 128) * math.ceil(n / 128), nsplit(M, n, K, 0, n_cu)
+                coarse = max(1, K // 256)
+                assert 1 <= ns <= max(1, 512 // base) and ns <= max(1, K // 128)
+                if base * coarse <= 512:
+                    assert math.ceil(base * ns / n_cu) <= math.ceil(base * coarse / n_cu)
+                    assert ns >= min(coarse, 512 // base)
+                finer += ns > coarse
+    assert finer > 0
