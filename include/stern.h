@@ -433,7 +433,9 @@ int stern_tunable(stern_system* sys, int which, int value);
  * synthetic rows (HIP events on the system's stream; needs set_occupied) and
  * keeps the fastest. With cache_path != NULL, choices are read from / appended
  * to that text file, keyed by (GPU arch, grid, active z lines, N_pw, padded
- * N_occ, padded atom count, n_vec); a complete hit times nothing. chosen
+ * N_occ, padded atom count, n_vec, version of the kernels that the values
+ * stand for: choices of another version are found anew); a complete hit times
+ * nothing. chosen
  * (optional, STERN_NTUNE ints) receives the values. Returns the number of
  * candidates timed. Synchronous; uses the apply workspace. */
 int stern_autotune(stern_system* sys, int n_vec, const char* cache_path, int* chosen);

@@ -2965,6 +2965,10 @@ int stern_pdep_davidson(stern_system* S, const stern_pdep_opts* o, double* eig, 
 
 // ------------------------------------------------------------- autotuner ----
 
+// What the tunables' values stand for, in the cache's key: 2 since plane variant 1 holds lines in registers and the workgroup
+// targets fill their last round. Choices found between other kernels are found anew.
+constexpr int kTuneVersion = 2;
+
 const char* stern_autotune_report(void) { return g_tune_report.c_str(); }
 
 int stern_tunable(stern_system* S, int which, int value) {
@@ -3008,8 +3012,8 @@ int stern_autotune(stern_system* S, int n_vec, const char* cache_path, int* chos
   hipDeviceProp_t prop;
   HIPOK(hipGetDeviceProperties(&prop, S->device));
   char key[512];
-  std::snprintf(key, sizeof key, "%s N=%d nza=%d npw=%d nocc_pad=%d natoms_pad=%d nvec=%d", prop.gcnArchName,
-                S->hb.N, S->hb.nza, S->hb.npw, S->nocc_pad, S->natoms_pad, n_vec);
+  std::snprintf(key, sizeof key, "%s N=%d nza=%d npw=%d nocc_pad=%d natoms_pad=%d nvec=%d kernels=%d", prop.gcnArchName,
+                S->hb.N, S->hb.nza, S->hb.npw, S->nocc_pad, S->natoms_pad, n_vec, kTuneVersion);
   int* slots[STERN_NTUNE] = {&S->plane_var64, &S->plane_var32, &S->gemm64_wg, &S->gemm16_wg, &S->gemm16_expand};
   // cached choices
   if (cache_path) {
