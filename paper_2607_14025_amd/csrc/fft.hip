@@ -760,13 +760,14 @@ __global__ __launch_bounds__(64 * W) void k_plane_hw(Z<T>* __restrict__ pen, con
 // Bound by the vector ALU: counters put it at 85% of the issue slots at N = 64 and 72 in FP32 (FP64
 // instructions take about twice the slots, and the share is the same), 70% at N = 128, where 200
 // registers leave two waves per SIMD. The scheduling barriers of fft_half.hpp hold the registers near
-// the 2 M of the line itself: without them the compiler needs twice as many and spills. Microseconds
-// for 1,024 vectors, against the two-stage kernel below (k_plane_hw):
-//     N     FP32           FP64             N     FP32           FP64
-//    24     96 (190)      140 (287)        72    1,270 (1,690)  2,480 (3,060)
-//    36    178 (370)      298 (690)        96    3,170 (4,040)  8,640 (10,080)
-//    48    346 (549)      738 (1,180)     108    5,550 (7,370) 11,890 (13,950)
-//    54    615 (903)    1,280 (1,550)     128    8,300 (9,880) 18,290 (23,280)
+// the 2 M of the line itself: without them the compiler needs twice as many and spills. Microseconds of the
+// kernel alone for 1,024 vectors, from a kernel trace, against the two-stage kernel below (k_plane_hw):
+//     N     FP32            FP64              N     FP32            FP64
+//    24     24 (124)        41 (176)         64    539 (675)     1,034 (1,450)
+//    32     56 (153)       101 (242)         72    803 (1,199)   1,626 (2,450)
+//    36     86 (280)       156 (471)         96  2,221 (3,408)   6,327 (8,483)
+//    48    217 (425)       411 (747)        108  3,589 (6,050)   9,015 (11,071)
+//    54    425 (626)       864 (1,014)      128  5,806 (7,569)  13,469 (17,971)
 // Odd N (9, 27, 81) has no two lanes to a line and stays with the two-stage kernel.
 template <int N, class T>
 struct PlaneHCfg {
@@ -912,7 +913,7 @@ constexpr size_t planem_lds_bytes(int nv, int nza) {
 
 // Pencils of vector i nb + b = forward planes of psi_r[v0 + b] * mul[i] (mul real: the right-hand sides of a
 // batch of bands and fields; complex: V psi of the Liouville apply). Workgroup (ix, b) takes nv fields i at a
-// time, as k_plane_half does with its vectors. 72^3, 128 bands x 16 fields: 3.05 -> 2.85 ms (full planes in
+// time, as k_plane_half does with its vectors. 72^3, 128 bands x 16 fields: 2.93 -> 2.63 ms (full planes in
 // LDS before); 128^3, 256 x 4: 17.1 -> 12.9 ms (four stages through LDS). V psi of 8 excitations x 128 bands at
 // 72^3: 1.83 ms, against 2.44 for the products on full grids and 2.13 for their transforms.
 template <int N, class MUL>

@@ -5,6 +5,11 @@
       results database; with the bench's log, the traced durations of the bench's timed
       launches of KERNEL against the bench's own HIP-event time per launch.
 
+  python3 -m paper_2607_14025_amd.rocprof_summary passes CSV TITLE PASSES [TOP] >> summary.md
+      kernel table of one pass from the kernel-trace CSV of a program that rests for 0.4 s or more
+      before its last PASSES passes: launches, time from the first to the last, time with no kernel
+      running, and the TOP (10) kernels by their share of it.
+
   python3 -m paper_2607_14025_amd.rocprof_summary traffic FETCH_CSV WRITE_CSV BENCH_LOG LABEL KERNEL
           TITLE FETCH_COMMAND WRITE_COMMAND [TRAFFIC_JSON] > summary.md
       HBM bytes per launch of one kernel from two --pmc runs (FETCH_SIZE, then WRITE_SIZE) of
@@ -85,6 +90,30 @@ def stats(db: str, title: str, cmd: str) -> str:
         if p < 0.005:
             continue
         out.append(f"| `{short_name(n)}` | {c} | {t:.0f} | {a:.1f} | {p:.2f}% |")  # the view is in us
+    return "\n".join(out) + "\n"
+
+
+def passes(csv_path: str, title: str, n: int, top: int = 10) -> str:
+    with open(csv_path, newline="") as fh:
+        rows = sorted((int(r["Start_Timestamp"]), int(r["End_Timestamp"]), r["Kernel_Name"]) for r in csv.DictReader(fh))
+    cut, end = 0, rows[0][1]
+    for i, (t0, t1, _) in enumerate(rows):
+        if t0 - end > 400e6:
+            cut = i
+        end = max(end, t1)
+    rows = rows[cut:]
+    end, idle, by_name = rows[0][0], 0, {}
+    for t0, t1, name in rows:
+        idle += max(0, t0 - end)
+        end = max(end, t1)
+        e = by_name.setdefault(short_name(name), [0, 0])
+        e[0] += 1
+        e[1] += t1 - t0
+    span = end - rows[0][0]
+    out = [f"## {title}\n", f"{len(rows) / n:.0f} launches, {span / n / 1e3:.1f} us, of which no kernel runs for {idle / n / 1e3:.1f} us "
+           f"({100.0 * idle / span:.1f}%) (mean of {n} passes).\n", "| kernel | launches | us a launch | us a pass | share |", "|---|---:|---:|---:|---:|"]
+    for name, (c, t) in sorted(by_name.items(), key=lambda x: -x[1][1])[:top]:
+        out.append(f"| `{name}` | {c / n:g} | {t / c / 1e3:.2f} | {t / n / 1e3:.1f} | {100.0 * t / span:.1f}% |")
     return "\n".join(out) + "\n"
 
 
@@ -308,6 +337,8 @@ def main(argv):
         sys.stdout.write(stats(argv[1], argv[2], argv[3]))
         if len(argv) >= 7:  # BENCH_LOG LABEL KERNEL: agreement with the bench's event timing
             sys.stdout.write("\n" + launch_agreement(argv[1], argv[4], argv[5], argv[6]))
+    elif len(argv) >= 4 and argv[0] == "passes":
+        sys.stdout.write("\n" + passes(argv[1], argv[2], int(argv[3]), *([int(argv[4])] if len(argv) > 4 else [])))
     elif len(argv) >= 9 and argv[0] == "traffic":
         sys.stdout.write(traffic(*argv[1:10]))
     elif len(argv) >= 5 and argv[0] == "sq":
