@@ -1740,8 +1740,10 @@ static int liouville_rows(stern_system* S, const Z64* A, Z64* out, int n_exc) {
   const FftGeom g = S->geom();
   const int Kd = S->hbd.npw_pad;
   const bool fused = liouville_fused(S);
-  // excitations at a time: what the pencils hold, or the full grids
-  const int ce = fused ? std::max(1, std::min({n_exc, S->ws_solves / nb, 65535 / nb})) : liouville_chunk(S, n_exc);
+  // excitations at a time: what the pencils hold with about 2 GB of densities and their potentials, or the full grids
+  const size_t rho_b = (n3 + (size_t)N * S->hbd.ncol_pad + Kd) * sizeof(Z64);
+  const int ce = fused ? std::max(1, std::min({n_exc, S->ws_solves / nb, 65535 / nb, (int)(((size_t)2 << 30) / rho_b)}))
+                       : liouville_chunk(S, n_exc);
   const bool exch = S->lv_alpha != 0.0 || S->n_scr > 0;
   if (!fused) CHECKED(S->lv_ar.ensure((size_t)ce * nb * n3 * sizeof(Z64)));
   CHECKED(S->lv_rho.ensure((size_t)ce * n3 * sizeof(Z64)));
